@@ -10,11 +10,11 @@
 // then needs no feature values: at a node with feature f, coalition S goes
 // right iff (S >> f & 1) ? dx : (bits >> b & 1).
 //
-// The walk kernel gives each lane a few coalitions (independent paths
-// interleaved so their node loads overlap) and walks every (background,
-// tree) pair in ascending order, summing leaf outputs in FP64. Node records
-// are 16 bytes; the records of the top levels are shared by all lanes of a
-// wave, the deeper ones sit in L1/L2 (a 200-tree depth-6 forest is 400 KB).
+// The walk kernels list, per block of coalitions and (background, tree) pair,
+// the few leaves its coalitions can reach, let each coalition pick its leaf
+// from that list and sum the leaf outputs in FP64 in ascending order of the
+// pairs. Node records are 16 bytes (a 200-tree depth-6 forest is 400 KB, held
+// in L2).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -73,64 +73,294 @@ prep_kernel(const int32_t* __restrict__ feature, const double* __restrict__ thre
   }
 }
 
-// KP coalitions per lane: S = (block * KP + j) * kThreads + lane-in-block.
-template <typename OutT, int KP>
-__global__ void __launch_bounds__(kThreads)
-walk_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
-            const int32_t* __restrict__ roots, int n_trees, int n_nodes, int n_bg,
-            int max_depth, int d, OutT* __restrict__ v) {
-  const uint32_t n_coal = 1u << d;
-  uint32_t S[KP];
-  double acc[KP];
-#pragma unroll
-  for (int j = 0; j < KP; ++j) {
-    S[j] = ((uint32_t)blockIdx.x * KP + j) * kThreads + threadIdx.x;
-    acc[j] = 0.0;
-  }
-  const uint32_t S_any = S[0] < n_coal ? S[0] : 0;
-#pragma unroll
-  for (int j = 0; j < KP; ++j)
-    if (S[j] >= n_coal) S[j] = S_any;          // walk a valid coalition, store nothing
-  const int n_chunks = (n_bg + kBgChunk - 1) / kBgChunk;
-  for (int c = 0; c < n_chunks; ++c) {
-    const Node* P = prep + (int64_t)c * n_nodes;
-    const int nb = min(kBgChunk, n_bg - c * kBgChunk);
-    for (int jb = 0; jb < nb; ++jb) {
-      for (int t = 0; t < n_trees; ++t) {
-        const int r = roots[t];
-        int n[KP];
-#pragma unroll
-        for (int j = 0; j < KP; ++j) n[j] = r;
-        for (int lv = 0; lv < max_depth; ++lv) {
-          Node w[KP];
-#pragma unroll
-          for (int j = 0; j < KP; ++j) w[j] = P[n[j]];
-          bool inner = false;
-#pragma unroll
-          for (int j = 0; j < KP; ++j) {
-            if (w[j].code >= 0) {
-              const uint32_t f = (uint32_t)w[j].code & 255u;
-              const uint32_t go = ((S[j] >> f) & 1u) ? ((uint32_t)w[j].code >> 8) & 1u
-                                                     : (w[j].bits >> jb) & 1u;
-              n[j] = go ? w[j].right : w[j].left;
-              inner = true;
-            }
-          }
-          if (!__any(inner)) break;
+// ---- walk route ----
+// A workgroup owns a block of 2^m consecutive coalitions, which share their
+// bits from m up. For one background and one tree most nodes are then
+// decided for the whole block: x and the background fall on the same side
+// of the threshold, the feature is one of the shared bits, or the path has
+// already fixed it. What is left is a short list of reachable leaves, each
+// with the low bits a coalition must have and must not have, and a coalition
+// takes the one leaf whose bits it matches. With thresholds spread like the
+// points, 200 depth-6 trees on 20 features leave 2.5 leaves a tree and block
+// of 1024 coalitions, against 6 dependent node loads a coalition for a walk
+// of its own.
+//
+// Per chunk of (background, tree) pairs, one thread per pair lists the
+// leaves of its pair into LDS (need bits and FP64 outputs); then the
+// coalitions test the lists and add the leaf outputs pair by pair, in the
+// order of the pairs, so v is bitwise the sum of the plain walk. A pair with
+// more than NK leaves in a block is walked per coalition instead.
+
+// need word of a leaf: bit f for a feature f < m that must be in S, bit
+// 16 + f for one that must not be; a coalition matches iff
+// (need & ~X(S)) == 0 with X(S) = S_low | ~S_low << 16.
+
+// LDS of a chunk of NP pairs: NK need words, the leaf count and the root per
+// pair (row of NK + 2 words, read as 8-byte words), then the leaf outputs in
+// rows of NK + 1 (odd, so that the threads of a wave write distinct banks).
+template <int NP, int NK>
+struct LeafLists {
+  static constexpr int kNeedRow = NK + 2;
+  static constexpr int kValRow = NK + 1;
+  uint2 need2[NP * kNeedRow / 2];
+  double val[NP * kValRow];
+  __device__ __forceinline__ uint32_t* need() { return reinterpret_cast<uint32_t*>(need2); }
+};
+
+// Leaves of one tree reachable inside the block (depth-first over the
+// choices at undecided nodes; each leaf is reached by a walk from the root
+// that follows the recorded choices). Returns the count, NK + 1 if more.
+template <int NK>
+__device__ __forceinline__ int list_leaves(const Node* __restrict__ P, const double* __restrict__ value,
+                                           int root, int jb, int m, uint32_t shared_bits,
+                                           uint32_t* __restrict__ need_row, double* __restrict__ val_row) {
+  uint32_t choice = 0;   // bit k: the k-th undecided feature of the path is in S
+  int depth = 0, n = 0;
+  for (;;) {
+    int node = root, k = 0;
+    uint32_t need = 0;
+    for (;;) {
+      const Node w = P[node];
+      if (w.code < 0) break;
+      const uint32_t dx = ((uint32_t)w.code >> 8) & 1u, db = (w.bits >> jb) & 1u;
+      uint32_t go = dx;
+      if (dx != db) {
+        const uint32_t f = (uint32_t)w.code & 255u;
+        uint32_t in;
+        if ((int)f >= m) {
+          in = (shared_bits >> f) & 1u;
+        } else if ((need >> f) & 0x10001u) {
+          in = (need >> f) & 1u;
+        } else {
+          if (k == depth) { choice &= ~(1u << k); ++depth; }
+          in = (choice >> k) & 1u;
+          need |= in ? 1u << f : 0x10000u << f;
+          ++k;
         }
-#pragma unroll
-        for (int j = 0; j < KP; ++j) acc[j] += value[n[j]];
+        go = in ? dx : db;
       }
+      node = go ? w.right : w.left;
     }
-  }
-#pragma unroll
-  for (int j = 0; j < KP; ++j) {
-    const uint32_t s = ((uint32_t)blockIdx.x * KP + j) * kThreads + threadIdx.x;
-    if (s < n_coal) v[s] = (OutT)(acc[j] / (double)n_bg);
+    if (n == NK) return NK + 1;
+    need_row[n] = need;
+    val_row[n] = value[node];
+    ++n;
+    while (depth > 0 && ((choice >> (depth - 1)) & 1u)) --depth;
+    if (depth == 0) return n;
+    choice |= 1u << (depth - 1);
   }
 }
 
-constexpr int kWalkKP = 2;
+// One chunk: pairs [g0, g0 + np) of the (background, tree) sequence.
+template <int NP, int NK>
+__device__ __forceinline__ void build_lists(const Node* __restrict__ prep, const double* __restrict__ value,
+                                            const int32_t* __restrict__ roots, int n_trees,
+                                            int n_nodes, int64_t g0, int np, int m,
+                                            uint32_t shared_bits, LeafLists<NP, NK>& L) {
+  const int p = threadIdx.x;
+  if (p >= np) return;
+  const int64_t g = g0 + p;
+  const int b = (int)(g / n_trees);
+  const int root = roots[(int)(g - (int64_t)b * n_trees)];
+  uint32_t* row = L.need() + p * LeafLists<NP, NK>::kNeedRow;
+  row[NK] = (uint32_t)list_leaves<NK>(prep + (int64_t)(b / kBgChunk) * n_nodes, value, root,
+                                      b % kBgChunk, m, shared_bits, row,
+                                      L.val + p * LeafLists<NP, NK>::kValRow);
+  row[NK + 1] = (uint32_t)root;
+}
+
+// Plain walk of one coalition (pairs with more leaves than a list holds).
+__device__ __forceinline__ int walk_one(const Node* __restrict__ P, int root, int jb, uint32_t S) {
+  int node = root;
+  for (;;) {
+    const Node w = P[node];
+    if (w.code < 0) return node;
+    const uint32_t f = (uint32_t)w.code & 255u;
+    const uint32_t go = ((S >> f) & 1u) ? ((uint32_t)w.code >> 8) & 1u : (w.bits >> jb) & 1u;
+    node = go ? w.right : w.left;
+  }
+}
+
+// The lists of 64 pairs, one per lane, as a wave reads them: the first four
+// need words and the count.
+struct LaneLists {
+  uint32_t nd[4], cnt;
+};
+template <int NP, int NK>
+__device__ __forceinline__ LaneLists lane_lists(LeafLists<NP, NK>& L, int p) {
+  constexpr int R2 = LeafLists<NP, NK>::kNeedRow / 2;
+  const uint2 a = L.need2[p * R2], b = L.need2[p * R2 + 1];
+  return LaneLists{{a.x, a.y, b.x, b.y}, L.need2[p * R2 + NK / 2].x};
+}
+// Index in pair p's list of the leaf each of KP coalitions takes (nx = ~X);
+// q: p's lane in ll. The pair and its list are uniform in the wave.
+template <int NP, int NK, int KP>
+__device__ __forceinline__ void match(LeafLists<NP, NK>& L, const LaneLists& ll, int p, int q, int n,
+                                      const uint32_t (&nx)[KP], int (&idx)[KP]) {
+#pragma unroll
+  for (int j = 0; j < KP; ++j) idx[j] = n - 1;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (i < n - 1) {
+      const uint32_t need = (uint32_t)__builtin_amdgcn_readlane((int)ll.nd[i], q);
+#pragma unroll
+      for (int j = 0; j < KP; ++j) idx[j] = (need & nx[j]) == 0u ? i : idx[j];
+    }
+  for (int i = 4; i < n - 1; ++i) {
+    const uint32_t need = L.need()[p * LeafLists<NP, NK>::kNeedRow + i];
+#pragma unroll
+    for (int j = 0; j < KP; ++j) idx[j] = (need & nx[j]) == 0u ? i : idx[j];
+  }
+}
+
+// Every thread owns KP coalitions, base + tid + j * kThreads.
+constexpr int kWideNK = 12;
+template <typename OutT, int KP>
+__global__ void __launch_bounds__(kThreads)
+walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
+                 const int32_t* __restrict__ roots, int n_trees, int n_nodes, int n_bg, int d, int m,
+                 OutT* __restrict__ v) {
+  constexpr int NP = kThreads, NK = kWideNK;
+  __shared__ LeafLists<NP, NK> L;
+  const uint32_t base = (uint32_t)blockIdx.x * (kThreads * KP);
+  const int lane = threadIdx.x & 63;
+  uint32_t nx[KP];
+  double acc[KP];
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    const uint32_t low = (threadIdx.x + j * kThreads) & ((1u << m) - 1u);
+    nx[j] = ~low & 0xffffu;
+    nx[j] |= low << 16;
+    acc[j] = 0.0;
+  }
+  const int64_t total = (int64_t)n_bg * n_trees;
+  for (int64_t g0 = 0; g0 < total; g0 += NP) {
+    const int np = (int)min((int64_t)NP, total - g0);
+    build_lists<NP, NK>(prep, value, roots, n_trees, n_nodes, g0, np, m, base, L);
+    __syncthreads();
+    for (int p0 = 0; p0 < np; p0 += 64) {
+      const LaneLists ll = lane_lists<NP, NK>(L, min(p0 + lane, np - 1));
+      const int nq = min(64, np - p0);
+      for (int q = 0; q < nq; ++q) {
+        const int p = p0 + q;
+        const int n = __builtin_amdgcn_readlane((int)ll.cnt, q);
+        if (n > NK) {
+          const int b = (int)((g0 + p) / n_trees);
+          const int root = (int)L.need()[p * LeafLists<NP, NK>::kNeedRow + NK + 1];
+          const Node* P = prep + (int64_t)(b / kBgChunk) * n_nodes;
+#pragma unroll
+          for (int j = 0; j < KP; ++j)
+            acc[j] += value[walk_one(P, root, b % kBgChunk, base | (nx[j] >> 16))];
+        } else {
+          int idx[KP];
+          match<NP, NK, KP>(L, ll, p, q, n, nx, idx);
+#pragma unroll
+          for (int j = 0; j < KP; ++j) acc[j] += L.val[p * LeafLists<NP, NK>::kValRow + idx[j]];
+        }
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    const uint32_t s = base + threadIdx.x + j * kThreads;
+    if (s < (1u << d)) v[s] = (OutT)(acc[j] / (double)n_bg);
+  }
+}
+
+// Few coalitions: a workgroup owns 64 of them and its waves split the pairs.
+// Each wave matches 64 pairs of a chunk and leaves the leaf indexes (one byte
+// per pair and coalition) in LDS; one wave then adds the outputs in the
+// order of the pairs.
+constexpr int kNarrowNK = 16;
+constexpr int kNarrowThreads = 512;
+template <typename OutT>
+__global__ void __launch_bounds__(kNarrowThreads)
+walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
+                   const int32_t* __restrict__ roots, int n_trees, int n_nodes, int n_bg, int d,
+                   OutT* __restrict__ v) {
+  constexpr int NP = kNarrowThreads, NK = kNarrowNK;
+  constexpr int VR = LeafLists<NP, NK>::kValRow;
+  __shared__ LeafLists<NP, NK> L;
+  __shared__ uint32_t pick[NP / 4][64];   // bytes: leaf index of pairs 4 r .. 4 r + 3 (255: walk)
+  const int m = min(d, 6);
+  const uint32_t base = (uint32_t)blockIdx.x << 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t low = (uint32_t)lane & ((1u << m) - 1u);
+  const uint32_t nx[1] = {(~low & 0xffffu) | (low << 16)};
+  double acc = 0.0;
+  const int64_t total = (int64_t)n_bg * n_trees;
+  for (int64_t g0 = 0; g0 < total; g0 += NP) {
+    const int np = (int)min((int64_t)NP, total - g0);
+    build_lists<NP, NK>(prep, value, roots, n_trees, n_nodes, g0, np, m, base, L);
+    __syncthreads();
+    const int p0 = wave * 64;
+    if (p0 < np) {
+      const LaneLists ll = lane_lists<NP, NK>(L, min(p0 + lane, np - 1));
+      const int nq = min(64, np - p0);
+      for (int q0 = 0; q0 < nq; q0 += 4) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int q = min(q0 + i, nq - 1);
+          const int n = __builtin_amdgcn_readlane((int)ll.cnt, q);
+          int idx[1] = {255};
+          if (n <= NK) match<NP, NK, 1>(L, ll, p0 + q, q, n, nx, idx);
+          w |= (uint32_t)idx[0] << (8 * i);
+        }
+        pick[(p0 + q0) >> 2][lane] = w;
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      for (int p = 0; p < np; p += 4) {
+        const uint32_t w = pick[p >> 2][lane];
+        const int nq = min(4, np - p);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (i >= nq) break;
+          const int idx = (int)((w >> (8 * i)) & 255u);
+          if (__builtin_expect(idx == 255, 0)) {   // uniform: the whole pair has no list
+            const int b = (int)((g0 + p + i) / n_trees);
+            const int root = (int)L.need()[(p + i) * LeafLists<NP, NK>::kNeedRow + NK + 1];
+            acc += value[walk_one(prep + (int64_t)(b / kBgChunk) * n_nodes, root, b % kBgChunk,
+                                  base | low)];
+          } else {
+            acc += L.val[(p + i) * VR + idx];
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (wave == 0) {
+    const uint32_t s = base + (uint32_t)lane;
+    if (s < (1u << d)) v[s] = (OutT)(acc / (double)n_bg);
+  }
+}
+
+// Coalitions per thread of the wide kernel, 0 for the narrow one.
+int walk_kp(int d) { return d >= 19 ? 4 : d >= 18 ? 2 : d >= 16 ? 1 : 0; }
+
+template <typename OutT>
+void launch_walk(const Node* prep, const double* value, const int32_t* roots, int n_trees,
+                 int n_nodes, int n_bg, int d, OutT* v, hipStream_t st) {
+  const int kp = walk_kp(d);
+  if (kp == 0) {
+    const int grid = d > 6 ? 1 << (d - 6) : 1;
+    walk_narrow_kernel<OutT><<<grid, kNarrowThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes,
+                                                              n_bg, d, v);
+    return;
+  }
+  const int m = kp == 4 ? 10 : kp == 2 ? 9 : 8;
+  const int grid = 1 << (d - m);
+  switch (kp) {
+    case 1: walk_wide_kernel<OutT, 1><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, n_bg, d, m, v); break;
+    case 2: walk_wide_kernel<OutT, 2><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, n_bg, d, m, v); break;
+    default: walk_wide_kernel<OutT, 4><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, n_bg, d, m, v); break;
+  }
+}
 
 // ---- Moebius route ----
 // A leaf of a tree is reached at z_b(S) iff every test on its root path
@@ -259,7 +489,7 @@ using namespace fsi;
 using namespace fsi::forest;
 
 struct fsi_forest_s {
-  int d = 0, n_trees = 0, n_nodes = 0, max_bg = 0, max_depth = 0, device = 0;
+  int d = 0, n_trees = 0, n_nodes = 0, max_bg = 0, device = 0;
   int32_t* feature = nullptr;
   int32_t* left = nullptr;
   int32_t* right = nullptr;
@@ -417,7 +647,7 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
     ~Guard() { free_forest(f); }
   } guard{F};
   F->d = d; F->n_trees = n_trees; F->n_nodes = n_nodes; F->max_bg = max_bg;
-  F->max_depth = depth; F->device = dev;
+  F->device = dev;
   // leaves keep feature -1 on the device whatever negative value they had
   std::vector<int32_t> feat(feature, feature + n_nodes);
   for (auto& f : feat) f = f < 0 ? -1 : f;
@@ -480,17 +710,10 @@ fsi_status fsi_forest_values(fsi_forest_t F, const double* x_dev, int n_bg, cons
   const int prep_grid = (int)std::min<int64_t>((prep_total + kThreads - 1) / kThreads, 4096);
   prep_kernel<<<prep_grid, kThreads, 0, stream>>>(F->feature, F->threshold, F->left, F->right,
                                                   F->n_nodes, F->d, x_dev, bg_dev, n_bg, F->prep);
-  const int64_t n_coal = (int64_t)1 << F->d;
-  const int64_t per_block = (int64_t)kThreads * kWalkKP;
-  const int grid = (int)((n_coal + per_block - 1) / per_block);
   if (dtype == FSI_DTYPE_F64)
-    walk_kernel<double, kWalkKP><<<grid, kThreads, 0, stream>>>(
-        F->prep, F->value, F->roots, F->n_trees, F->n_nodes, n_bg, F->max_depth, F->d,
-        (double*)v_dev);
+    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, n_bg, F->d, (double*)v_dev, stream);
   else
-    walk_kernel<float, kWalkKP><<<grid, kThreads, 0, stream>>>(
-        F->prep, F->value, F->roots, F->n_trees, F->n_nodes, n_bg, F->max_depth, F->d,
-        (float*)v_dev);
+    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, n_bg, F->d, (float*)v_dev, stream);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ffail(FSI_ERR_HIP, std::string("forest launch: ") + hipGetErrorString(e));
   return FSI_OK;
