@@ -383,8 +383,8 @@ void launch_walk(const Node* prep, const double* value, const int32_t* roots, in
 // the path], the leaf's indicator is prod_f (beta_f + [f in S](alpha_f -
 // beta_f)), whose Moebius coefficients sit on R = I u Q: I = {f: beta_f = 0}
 // (unreachable if some f in I has alpha_f = 0), Q any subset of
-// Fr = {f: beta_f = 1, alpha_f = 0}, with sign (-1)^|Q|. One thread per
-// (background, path) adds value / B * (-1)^|Q| at every such R.
+// Fr = {f: beta_f = 1, alpha_f = 0}, with sign (-1)^|Q|; value / B * (-1)^|Q|
+// is added at every such R.
 __global__ void __launch_bounds__(kThreads)
 fill_kernel(double* __restrict__ a, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
@@ -392,19 +392,50 @@ fill_kernel(double* __restrict__ a, int64_t n) {
     a[i] = 0.0;
 }
 
+// One thread per path and group of kScatterBg backgrounds: the path's nodes
+// and thresholds are read once per group, the points' coordinates from LDS.
+// Most coefficients fall on a few small sets (every tree and background adds
+// one at the empty set), and FP64 atomics on one address serialise in
+// memory: a workgroup collects the sets of at most two players in LDS (index
+// 0, then 1 + i, then 1 + d + C(j, 2) + i for i < j) and adds each to memory
+// once at the end.
+constexpr int kScatterBg = 8;
+constexpr int kScatterGrid = 512;   // workgroups that collect and flush
+constexpr int kSmallSets = 1 + kMaxD + kMaxD * (kMaxD - 1) / 2;
+
 __global__ void __launch_bounds__(kThreads)
 mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __restrict__ steps,
                       const int32_t* __restrict__ path_leaf, int n_paths,
                       const int32_t* __restrict__ feature, const double* __restrict__ threshold,
                       const double* __restrict__ value, int d, const double* __restrict__ x,
                       const double* __restrict__ bg, int n_bg, double* __restrict__ a) {
-  const int64_t total = (int64_t)n_bg * n_paths;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * kThreads) {
-    const int b = (int)(i / n_paths);
-    const int p = (int)(i - (int64_t)b * n_paths);
-    const double* z = bg + (int64_t)b * d;
-    uint32_t seen = 0, aok = ~0u, bok = ~0u;
+  __shared__ double small[kSmallSets];
+  __shared__ double xs[kMaxD], zs[kScatterBg][kMaxD];
+  const int n_small = 1 + d + d * (d - 1) / 2;
+  for (int i = threadIdx.x; i < n_small; i += kThreads) small[i] = 0.0;
+  if ((int)threadIdx.x < d) xs[threadIdx.x] = x[threadIdx.x];
+  const int chunks = (n_paths + kThreads - 1) / kThreads;    // of paths, per group
+  const int groups = (n_bg + kScatterBg - 1) / kScatterBg;
+  const int64_t total = (int64_t)chunks * groups;
+  int g_prev = -1;
+  for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
+    const int g = (int)(it / chunks);
+    const int p = (int)(it - (int64_t)g * chunks) * kThreads + (int)threadIdx.x;
+    const int b0 = g * kScatterBg;
+    const int nb = min(kScatterBg, n_bg - b0);
+    if (g != g_prev) {   // uniform in the workgroup
+      __syncthreads();
+      for (int i = threadIdx.x; i < kScatterBg * d; i += kThreads) {
+        const int b = i / d;
+        zs[b][i - b * d] = bg[(int64_t)(b0 + min(b, nb - 1)) * d + (i - b * d)];
+      }
+      __syncthreads();
+      g_prev = g;
+    }
+    if (p >= n_paths) continue;
+    uint32_t seen = 0, aok = ~0u, bok[kScatterBg];
+#pragma unroll
+    for (int b = 0; b < kScatterBg; ++b) bok[b] = ~0u;
     for (int s = path_off[p]; s < path_off[p + 1]; ++s) {
       const int e = steps[s];
       const int node = e >> 1;
@@ -413,18 +444,47 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
       const double th = threshold[node];
       const uint32_t bit = 1u << f;
       seen |= bit;
-      if ((x[f] >= th) != dir) aok &= ~bit;
-      if ((z[f] >= th) != dir) bok &= ~bit;
+      if ((xs[f] >= th) != dir) aok &= ~bit;
+#pragma unroll
+      for (int b = 0; b < kScatterBg; ++b)
+        if ((zs[b][f] >= th) != dir) bok[b] &= ~bit;
     }
-    const uint32_t I = seen & ~bok;
-    if (I & ~aok) continue;                        // never reached
-    const uint32_t Fr = seen & bok & ~aok;
     const double c = value[path_leaf[p]] / (double)n_bg;
-    uint32_t Q = 0;
-    do {
-      atomicAdd(a + (I | Q), (__popc(Q) & 1) ? -c : c);
-      Q = (Q - Fr) & Fr;
-    } while (Q != 0);
+#pragma unroll
+    for (int b = 0; b < kScatterBg; ++b) {
+      const uint32_t I = seen & ~bok[b];
+      if (b >= nb || (I & ~aok)) continue;           // never reached
+      const uint32_t Fr = seen & bok[b] & ~aok;
+      uint32_t Q = 0;
+      do {
+        const uint32_t R = I | Q;
+        const double v = (__popc(Q) & 1) ? -c : c;
+        if (__popc(R) <= 2) {
+          int k = 0;
+          if (R) {
+            const int j = 31 - __clz((int)R), i = __ffs((int)R) - 1;
+            k = i == j ? 1 + i : 1 + d + j * (j - 1) / 2 + i;
+          }
+          atomicAdd(small + k, v);
+        } else {
+          atomicAdd(a + R, v);
+        }
+        Q = (Q - Fr) & Fr;
+      } while (Q != 0);
+    }
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < n_small; k += kThreads) {
+    if (small[k] == 0.0) continue;
+    uint32_t R = 0;
+    if (k > d) {
+      int j = 1, o = k - 1 - d;
+      while (o >= j) o -= j++;
+      R = (1u << j) | (1u << o);
+    } else if (k > 0) {
+      R = 1u << (k - 1);
+    }
+    atomicAdd(a + R, small[k]);
   }
 }
 
@@ -750,11 +810,11 @@ fsi_status fsi_forest_mobius(fsi_forest_t F, const double* x_dev, int n_bg, cons
   const int64_t n_coal = (int64_t)1 << F->d;
   fill_kernel<<<(int)std::min<int64_t>((n_coal + kThreads - 1) / kThreads, 8192), kThreads, 0,
                 stream>>>(a_dev, n_coal);
-  const int64_t work = (int64_t)n_bg * F->n_paths;
-  mobius_scatter_kernel<<<(int)std::min<int64_t>((work + kThreads - 1) / kThreads, 65535),
-                          kThreads, 0, stream>>>(F->path_off, F->steps, F->path_leaf, F->n_paths,
-                                                 F->feature, F->threshold, F->value, F->d, x_dev,
-                                                 bg_dev, n_bg, a_dev);
+  const int64_t work = (int64_t)((n_bg + kScatterBg - 1) / kScatterBg) *
+                       ((F->n_paths + kThreads - 1) / kThreads);
+  mobius_scatter_kernel<<<(int)std::min<int64_t>(work, kScatterGrid), kThreads, 0, stream>>>(
+      F->path_off, F->steps, F->path_leaf, F->n_paths, F->feature, F->threshold, F->value, F->d,
+      x_dev, bg_dev, n_bg, a_dev);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ffail(FSI_ERR_HIP, std::string("forest launch: ") + hipGetErrorString(e));
   return FSI_OK;
