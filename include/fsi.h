@@ -199,8 +199,9 @@ typedef struct {
   int32_t fast_instances;   /* instances on the register-phase kernel       */
   int32_t tiles_per_item;   /* register-phase kernel: tiles per work item   */
   int32_t tile_shift;       /* generic tile: bits below the largest fitting */
-  int32_t mob_group;        /* two-pass: bits per strided high pass; 0 for  */
-                            /* the fused algorithm                          */
+  int32_t mob_group;        /* two-pass: most bits of a strided high pass   */
+                            /* (8 unless autotuned); 0 for the fused        */
+                            /* algorithm                                    */
   float tuned_ms;           /* measured time of the chosen schedule (ms)    */
 } fsi_schedule;
 
@@ -250,8 +251,8 @@ fsi_status fsi_apply(fsi_plan_t plan, const void* v_dev, void* out_dev,
 
 /* Moebius transform alone (Sec. 4.2, Appendix B), in place on a_dev
  * (2^d elements of the plan's storage dtype): for every bit i and every mask
- * m with bit i set, a[m] -= a[m with bit i cleared]. Low bits are staged in
- * LDS, high bits run as coalesced strided passes. */
+ * m with bit i set, a[m] -= a[m with bit i cleared]. One pass over the low 12
+ * bits, then one strided pass per 8 bits above them. */
 fsi_status fsi_mobius(fsi_plan_t plan, void* a_dev, hipStream_t stream);
 
 /* Batched plan over n instances of possibly different (d_i, l_i)

@@ -180,7 +180,7 @@ struct Sched {
   int kernel = -1;      // fsi_kernel to use, -1: the option's
   int tb_shift = 0;     // generic tile: bits relative to the largest that fits LDS (<= 0)
   int chunk_shift = 0;  // register-phase kernel: log2 tiles per item relative to the default
-  int mob_group = 0;    // two-pass: bits per strided high Moebius pass (0: 6)
+  int mob_group = 0;    // two-pass: most bits of a strided high Moebius pass (0: kMobGroup)
   int algo = 0;         // FSI_ALGO_FUSED or FSI_ALGO_TWO_PASS; 0: the option's
 };
 
@@ -561,12 +561,6 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     });
   }
 
-  // every tile of every instance (standalone Moebius low pass)
-  std::vector<TileItem> all_tiles;
-  for (int i = 0; i < n; ++i) {
-    const ClassHost& C = P->classes[P->cls_of[i]];
-    for (int64_t t = 0; t < ((int64_t)1 << C.h); ++t) all_tiles.push_back(TileItem{i, (int32_t)t});
-  }
   // generic tiles: larger tiles first, so a persistent grid finishes evenly
   std::vector<TileItem> tiles;
   for (int i = 0; i < n; ++i) {
@@ -577,22 +571,26 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   std::stable_sort(tiles.begin(), tiles.end(), [&](const TileItem& a, const TileItem& b) {
     return P->classes[P->cls_of[a.inst]].b > P->classes[P->cls_of[b.inst]].b;
   });
-  // strided high-bit passes of the two-pass butterfly (also fsi_mobius)
-  std::vector<MobItem> mob[kMaxMobPasses];
+  // passes of the Moebius butterfly (two-pass plans, and fsi_mobius on plans
+  // of one instance): a low pass of kMobTileBits bits, then the bits above in
+  // as few strided passes as their cap allows, of even size (2^13 .. 2^20
+  // take one, 2^21 .. 2^28 two)
+  std::vector<MobItem> mob_low, mob[kMaxMobPasses];
   int n_passes = 0;
-  for (int i = 0; i < n; ++i) {
-    const ClassHost& C = P->classes[P->cls_of[i]];
-    int lo = C.b, p = 0;
-    while (lo < dh[i]) {
-      const int G = std::min(sc.mob_group > 0 ? sc.mob_group : 6, dh[i] - lo);
-      const int cb = std::min(lo, kMaxTileBits - G);
-      if (p >= kMaxMobPasses) { return fail(FSI_ERR_INTERNAL, "too many passes"); }
-      const int64_t nblk = (int64_t)1 << (dh[i] - G - cb);
-      for (int64_t bk = 0; bk < nblk; ++bk) mob[p].push_back(MobItem{i, lo, G, cb, bk});
+  const int mob_cap = sc.mob_group > 0 ? std::min(sc.mob_group, kMobGroup) : kMobGroup;
+  for (int i = 0; i < n && (single || algo == ALGO_TWO_PASS); ++i) {
+    const int64_t ntile = (int64_t)1 << std::max(0, dh[i] - kMobTileBits);
+    for (int64_t t = 0; t < ntile; ++t) mob_low.push_back(MobItem{i, 0, kMobTileBits, 0, t});
+    const int high = std::max(0, dh[i] - kMobTileBits);
+    const int np = (high + mob_cap - 1) / mob_cap;
+    if (np > kMaxMobPasses) { return fail(FSI_ERR_INTERNAL, "too many passes"); }
+    for (int p = 0, lo = kMobTileBits; p < np; ++p) {
+      const int G = (dh[i] - lo + np - p - 1) / (np - p);
+      for (int64_t t = 0; t < ntile; ++t)
+        mob[p].push_back(MobItem{i, lo, G, kMobTileBits - G, t});
       lo += G;
-      ++p;
     }
-    n_passes = std::max(n_passes, p);
+    n_passes = std::max(n_passes, np);
   }
 
   // ---- device arena ----
@@ -636,7 +634,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   const size_t o_cls = stage(buf, cdev.data(), cdev.size());
   const size_t o_inst = stage(buf, insts.data(), insts.size());
   const size_t o_tiles = stage(buf, tiles.data(), tiles.size());
-  const size_t o_all_tiles = stage(buf, all_tiles.data(), all_tiles.size());
+  const size_t o_mob_low = stage(buf, mob_low.data(), mob_low.size());
   size_t o_mob[kMaxMobPasses] = {0, 0, 0, 0};
   for (int p = 0; p < n_passes; ++p) o_mob[p] = stage(buf, mob[p].data(), mob[p].size());
   const size_t o_ooff = stage(buf, P->ooff.data(), P->ooff.size());
@@ -722,8 +720,6 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   }
 
   // ---- schedule ----
-  // Moebius passes stage at most 2^12 elements of at most 8 bytes
-  const size_t mob_lds = ((size_t)1 << kMaxTileBits) * 8;
   size_t tile_lds = 0;
   for (size_t c = 0; c < P->classes.size(); ++c) {
     const ClassHost& C = P->classes[c];
@@ -731,7 +727,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     tile_lds = std::max<size_t>(tile_lds, std::max<size_t>(2 * (size_t)C.lds_elems * sweep_elem_bytes(prec),
                                                            ((size_t)1 << C.b) * mob_elem_bytes(prec)));
   }
-  e = configure_kernels(prec, algo, tile_lds, mob_lds);
+  e = configure_kernels(prec, algo, tile_lds);
   if (e != hipSuccess) { return fail(FSI_ERR_HIP, std::string("configure_kernels: ") + hipGetErrorString(e)); }
   if (tile_lds == 0) tile_lds = 1024;
   const int per_cu = std::max(1, std::min<int>(4, (int)((160 * 1024) / std::max<size_t>(tile_lds, 1))));
@@ -742,8 +738,9 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   a.n_inst = n;
   a.tile_items = reinterpret_cast<const TileItem*>(A + o_tiles);
   a.n_tile_items = (int)tiles.size();
-  a.all_tiles = reinterpret_cast<const TileItem*>(A + o_all_tiles);
-  a.n_all_tiles = (int)all_tiles.size();
+  a.mob_low = reinterpret_cast<const MobItem*>(A + o_mob_low);
+  a.n_mob_low = (int)mob_low.size();
+  a.grid_mob = n_cu * 4;   // 34 KB of LDS each
   a.n_mob_passes = n_passes;
   for (int p = 0; p < kMaxMobPasses; ++p) {
     a.mob_items[p] = p < n_passes ? reinterpret_cast<const MobItem*>(A + o_mob[p]) : nullptr;
@@ -754,10 +751,9 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   a.Y = P->Y;
   a.Ylo = P->ylo_off >= 0 ? P->Y + P->ylo_off : nullptr;
   a.work = P->work;
-  a.grid_tile = std::max(1, std::min<int>((int)std::max(tiles.size(), all_tiles.size()), n_cu * per_cu));
+  a.grid_tile = std::max(1, std::min<int>((int)tiles.size(), n_cu * per_cu));
   a.grid_reduce = (int)std::max<int64_t>(1, std::min<int64_t>((a.total_out + 255) / 256, (int64_t)n_cu * 8));
   a.tile_lds = tile_lds;
-  a.mob_lds = mob_lds;
   a.partial = P->partial;
   a.n_generic = n_generic;
   a.wide_items = reinterpret_cast<const WideItem*>(A + o_witems);
@@ -805,7 +801,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   for (int i = 0; i < n; ++i) P->sched.fast_instances += insts[i].fast;
   P->sched.tiles_per_item = fitems.empty() ? 0 : (int)chunk;
   P->sched.tile_shift = sc.tb_shift;
-  P->sched.mob_group = algo == ALGO_TWO_PASS ? (sc.mob_group > 0 ? sc.mob_group : 6) : 0;
+  P->sched.mob_group = algo == ALGO_TWO_PASS ? mob_cap : 0;
   P->sched.tuned_ms = 0.f;
   P->partial_bytes = (size_t)ptot * sizeof(double);
   P->y_bytes = (size_t)ywords * sizeof(double);

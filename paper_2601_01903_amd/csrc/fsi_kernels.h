@@ -9,6 +9,8 @@ namespace fsi {
 
 constexpr int kTileThreads = 512;
 constexpr int kMaxMobPasses = 4;   // high-bit groups of the two-pass butterfly
+constexpr int kMobTileBits = 12;   // elements of a butterfly tile (log2); bits of its low pass
+constexpr int kMobGroup = 8;       // most bits of a high pass
 
 struct TileItem {
   int32_t inst, tile;       // instance, high index U_H of the tile
@@ -16,7 +18,7 @@ struct TileItem {
 
 struct MobItem {
   int32_t inst, lo, G, cb;  // group bits [lo, lo+G); 2^cb consecutive low indices
-  int64_t block;            // (bits above the group) * 2^(lo-cb) + low chunk
+  int64_t block;            // (bits above the group) * 2^(lo-cb) + low chunk; low pass: the tile
 };
 
 // Register-phase kernel (fsi_tile11.hip)
@@ -94,8 +96,8 @@ struct LaunchArgs {
   int n_inst;
   const TileItem* tile_items;     // tiles of the generic tile kernel
   int n_tile_items;
-  const TileItem* all_tiles;      // every tile (standalone Moebius)
-  int n_all_tiles;
+  const MobItem* mob_low;         // butterfly tiles of every instance
+  int n_mob_low, grid_mob;
   const MobItem* mob_items[kMaxMobPasses];
   int n_mob_items[kMaxMobPasses];
   int n_mob_passes;
@@ -107,7 +109,7 @@ struct LaunchArgs {
   double* Y;
   double* Ylo;                // two-pass FP64: low words of the per-tile results (else null)
   int grid_tile, grid_reduce;
-  size_t tile_lds, mob_lds;
+  size_t tile_lds;
   const double* partial;      // register-phase kernel partial sums
   FastLaunch fast;            // n_items == 0: no register-phase stage
   int n_generic;              // instances of the generic (or two-pass) path outside the wide gather
@@ -123,7 +125,7 @@ struct LaunchArgs {
 
 // Sets the dynamic-LDS limits of the kernels a plan will launch (call once
 // per plan, outside any graph capture).
-hipError_t configure_kernels(int prec, int algo, size_t tile_lds, size_t mob_lds);
+hipError_t configure_kernels(int prec, int algo, size_t tile_lds);
 hipError_t launch_apply(const LaunchArgs& a, hipStream_t st);
 // Kernel launches of one apply, in order; launch_apply runs all of them.
 int num_stages(const LaunchArgs& a);

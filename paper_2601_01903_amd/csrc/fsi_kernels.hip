@@ -13,6 +13,7 @@
 //
 // All kernels are persistent: a grid sized to the machine walks a work list.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 
 #include "fsi_kernels.h"
@@ -402,87 +403,121 @@ fast_reduce_kernel(const InstDev* __restrict__ insts, const int2* __restrict__ c
 }
 
 // ---------------------------------------------------------------- Moebius (two-pass)
-// Low pass: each work item is a tile of 2^b consecutive values; butterflies
-// over the b low bits in LDS; the result goes to dst (in place allowed).
-template <typename InT, typename MobT>
-__global__ void __launch_bounds__(kTileThreads)
-mobius_low_kernel(const ClassDev* __restrict__ classes, const InstDev* __restrict__ insts,
-                  const TileItem* __restrict__ items, int n_items, const InT* src,
-                  MobT* dst, int src_is_values) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  MobT* m = reinterpret_cast<MobT*>(smem);
-  const int tid = threadIdx.x;
-  constexpr int NT = kTileThreads;
-  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-    const TileItem w = items[it];
-    const InstDev I = insts[w.inst];
-    const int b = classes[I.cls].b;
-    const int nt = 1 << b;
-    const InT* s = src + (src_is_values ? I.voff : I.woff) + ((int64_t)w.tile << b);
-    MobT* o = dst + I.woff + ((int64_t)w.tile << b);
-    for (int i = tid; i < nt; i += NT) m[i] = Num<MobT>::from_in(s[i]);
-    __syncthreads();
-    for (int bit = 0; bit < b; ++bit) {
-      for (int p = tid; p < (nt >> 1); p += NT) {
-        const int lo = ((p >> bit) << (bit + 1)) | (p & ((1 << bit) - 1));
-        const int hi = lo | (1 << bit);
-        m[hi] = Num<MobT>::sub(m[hi], m[lo]);
-      }
-      __syncthreads();
+// One pass of the butterfly over the G bits [lo, lo + G) of one instance. A
+// work item is a tile of 2^kMobTileBits elements: 2^cb consecutive low
+// indices (cb = kMobTileBits - G; 0 for the low pass, lo = 0) for each
+// setting of the G bits, at one setting of the other bits. A thread holds 16
+// elements of the tile, i.e. four of its bits, in registers, runs those
+// levels there and hands the tile to the next four through LDS, so a pass
+// reads and writes each value once with one exchange for G <= 8 and three for
+// the low pass. (One level per LDS round trip and barrier, as before, held a
+// pass over 2^24 FP64 values at 64 us where memory allows 40.)
+//
+// Every layout is an affine map of the thread: mob_field(t, P) | k << P puts
+// the four register bits k at tile bits P .. P + 3. Global accesses use
+// P >= 4, whose waves touch runs of at least 16 consecutive elements. The
+// levels run in ascending order of their bits.
+constexpr int kMobElems = 16;                       // per thread
+constexpr int kMobThreads = (1 << kMobTileBits) / kMobElems;
+
+// LDS place of tile element e: one element of padding per 16, so that lanes
+// 16 and 256 elements apart meet different banks.
+__device__ __forceinline__ int mob_pad(int e) { return e + (e >> 4); }
+constexpr int kMobLds = (1 << kMobTileBits) + (1 << kMobTileBits >> 4);
+__device__ __forceinline__ int mob_field(int t, int p) {
+  return (t & ((1 << p) - 1)) | ((t >> p) << (p + 4));
+}
+// levels [j0, 4) of the four register bits
+template <typename T>
+__device__ __forceinline__ void mob_levels(T (&x)[kMobElems], int j0) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (j >= j0) {
+#pragma unroll
+      for (int k = 0; k < kMobElems; ++k)
+        if (k & (1 << j)) x[k] = Num<T>::sub(x[k], x[k ^ (1 << j)]);
     }
-    for (int i = tid; i < nt; i += NT) o[i] = m[i];
-    __syncthreads();
-  }
+}
+// the tile from layout `from` to layout `to`
+template <typename T>
+__device__ __forceinline__ void mob_exchange(T* m, T (&x)[kMobElems], int from, int to) {
+  const int a = mob_field(threadIdx.x, from), b = mob_field(threadIdx.x, to);
+#pragma unroll
+  for (int k = 0; k < kMobElems; ++k) m[mob_pad(a | (k << from))] = x[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kMobElems; ++k) x[k] = m[mob_pad(b | (k << to))];
+  __syncthreads();
 }
 
-// High pass: bits [lo, lo + G) of one instance. A work item is a block of
-// 2^G x 2^cb values: 2^cb consecutive low indices (coalesced) for each of
-// the 2^G settings of the group bits, for one setting of the other bits.
-template <typename MobT>
-__global__ void __launch_bounds__(kTileThreads)
-mobius_high_kernel(const InstDev* __restrict__ insts, const MobItem* __restrict__ items,
-                   int n_items, MobT* data) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  MobT* m = reinterpret_cast<MobT*>(smem);
-  const int tid = threadIdx.x;
-  constexpr int NT = kTileThreads;
+// Low pass: kMobTileBits consecutive bits from 0 (all d of them where d is
+// smaller: the elements past 2^d are neither read nor written, and no valid
+// element depends on them). The result goes to dst (in place allowed).
+template <typename InT, typename MobT>
+__global__ void __launch_bounds__(kMobThreads)
+mobius_low_kernel(const InstDev* __restrict__ insts, const MobItem* __restrict__ items,
+                  int n_items, const InT* src, MobT* dst, int src_is_values) {
+  static_assert(kMobTileBits == 12, "the rounds below cover 4 + 4 + 4 bits");
+  __shared__ MobT m[kMobLds];
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const MobItem w = items[it];
     const InstDev I = insts[w.inst];
-    const int G = w.G, lo = w.lo, cb = w.cb;
-    const int n = 1 << (G + cb);
-    const int64_t nchunk = (int64_t)1 << (lo - cb);
-    const int64_t cl = w.block % nchunk;          // which chunk of low indices
-    const int64_t rest = w.block / nchunk;        // the bits above the group
-    MobT* base = data + I.woff + (rest << (lo + G)) + (cl << cb);
-    for (int i = tid; i < n; i += NT) {
-      const int g = i >> cb, c = i & ((1 << cb) - 1);
-      m[i] = base[((int64_t)g << lo) + c];
+    const int nv = 1 << min(I.d, kMobTileBits);       // valid elements
+    const InT* s = src + (src_is_values ? I.voff : I.woff) + (w.block << kMobTileBits);
+    MobT* o = dst + I.woff + (w.block << kMobTileBits);
+    const int a = mob_field(threadIdx.x, 8);
+    MobT x[kMobElems];
+#pragma unroll
+    for (int k = 0; k < kMobElems; ++k) {
+      const int e = a | (k << 8);
+      x[k] = e < nv ? Num<MobT>::from_in(s[e]) : Num<MobT>::zero();
     }
-    __syncthreads();
-    for (int bit = 0; bit < G; ++bit) {
-      for (int p = tid; p < (n >> 1); p += NT) {
-        const int bb = bit + cb;
-        const int lo2 = ((p >> bb) << (bb + 1)) | (p & ((1 << bb) - 1));
-        const int hi2 = lo2 | (1 << bb);
-        m[hi2] = Num<MobT>::sub(m[hi2], m[lo2]);
-      }
-      __syncthreads();
+    mob_exchange<MobT>(m, x, 8, 0);
+    mob_levels<MobT>(x, 0);
+    mob_exchange<MobT>(m, x, 0, 4);
+    mob_levels<MobT>(x, 0);
+    mob_exchange<MobT>(m, x, 4, 8);
+    mob_levels<MobT>(x, 0);
+#pragma unroll
+    for (int k = 0; k < kMobElems; ++k) {
+      const int e = a | (k << 8);
+      if (e < nv) o[e] = x[k];
     }
-    for (int i = tid; i < n; i += NT) {
-      const int g = i >> cb, c = i & ((1 << cb) - 1);
-      base[((int64_t)g << lo) + c] = m[i];
-    }
-    __syncthreads();
   }
 }
 
-// Convert a Moebius-type buffer back to the storage type (fsi_mobius).
-template <typename MobT, typename OutT>
-__global__ void convert_kernel(const MobT* __restrict__ a, OutT* __restrict__ o, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    o[i] = (OutT)to_sweep(a[i], (double*)nullptr);
+// High pass: bits [lo, lo + G), 1 <= G <= kMobGroup, lo >= kMobTileBits.
+template <typename MobT>
+__global__ void __launch_bounds__(kMobThreads)
+mobius_high_kernel(const InstDev* __restrict__ insts, const MobItem* __restrict__ items,
+                   int n_items, MobT* data) {
+  static_assert(kMobGroup == 8, "two rounds of four bits");
+  __shared__ MobT m[kMobLds];
+  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const MobItem w = items[it];
+    const InstDev I = insts[w.inst];
+    const int G = w.G, lo = w.lo, cb = w.cb;         // G + cb = kMobTileBits
+    const int64_t cl = w.block & (((int64_t)1 << (lo - cb)) - 1);   // which run of low indices
+    const int64_t rest = w.block >> (lo - cb);                      // the bits above the group
+    MobT* base = data + I.woff + (rest << (lo + G)) + (cl << cb);
+    const int cmask = (1 << cb) - 1;
+    auto at = [&](int e) { return ((int64_t)(e >> cb) << lo) + (e & cmask); };
+    // the lowest (at most) four group bits at p0 .. 11, then those above
+    // them, the last of tile bits 8 .. 11
+    const int p0 = min(cb, 8);
+    MobT x[kMobElems];
+    const int a0 = mob_field(threadIdx.x, p0);
+#pragma unroll
+    for (int k = 0; k < kMobElems; ++k) x[k] = base[at(a0 | (k << p0))];
+    mob_levels<MobT>(x, cb - p0);
+    if (G > 4) {
+      mob_exchange<MobT>(m, x, p0, 8);
+      mob_levels<MobT>(x, cb - 4);
+    }
+    const int a1 = mob_field(threadIdx.x, 8);
+#pragma unroll
+    for (int k = 0; k < kMobElems; ++k) base[at(a1 | (k << 8))] = x[k];
+  }
 }
 
 // ---------------------------------------------------------------- launchers
@@ -495,27 +530,18 @@ hipError_t set_lds(K kernel, size_t bytes) {
 }  // namespace
 
 template <typename InT, typename MobT, typename SwT>
-hipError_t configure_path(int algo, size_t tile_lds, size_t mob_lds) {
-  hipError_t e;
+hipError_t configure_path(int algo, size_t tile_lds) {
   if (algo == ALGO_FUSED) return set_lds(tile_kernel<InT, MobT, SwT, true>, tile_lds);
-  if ((e = set_lds(mobius_low_kernel<InT, MobT>, mob_lds)) != hipSuccess) return e;
-  if ((e = set_lds(mobius_high_kernel<MobT>, mob_lds)) != hipSuccess) return e;
   return set_lds(tile_kernel<MobT, MobT, SwT, false>, tile_lds);
 }
 
-hipError_t configure_kernels(int prec, int algo, size_t tile_lds, size_t mob_lds) {
-  hipError_t e;
-  // fsi_mobius runs in the storage type
-  if ((e = set_lds(mobius_low_kernel<double, double>, mob_lds)) != hipSuccess) return e;
-  if ((e = set_lds(mobius_low_kernel<float, float>, mob_lds)) != hipSuccess) return e;
-  if ((e = set_lds(mobius_high_kernel<double>, mob_lds)) != hipSuccess) return e;
-  if ((e = set_lds(mobius_high_kernel<float>, mob_lds)) != hipSuccess) return e;
+hipError_t configure_kernels(int prec, int algo, size_t tile_lds) {
   switch (prec) {
-    case PREC_F64: return configure_path<double, double, double>(algo, tile_lds, mob_lds);
-    case PREC_F32: return configure_path<float, float, float>(algo, tile_lds, mob_lds);
-    case PREC_F32_COMP: return configure_path<float, TwoFloat, float>(algo, tile_lds, mob_lds);
-    case PREC_F32_FP64MOB: return configure_path<float, double, float>(algo, tile_lds, mob_lds);
-    case PREC_F32_FP64REG: return configure_path<float, double, double>(algo, tile_lds, mob_lds);
+    case PREC_F64: return configure_path<double, double, double>(algo, tile_lds);
+    case PREC_F32: return configure_path<float, float, float>(algo, tile_lds);
+    case PREC_F32_COMP: return configure_path<float, TwoFloat, float>(algo, tile_lds);
+    case PREC_F32_FP64MOB: return configure_path<float, double, float>(algo, tile_lds);
+    case PREC_F32_FP64REG: return configure_path<float, double, double>(algo, tile_lds);
   }
   return hipErrorInvalidValue;
 }
@@ -528,6 +554,23 @@ int num_stages(const LaunchArgs& a) {
     return fast_launches(a.fast) + (a.n_tile_items > 0) + (a.n_generic > 0) +
            2 * (a.n_wide_items > 0) + (a.n_red_chunks > 0);
   return 3 + a.n_mob_passes;
+}
+
+template <typename InT, typename MobT>
+hipError_t launch_mob_low(const LaunchArgs& a, const void* src, int src_is_values, hipStream_t st) {
+  const int grid = std::min(a.n_mob_low, a.grid_mob);
+  hipLaunchKernelGGL((mobius_low_kernel<InT, MobT>), dim3(grid), dim3(kMobThreads), 0, st, a.insts,
+                     a.mob_low, a.n_mob_low, static_cast<const InT*>(src),
+                     static_cast<MobT*>(a.work), src_is_values);
+  return hipGetLastError();
+}
+template <typename MobT>
+hipError_t launch_mob_high(const LaunchArgs& a, int p, hipStream_t st) {
+  if (a.n_mob_items[p] == 0) return hipSuccess;
+  const int grid = std::min(a.n_mob_items[p], a.grid_mob);
+  hipLaunchKernelGGL(mobius_high_kernel<MobT>, dim3(grid), dim3(kMobThreads), 0, st, a.insts,
+                     a.mob_items[p], a.n_mob_items[p], static_cast<MobT*>(a.work));
+  return hipGetLastError();
 }
 
 template <typename InT, typename MobT, typename SwT>
@@ -589,19 +632,8 @@ hipError_t launch_stage_t(const LaunchArgs& a, int stage, hipStream_t st) {
                        static_cast<const InT*>(a.values), a.Y, nullptr);
     return hipGetLastError();
   }
-  if (stage == 0) {
-    hipLaunchKernelGGL((mobius_low_kernel<InT, MobT>), dim3(a.grid_tile), dim3(kTileThreads),
-                       a.mob_lds, st, a.classes, a.insts, a.tile_items, a.n_tile_items,
-                       static_cast<const InT*>(a.values), static_cast<MobT*>(a.work), 1);
-    return hipGetLastError();
-  }
-  if (stage <= a.n_mob_passes) {
-    const int p = stage - 1;
-    if (a.n_mob_items[p] == 0) return hipSuccess;
-    hipLaunchKernelGGL(mobius_high_kernel<MobT>, dim3(a.grid_tile), dim3(kTileThreads), a.mob_lds,
-                       st, a.insts, a.mob_items[p], a.n_mob_items[p], static_cast<MobT*>(a.work));
-    return hipGetLastError();
-  }
+  if (stage == 0) return launch_mob_low<InT, MobT>(a, a.values, 1, st);
+  if (stage <= a.n_mob_passes) return launch_mob_high<MobT>(a, stage - 1, st);
   hipLaunchKernelGGL((tile_kernel<MobT, MobT, SwT, false>), dim3(a.grid_tile), dim3(kTileThreads),
                      a.tile_lds, st, a.classes, a.insts, a.tile_items, a.n_tile_items,
                      static_cast<const MobT*>(a.work), a.Y, a.Ylo);
@@ -630,22 +662,11 @@ hipError_t launch_apply(const LaunchArgs& a, hipStream_t st) {
 
 template <typename T>
 hipError_t launch_mobius_t(const LaunchArgs& a, hipStream_t st) {
-  hipError_t e;
-  auto km = mobius_low_kernel<T, T>;
   // in place on the caller's buffer: the instance's work offset is 0 and
   // the source is the buffer itself (src_is_values = 0 -> offset woff)
-  hipLaunchKernelGGL(km, dim3(a.grid_tile), dim3(kTileThreads), a.mob_lds, st, a.classes,
-                     a.insts, a.all_tiles, a.n_all_tiles, static_cast<const T*>(a.work),
-                     static_cast<T*>(a.work), 0);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  auto kh = mobius_high_kernel<T>;
-  for (int p = 0; p < a.n_mob_passes; ++p) {
-    if (a.n_mob_items[p] == 0) continue;
-    hipLaunchKernelGGL(kh, dim3(a.grid_tile), dim3(kTileThreads), a.mob_lds, st, a.insts,
-                       a.mob_items[p], a.n_mob_items[p], static_cast<T*>(a.work));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  hipError_t e = launch_mob_low<T, T>(a, a.work, 0, st);
+  for (int p = 0; p < a.n_mob_passes && e == hipSuccess; ++p) e = launch_mob_high<T>(a, p, st);
+  return e;
 }
 
 hipError_t launch_mobius(const LaunchArgs& a, hipStream_t st) {
