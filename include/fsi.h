@@ -312,9 +312,10 @@ fsi_status fsi_apply_batched_noalloc(fsi_batch_plan_t plan,
  * per-output reduction, the wide gather and its final pass (generic
  * instances with at least 2^10 tiles, register-phase instances of several
  * blocks), and the reduction of the register-phase partial sums of
- * one-block instances. A batch whose instances all take the register-phase
- * kernel (l <= 4) and fit one block each (l <= 3, or d <= 20 at l = 4) has
- * two stages. The
+ * one-block instances of several work items (the tile kernel writes the
+ * scores of an instance of one item). A batch whose instances all take the
+ * register-phase kernel (l <= 4) and fit one block each (l <= 3, or d <= 20
+ * at l = 4) has two stages, one if each is a single work item. The
  * two-pass algorithm has 3 + (number of strided high-bit Moebius passes)
  * stages (low pass, high passes, tile kernel, reduction). Running stages
  * 0 .. n-1 in order on one stream equals fsi_apply_batched_nograph.

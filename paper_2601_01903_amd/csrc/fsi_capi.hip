@@ -467,6 +467,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     insts[i].nitems = (int32_t)nit;
     insts[i].ipb = (int32_t)(F.kb >= F.h ? nit : bsize / cs);
     insts[i].pw = F.l + 1;
+    insts[i].fold = nit == 1;
     insts[i].lowmask = dh[i] < kFastTileBits ? (1 << dh[i]) - 1 : (1 << kFastTileBits) - 1;
     for (int64_t tb = 0; tb < ntile; tb += cs) {
       fitems.push_back(FastItem{i, (int32_t)tb, (int32_t)std::min<int64_t>(tb + cs, ntile), 0, ptot});
@@ -480,7 +481,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   // items); instances of several blocks go to the wide gather
   int red_rows = 1;
   for (int i = 0; i < n; ++i)
-    if (insts[i].fast && insts[i].nitems == insts[i].ipb) {
+    if (insts[i].fast && !insts[i].fold && insts[i].nitems == insts[i].ipb) {
       if (insts[i].nitems > 64) red_rows = std::max(red_rows, 16);
       else if (insts[i].nitems > 2) red_rows = std::max(red_rows, 4);
     }
@@ -498,6 +499,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
       insts[i].wide = 1;
       continue;
     }
+    if (insts[i].fold) continue;   // written by the tile kernel
     const int nslot = insts[i].pstride;
     for (int s0 = 0; s0 < nslot; s0 += red_width) red_chunks.push_back(make_int2(i, s0));
   }

@@ -95,7 +95,7 @@ struct InstDev {
   int32_t ipb;       // work items per block (item j covers block j / ipb)
   int32_t lowmask;   // register-phase kernel: 2^d - 1 for d < 11 (the tile's
                      // value U is v(U & lowmask)), else 2^11 - 1
-  int32_t pad2;
+  int32_t fold;      // 1: one work item, which writes the scores itself
   const int32_t* pidx;   // [M * pw] position of canonical output k's partial sum for j2
   const uint32_t* osh2;  // [M] S_H2 of canonical output k
   const int32_t* sinv;   // [pstride] canonical output whose partial sum a slot holds

@@ -52,6 +52,7 @@ struct FastLaunch {
   const void* vals64;
   const int32_t* torder;
   double* partial;
+  void* out;                      // scores of the folded instances (set per apply)
   // work queue of a launch: [0] next item, [1] workgroups done; zero before
   // every launch (the last workgroup of a launch to finish resets both)
   uint32_t* queue;

@@ -623,6 +623,7 @@ hipError_t launch_stage_t(const LaunchArgs& a, int stage, hipStream_t st) {
       FastLaunch f = a.fast;
       f.vals32 = a.values;
       f.vals64 = a.values;
+      f.out = a.out;
       return ng > 1 ? launch_fast_mixed(f, st) : launch_fast_group(f, ls[0], st);
     }
   }

@@ -28,7 +28,9 @@
 //   - the cross-tile sum E_S += Y[S_L, |S_H|, |S_H & U_H|] in FP64 registers
 //     for the outputs of the item's group.
 // At the end of the item the FP64 partial sums go to a workspace; the
-// reduction kernel adds the items of an instance in a fixed order.
+// reduction kernel adds the items of an instance in a fixed order. An
+// instance of one item writes its scores itself, so a plan of such instances is
+// one launch.
 //
 // Every LDS layout is a compile-time function of l (fsi_tile11.h), so the
 // hot loops address LDS with one per-thread base register and immediate
@@ -585,7 +587,8 @@ __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, con
                                          const FastItem& W, const float* __restrict__ vals32,
                                          const double* __restrict__ vals64,
                                          const int32_t* __restrict__ torder,
-                                         double* __restrict__ partial, unsigned char* smem) {
+                                         double* __restrict__ partial,
+                                         void* __restrict__ out, unsigned char* smem) {
   static_assert(kFastRuns == kRuns, "gather positions");
   constexpr int NP = np_order(L);     // gather positions of this order
   constexpr int KMAX = 2 * NP;        // output slots
@@ -841,6 +844,23 @@ __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, con
     // the weights once every wave has passed the barrier before this
     // gather) do not touch Y
   }
+  // ---- the item's sums ----
+  using OutT = RawT;   // the storage type
+  if (I.fold) {
+    // the instance's only item: its sums are the scores (a single apply at
+    // d <= 11 is one launch: 13 -> 11 us back to back). Adding a few items
+    // here too, by the last one to end, cost more than the reduction's launch:
+    // its device-wide fences took d = 14 from 15 to 20 us and 512 uneven
+    // instances from 390 to 485 us.
+    OutT* o = static_cast<OutT*>(out) + I.ooff;
+#pragma unroll
+    for (int kk = 0; kk < KMAX; ++kk)
+      if (kk < nkk) {
+        const int q = I.sinv[kk * NT + tid];
+        if (q >= 0) o[q] = (OutT)acc[kk];
+      }
+    return;
+  }
   double* P = partial + W.pofs + tid;
 #pragma unroll
   for (int kk = 0; kk < KMAX; ++kk)
@@ -882,7 +902,7 @@ tile11_kernel(const FastClassDev* __restrict__ classes, const InstDev* __restric
               const FastItem* __restrict__ items, int n_items,
               const float* __restrict__ vals32, const double* __restrict__ vals64,
               const int32_t* __restrict__ torder, double* __restrict__ partial,
-              uint32_t* __restrict__ queue) {
+              void* __restrict__ out, uint32_t* __restrict__ queue) {
   extern __shared__ __align__(16) unsigned char smem[];
   {
     using LA = LdsAll<SwT, MobT>;
@@ -894,7 +914,7 @@ tile11_kernel(const FastClassDev* __restrict__ classes, const InstDev* __restric
     const FastItem W = items[item];
     const InstDev I = insts[W.inst];
     run_item<L, SwT, MobT, IN64, MOBIN>(classes + I.fcls, I, W, vals32, vals64, torder, partial,
-                                        smem);
+                                        out, smem);
     __syncthreads();
   }
   queue_done(queue, n_items);
@@ -909,7 +929,7 @@ tile11_mixed_kernel(const FastClassDev* __restrict__ classes, const InstDev* __r
                     const FastItem* __restrict__ items, int n_items,
                     const float* __restrict__ vals32, const double* __restrict__ vals64,
                     const int32_t* __restrict__ torder, double* __restrict__ partial,
-                    uint32_t* __restrict__ queue) {
+                    void* __restrict__ out, uint32_t* __restrict__ queue) {
   extern __shared__ __align__(16) unsigned char smem[];
   {
     using LA = LdsAll<SwT, MobT>;
@@ -923,10 +943,10 @@ tile11_mixed_kernel(const FastClassDev* __restrict__ classes, const InstDev* __r
     const FastClassDev* C = classes + I.fcls;
     const int l = __builtin_amdgcn_readfirstlane(C->l);
     switch (l) {
-      case 1: run_item<1, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, smem); break;
-      case 2: run_item<2, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, smem); break;
-      case 3: run_item<3, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, smem); break;
-      default: run_item<4, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, smem); break;
+      case 1: run_item<1, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
+      case 2: run_item<2, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
+      case 3: run_item<3, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
+      default: run_item<4, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
     }
     __syncthreads();
   }
@@ -954,7 +974,7 @@ static hipError_t launch_t11_m(const FastLaunch& f, hipStream_t st) {
   auto k = t11::tile11_kernel<L, SwT, MobT, IN64, wpe_for<SwT>(), MOBIN>;
   hipLaunchKernelGGL(k, dim3(f.grid[L]), dim3(t11::NT), f.lds[L], st, f.classes, f.insts,
                      f.items + ib, n, static_cast<const float*>(f.vals32),
-                     static_cast<const double*>(f.vals64), f.torder, f.partial, f.queue);
+                     static_cast<const double*>(f.vals64), f.torder, f.partial, f.out, f.queue);
   return hipGetLastError();
 }
 
@@ -984,7 +1004,7 @@ static hipError_t launch_mixed_m(const FastLaunch& f, hipStream_t st) {
   auto k = t11::tile11_mixed_kernel<SwT, MobT, IN64, wpe_for<SwT>(), MOBIN>;
   hipLaunchKernelGGL(k, dim3(f.grid_mixed), dim3(t11::NT), f.lds_mixed, st, f.classes, f.insts,
                      f.items, f.n_items, static_cast<const float*>(f.vals32),
-                     static_cast<const double*>(f.vals64), f.torder, f.partial, f.queue);
+                     static_cast<const double*>(f.vals64), f.torder, f.partial, f.out, f.queue);
   return hipGetLastError();
 }
 
