@@ -20,6 +20,7 @@
 #include "fsi_abi.h"
 #include "fsi_internal.h"
 #include "fsi_kernels.h"
+#include "fsi_tile11.h"
 
 using namespace fsi;
 
@@ -101,6 +102,8 @@ struct fsi_batch_plan_s {
   double* wide_partial = nullptr;  // wide gather partial sums
   std::vector<FastClassHost> fclasses;
   std::vector<int> fast_of;        // per class: index into fclasses or -1
+  std::vector<FastClassHost> hclasses;
+  std::vector<int> high_of;        // per class: index into hclasses (orders 5, 6) or -1
   LaunchArgs args{};
   // bytes of each device workspace an apply writes and reads back (partial
   // sums, per-tile results, wide-gather partials, two-pass Moebius
@@ -292,19 +295,25 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
         return fail(FSI_ERR_UNSUPPORTED, "register-phase kernel does not apply to instance " +
                                              std::to_string(i));
       }
-      int b = want_fast ? fb : choose_tile_bits(dh[i], lh[i], prec, opts.tile_bits);
-      if (!want_fast && opts.tile_bits == 0) b = std::max(1, b + sc.tb_shift);
-      std::string err = build_class(want_fast ? dfast : dh[i], lh[i], b, algo, opts.index,
-                                    opts.input, &C);
+      // the same phases with the per-tile results in memory: orders 5 and 6,
+      // where the kernel is left to the plan
+      const bool want_high = kern == FSI_KERNEL_AUTO && algo == ALGO_FUSED &&
+                             fast_supported(prec) && lh[i] >= kHighMinL && lh[i] <= kHighMaxL &&
+                             (opts.tile_bits == 0 || opts.tile_bits == fb);
+      const bool phased = want_fast || want_high;
+      int b = phased ? fb : choose_tile_bits(dh[i], lh[i], prec, opts.tile_bits);
+      if (!phased && opts.tile_bits == 0) b = std::max(1, b + sc.tb_shift);
+      std::string err = build_class(phased ? dfast : dh[i], lh[i], b, algo, opts.index,
+                                    opts.input, &C, !phased);
       if (!err.empty()) { return fail(FSI_ERR_INTERNAL, err); }
-      if (want_fast && dh[i] < fb) {
+      if (phased && dh[i] < fb) {
         // the outputs are those of the instance's own d
         C.out_masks = canonical_masks(dh[i], lh[i]);
         C.M = (int)C.out_masks.size();
       }
       const int64_t need = std::max<int64_t>(2 * (int64_t)C.lds_elems * (int64_t)sweep_elem_bytes(prec),
                                              ((int64_t)1 << b) * (int64_t)mob_elem_bytes(prec));
-      if (!want_fast && need > kLdsBudget) {
+      if (!phased && need > kLdsBudget) {
         return fail(FSI_ERR_INVALID_ARG, "tile_bits too large for LDS at this l and precision");
       }
       int fidx = -1;
@@ -316,6 +325,15 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
         P->fclasses.push_back(std::move(F));
       }
       P->fast_of.push_back(fidx);
+      int hidx = -1;
+      if (want_high) {
+        FastClassHost F;
+        err = build_high_class(C, &F);
+        if (!err.empty()) { return fail(FSI_ERR_INTERNAL, err); }
+        hidx = (int)P->hclasses.size();
+        P->hclasses.push_back(std::move(F));
+      }
+      P->high_of.push_back(hidx);
       cls_index[key] = (int)P->classes.size();
       P->classes.push_back(std::move(C));
       it = cls_index.find(key);
@@ -342,7 +360,18 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     insts[i].woff = single ? 0 : wtot;
     // per-tile results in HBM only for the generic kernel (the register-phase
     // kernel keeps them in LDS)
-    if (P->fast_of[P->cls_of[i]] < 0) ytot += ((int64_t)1 << C.h) * C.Ysize;
+    const int hc = P->high_of[P->cls_of[i]];
+    if (hc >= 0) {
+      insts[i].high = 1;
+      insts[i].fcls = hc;
+      insts[i].pstride = t11::ysize(lh[i]);
+      insts[i].nout = C.M;
+      insts[i].nhigh = C.h;
+      insts[i].lowmask = dh[i] < kFastTileBits ? (1 << dh[i]) - 1 : (1 << kFastTileBits) - 1;
+      ytot += ((int64_t)1 << C.h) * t11::ysize(lh[i]);
+    } else if (P->fast_of[P->cls_of[i]] < 0) {
+      ytot += ((int64_t)1 << C.h) * C.Ysize;
+    }
     wtot += (int64_t)1 << dh[i];
   }
   // register-phase work items: runs of tiles of one instance, in the order of
@@ -489,6 +518,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   std::vector<int2> red_chunks;
   int n_generic = 0;
   for (int i = 0; i < n; ++i) {
+    if (insts[i].high) continue;
     if (!insts[i].fast) {
       // generic fused instances with many tiles: the wide gather
       insts[i].wide = (algo == ALGO_FUSED && P->classes[P->cls_of[i]].h >= kWideMinH) ? 1 : 0;
@@ -566,9 +596,34 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   // generic tiles: larger tiles first, so a persistent grid finishes evenly
   std::vector<TileItem> tiles;
   for (int i = 0; i < n; ++i) {
-    if (insts[i].fast) continue;
+    if (insts[i].fast || insts[i].high) continue;
     const ClassHost& C = P->classes[P->cls_of[i]];
     for (int64_t t = 0; t < ((int64_t)1 << C.h); ++t) tiles.push_back(TileItem{i, (int32_t)t});
+  }
+  // tiles of the orders 5 and 6, and their reduction: more rows of tiles per
+  // output while the outputs are too few to fill the machine
+  std::vector<TileItem> htiles;
+  std::vector<int2> hchunks;
+  int hbeg[kHighMaxL - kHighMinL + 2] = {0}, high_rows = 1;
+  {
+    int64_t outs = 0, most = 1;
+    for (int l = kHighMinL; l <= kHighMaxL; ++l) {
+      hbeg[l - kHighMinL] = (int)htiles.size();
+      for (int i = 0; i < n; ++i) {
+        if (!insts[i].high || lh[i] != l) continue;
+        outs += insts[i].nout;
+        most = std::max<int64_t>(most, (int64_t)1 << insts[i].nhigh);
+        for (int64_t t = 0; t < ((int64_t)1 << insts[i].nhigh); ++t)
+          htiles.push_back(TileItem{i, (int32_t)t});
+      }
+    }
+    hbeg[kHighMaxL - kHighMinL + 1] = (int)htiles.size();
+    while (high_rows < 16 && high_rows * 4 <= most && outs * high_rows < (int64_t)1 << 18)
+      high_rows *= 4;
+    const int width = kFastThreads / high_rows;
+    for (int i = 0; i < n; ++i)
+      if (insts[i].high)
+        for (int k = 0; k < insts[i].nout; k += width) hchunks.push_back(make_int2(i, k));
   }
   std::stable_sort(tiles.begin(), tiles.end(), [&](const TileItem& a, const TileItem& b) {
     return P->classes[P->cls_of[a.inst]].b > P->classes[P->cls_of[b.inst]].b;
@@ -627,6 +682,21 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     fo[f].zrow = stage(buf, F.zrow.data(), F.zrow.size());
     fo[f].uperm = stage(buf, F.uperm.data(), F.uperm.size());
   }
+  std::vector<FastClassDev> hdev(P->hclasses.size());
+  struct HOffs { size_t lam, unit_mask, zrow, uperm, hword, hhigh; };
+  std::vector<HOffs> ho(P->hclasses.size());
+  for (size_t f = 0; f < P->hclasses.size(); ++f) {
+    const FastClassHost& F = P->hclasses[f];
+    ho[f].lam = stage(buf, F.lam.data(), F.lam.size());
+    ho[f].unit_mask = stage(buf, F.unit_mask.data(), F.unit_mask.size());
+    ho[f].zrow = stage(buf, F.zrow.data(), F.zrow.size());
+    ho[f].uperm = stage(buf, F.uperm.data(), F.uperm.size());
+    ho[f].hword = stage(buf, F.hword.data(), F.hword.size());
+    ho[f].hhigh = stage(buf, F.hhigh.data(), F.hhigh.size());
+  }
+  const size_t o_hcls = stage(buf, hdev.data(), hdev.size());
+  const size_t o_htiles = stage(buf, htiles.data(), htiles.size());
+  const size_t o_hchunks = stage(buf, hchunks.data(), hchunks.size());
   const size_t o_fcls = stage(buf, fdev.data(), fdev.size());
   const size_t o_fitems = stage(buf, fitems.data(), fitems.size());
   const size_t o_red = stage(buf, red_chunks.data(), red_chunks.size());
@@ -692,6 +762,21 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
                           ? nullptr
                           : reinterpret_cast<const int32_t*>(A + fo[insts[i].fcls].sinv);
     }
+  for (size_t f = 0; f < P->hclasses.size(); ++f) {
+    const FastClassHost& F = P->hclasses[f];
+    FastClassDev& D = hdev[f];
+    D.d = F.d; D.l = F.l; D.h = F.h; D.M = F.M;
+    D.lam = reinterpret_cast<const double*>(A + ho[f].lam);
+    D.unit_mask = reinterpret_cast<const int32_t*>(A + ho[f].unit_mask);
+    D.zrow = reinterpret_cast<const int32_t*>(A + ho[f].zrow);
+    D.uperm = reinterpret_cast<const int32_t*>(A + ho[f].uperm);
+  }
+  std::memcpy(buf.data() + o_hcls, hdev.data(), hdev.size() * sizeof(FastClassDev));
+  for (int i = 0; i < n; ++i)
+    if (insts[i].high) {
+      insts[i].hword = reinterpret_cast<const uint32_t*>(A + ho[insts[i].fcls].hword);
+      insts[i].hhigh = reinterpret_cast<const uint32_t*>(A + ho[insts[i].fcls].hhigh);
+    }
   // instance descriptors carry the fast fields filled above
   std::memcpy(buf.data() + o_inst, insts.data(), insts.size() * sizeof(InstDev));
   e = hipMemcpy(P->arena, buf.data(), buf.size(), hipMemcpyHostToDevice);
@@ -725,7 +810,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   size_t tile_lds = 0;
   for (size_t c = 0; c < P->classes.size(); ++c) {
     const ClassHost& C = P->classes[c];
-    if (P->fast_of[c] >= 0) continue;
+    if (P->fast_of[c] >= 0 || P->high_of[c] >= 0) continue;
     tile_lds = std::max<size_t>(tile_lds, std::max<size_t>(2 * (size_t)C.lds_elems * sweep_elem_bytes(prec),
                                                            ((size_t)1 << C.b) * mob_elem_bytes(prec)));
   }
@@ -769,6 +854,21 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   a.n_red_chunks = (int)red_chunks.size();
   a.red_rows = red_rows;
   a.grid_red_chunks = std::max(1, std::min<int>((int)red_chunks.size(), n_cu * 8));
+  a.high = HighLaunch{};
+  if (!htiles.empty()) {
+    e = configure_high(prec);
+    if (e != hipSuccess) { return fail(FSI_ERR_HIP, std::string("configure_high: ") + hipGetErrorString(e)); }
+    a.high.prec = prec;
+    a.high.n_cu = n_cu;
+    a.high.mobius_in = opts.input == FSI_INPUT_MOBIUS;
+    a.high.classes = reinterpret_cast<const FastClassDev*>(A + o_hcls);
+    a.high.insts = a.insts;
+    a.high.items = reinterpret_cast<const TileItem*>(A + o_htiles);
+    for (int q = 0; q < kHighMaxL - kHighMinL + 2; ++q) a.high.lbeg[q] = hbeg[q];
+    a.high.chunks = reinterpret_cast<const int2*>(A + o_hchunks);
+    a.high.n_chunks = (int)hchunks.size();
+    a.high.red_rows = high_rows;
+  }
   a.fast = FastLaunch{};
   a.fast.n_items = (int)fitems.size();
   if (!fitems.empty()) {

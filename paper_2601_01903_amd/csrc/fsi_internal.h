@@ -74,6 +74,8 @@ struct FastClassHost {
   // [nkk * 256] canonical output of slot kk * 256 + t for one-block classes
   // (its j2 = 0 slot), -1 for an unused slot; empty for blocked classes
   std::vector<int32_t> sinv;
+  // orders 5 and 6 (build_high_class): result word and S_H of each output
+  std::vector<uint32_t> hword, hhigh;
 };
 
 struct InstDev {
@@ -95,9 +97,15 @@ struct InstDev {
   int32_t ipb;       // work items per block (item j covers block j / ipb)
   int32_t lowmask;   // register-phase kernel: 2^d - 1 for d < 11 (the tile's
                      // value U is v(U & lowmask)), else 2^11 - 1
+  int32_t high;      // 1: register-phase kernel of orders 5 and 6 (fcls its class, pstride
+                     // the per-tile results of a tile)
+  int32_t nout, nhigh;       // its outputs and high bits
   int32_t fold;      // 1: one work item, which writes the scores itself
   const int32_t* pidx;   // [M * pw] position of canonical output k's partial sum for j2
   const uint32_t* osh2;  // [M] S_H2 of canonical output k
+  const uint32_t* hword;  // orders 5, 6: [nout] per-tile result of output k at |S_H & U| = 0
+                          // | stride over |S_H & U| << 16
+  const uint32_t* hhigh;  // orders 5, 6: [nout] S_H of output k
   const int32_t* sinv;   // [pstride] canonical output whose partial sum a slot holds
                          // (one-block instances), -1 for an unused slot
 };
@@ -123,8 +131,11 @@ bool gfx950_device(int* dev, int* n_cu, std::string* why);
 double weight_full(int s, int t, int l, int index);
 // Largest sweep state of an in-tile sweep over b bits, in entries.
 int64_t sweep_peak_entries(int b, int l);
-// Builds all tables for one class; returns "" or an error message.
-std::string build_class(int d, int l, int b, int algo, int index, int mobius_in, ClassHost* out);
+// Builds the tables of one class: weights and outputs, and the generic
+// kernel's sweep and result tables unless sweep_tables is false. Returns "" or
+// an error message.
+std::string build_class(int d, int l, int b, int algo, int index, int mobius_in, ClassHost* out,
+                        bool sweep_tables = true);
 // Low high bits per block of the register-phase kernel for (d, l): h = d - 11
 // when every output fits the workgroup's slots, else the most that fit; -1
 // when the kernel does not apply.
@@ -134,5 +145,8 @@ int fast_output_slots(int d, int l);
 // Builds the register-phase kernel tables from an already built fused class
 // with b = 11 and l <= 4 (its final weights and output order).
 std::string build_fast_class(const ClassHost& C, FastClassHost* out);
+// The same for the kernel of orders 5 and 6: unit maps, weights, and the
+// per-tile result each output takes.
+std::string build_high_class(const ClassHost& C, FastClassHost* out);
 
 }  // namespace fsi

@@ -73,6 +73,24 @@ bool fast_supported(int prec);
 size_t fast_lds_bytes(int prec, int l);
 int fast_wgs_per_cu(int prec, int l);
 
+// Register-phase kernel of orders 5 and 6 (fsi_tile_high.hip): per-tile
+// results in memory, summed over the tiles by high_reduce_kernel. Items are
+// tiles, sorted by order: those of order kHighMinL + i are items
+// [lbeg[i], lbeg[i + 1]).
+constexpr int kHighMinL = 5, kHighMaxL = 6;
+struct HighLaunch {
+  int prec, n_cu, mobius_in;
+  const FastClassDev* classes;
+  const InstDev* insts;
+  const TileItem* items;
+  int lbeg[kHighMaxL - kHighMinL + 2];   // all zero: no such instance
+  const int2* chunks;                    // (instance, first output) per 256 / red_rows outputs
+  int n_chunks, red_rows;
+};
+hipError_t configure_high(int prec);
+hipError_t launch_high(const HighLaunch& f, int l, const void* vals, double* Y, hipStream_t st);
+hipError_t launch_high_reduce(const HighLaunch& f, const double* Y, void* out, hipStream_t st);
+
 // Wide gather (generic fused instances with many tiles): a work item is a
 // range of tiles and a group of up to kWideOuts outputs; each thread keeps
 // kWideK output accumulators in registers across the range. The partial
@@ -113,6 +131,7 @@ struct LaunchArgs {
   size_t tile_lds;
   const double* partial;      // register-phase kernel partial sums
   FastLaunch fast;            // n_items == 0: no register-phase stage
+  HighLaunch high;
   int n_generic;              // instances of the generic (or two-pass) path outside the wide gather
   const WideItem* wide_items;
   int n_wide_items, grid_wide;

@@ -216,7 +216,7 @@ reduce_kernel(const ClassDev* __restrict__ classes, const InstDev* __restrict__ 
     }
     const InstDev I = insts[lo];
     const int k = (int)(g - out_offset[lo]);
-    if (I.fast || I.wide) continue;   // written by fast_reduce_kernel / wide_final_kernel
+    if (I.fast || I.high || I.wide) continue;   // written by other kernels
     const ClassDev* C = classes + I.cls;
     const uint32_t oi = C->oinfo[k];
     const uint32_t SH = C->osh[k];
@@ -546,13 +546,21 @@ hipError_t configure_kernels(int prec, int algo, size_t tile_lds) {
   return hipErrorInvalidValue;
 }
 
+static int high_launches(const LaunchArgs& a) {
+  int n = 0;
+  for (int l = kHighMinL; l <= kHighMaxL; ++l)
+    n += a.high.lbeg[l - kHighMinL + 1] > a.high.lbeg[l - kHighMinL];
+  return n;
+}
+
 int num_stages(const LaunchArgs& a) {
-  // fused: [register-phase kernel per order l], [generic tile kernel],
-  //        [generic reduce], [wide gather, wide final], [register-phase reduce]
+  // fused: [register-phase kernel], [register-phase kernels of orders 5, 6],
+  //        [generic tile kernel], [generic reduce], [wide gather, wide final],
+  //        [reduce of orders 5, 6], [register-phase reduce]
   // two-pass: Moebius low pass, high passes, tile, reduce
   if (a.algo == ALGO_FUSED)
-    return fast_launches(a.fast) + (a.n_tile_items > 0) + (a.n_generic > 0) +
-           2 * (a.n_wide_items > 0) + (a.n_red_chunks > 0);
+    return fast_launches(a.fast) + high_launches(a) + (a.n_tile_items > 0) + (a.n_generic > 0) +
+           2 * (a.n_wide_items > 0) + (high_launches(a) > 0) + (a.n_red_chunks > 0);
   return 3 + a.n_mob_passes;
 }
 
@@ -573,66 +581,73 @@ hipError_t launch_mob_high(const LaunchArgs& a, int p, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <typename InT>
+hipError_t launch_fast_reduce(const LaunchArgs& a, hipStream_t st) {
+  InT* out = static_cast<InT*>(a.out);
+  if (a.red_rows == 1)
+    hipLaunchKernelGGL((fast_reduce_kernel<InT, 1>), dim3(a.grid_red_chunks), dim3(256), 0, st,
+                       a.insts, a.red_chunks, a.n_red_chunks, a.partial, out);
+  else if (a.red_rows == 4)
+    hipLaunchKernelGGL((fast_reduce_kernel<InT, 4>), dim3(a.grid_red_chunks), dim3(256), 0, st,
+                       a.insts, a.red_chunks, a.n_red_chunks, a.partial, out);
+  else
+    hipLaunchKernelGGL((fast_reduce_kernel<InT, 16>), dim3(a.grid_red_chunks), dim3(256), 0, st,
+                       a.insts, a.red_chunks, a.n_red_chunks, a.partial, out);
+  return hipGetLastError();
+}
+
+template <typename InT>
+hipError_t launch_reduce(const LaunchArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(reduce_kernel<InT>, dim3(a.grid_reduce), dim3(256), 0, st, a.classes,
+                     a.insts, a.n_inst, a.out_offset, a.total_out, a.Y, a.Ylo, a.partial,
+                     static_cast<InT*>(a.out));
+  return hipGetLastError();
+}
+
+// Stage `stage` of the fused algorithm: the launches num_stages counts, in order.
 template <typename InT, typename MobT, typename SwT>
-hipError_t launch_stage_t(const LaunchArgs& a, int stage, hipStream_t st) {
-  const int last = num_stages(a) - 1;
-  if (stage < 0 || stage > last) return hipErrorInvalidValue;
-  if (a.algo == ALGO_FUSED && a.n_red_chunks > 0 && stage == last) {
-    if (a.red_rows == 1)
-      hipLaunchKernelGGL((fast_reduce_kernel<InT, 1>), dim3(a.grid_red_chunks), dim3(256), 0, st,
-                         a.insts, a.red_chunks, a.n_red_chunks, a.partial,
-                         static_cast<InT*>(a.out));
-    else if (a.red_rows == 4)
-      hipLaunchKernelGGL((fast_reduce_kernel<InT, 4>), dim3(a.grid_red_chunks), dim3(256), 0, st,
-                         a.insts, a.red_chunks, a.n_red_chunks, a.partial,
-                         static_cast<InT*>(a.out));
-    else
-      hipLaunchKernelGGL((fast_reduce_kernel<InT, 16>), dim3(a.grid_red_chunks), dim3(256), 0, st,
-                         a.insts, a.red_chunks, a.n_red_chunks, a.partial,
-                         static_cast<InT*>(a.out));
-    return hipGetLastError();
-  }
-  if (a.algo == ALGO_FUSED && a.n_wide_items > 0) {
-    const int wfin = last - (a.n_red_chunks > 0);
-    if (stage == wfin - 1) {
-      hipLaunchKernelGGL(wide_gather_kernel, dim3(a.grid_wide), dim3(256), 0, st, a.classes,
-                         a.insts, a.wide_items, a.n_wide_items, a.out_offset, a.Y,
-                         a.partial, a.wide_partial);
-      return hipGetLastError();
-    }
-    if (stage == wfin) {
-      hipLaunchKernelGGL(wide_final_kernel<InT>, dim3(a.grid_wide_groups), dim3(256), 0, st,
-                         a.wide_groups, a.n_wide_groups, a.insts, a.out_offset, a.wide_partial,
-                         static_cast<InT*>(a.out));
-      return hipGetLastError();
-    }
-  }
-  if (a.algo != ALGO_FUSED
-          ? stage == last
-          : (a.n_generic > 0 &&
-             stage == last - (a.n_red_chunks > 0) - 2 * (a.n_wide_items > 0))) {
-    hipLaunchKernelGGL(reduce_kernel<InT>, dim3(a.grid_reduce), dim3(256), 0, st, a.classes,
-                       a.insts, a.n_inst, a.out_offset, a.total_out, a.Y, a.Ylo, a.partial,
-                       static_cast<InT*>(a.out));
-    return hipGetLastError();
-  }
-  if (a.algo == ALGO_FUSED) {
+hipError_t launch_fused_stage(const LaunchArgs& a, int stage, hipStream_t st) {
+  if (fast_launches(a.fast) > 0 && stage-- == 0) {
     int ls[kFastMaxL];
     const int ng = fast_groups(a.fast, ls);
-    if (stage < fast_launches(a.fast)) {
-      FastLaunch f = a.fast;
-      f.vals32 = a.values;
-      f.vals64 = a.values;
-      f.out = a.out;
-      return ng > 1 ? launch_fast_mixed(f, st) : launch_fast_group(f, ls[0], st);
-    }
+    FastLaunch f = a.fast;
+    f.vals32 = a.values;
+    f.vals64 = a.values;
+    f.out = a.out;
+    return ng > 1 ? launch_fast_mixed(f, st) : launch_fast_group(f, ls[0], st);
   }
-  if (a.algo == ALGO_FUSED) {
+  for (int l = kHighMinL; l <= kHighMaxL; ++l)
+    if (a.high.lbeg[l - kHighMinL + 1] > a.high.lbeg[l - kHighMinL] && stage-- == 0)
+      return launch_high(a.high, l, a.values, a.Y, st);
+  if (a.n_tile_items > 0 && stage-- == 0) {
     hipLaunchKernelGGL((tile_kernel<InT, MobT, SwT, true>), dim3(a.grid_tile), dim3(kTileThreads),
                        a.tile_lds, st, a.classes, a.insts, a.tile_items, a.n_tile_items,
                        static_cast<const InT*>(a.values), a.Y, nullptr);
     return hipGetLastError();
   }
+  if (a.n_generic > 0 && stage-- == 0) return launch_reduce<InT>(a, st);
+  if (a.n_wide_items > 0 && stage-- == 0) {
+    hipLaunchKernelGGL(wide_gather_kernel, dim3(a.grid_wide), dim3(256), 0, st, a.classes,
+                       a.insts, a.wide_items, a.n_wide_items, a.out_offset, a.Y, a.partial,
+                       a.wide_partial);
+    return hipGetLastError();
+  }
+  if (a.n_wide_items > 0 && stage-- == 0) {
+    hipLaunchKernelGGL(wide_final_kernel<InT>, dim3(a.grid_wide_groups), dim3(256), 0, st,
+                       a.wide_groups, a.n_wide_groups, a.insts, a.out_offset, a.wide_partial,
+                       static_cast<InT*>(a.out));
+    return hipGetLastError();
+  }
+  if (high_launches(a) > 0 && stage-- == 0) return launch_high_reduce(a.high, a.Y, a.out, st);
+  return launch_fast_reduce<InT>(a, st);
+}
+
+template <typename InT, typename MobT, typename SwT>
+hipError_t launch_stage_t(const LaunchArgs& a, int stage, hipStream_t st) {
+  const int last = num_stages(a) - 1;
+  if (stage < 0 || stage > last) return hipErrorInvalidValue;
+  if (a.algo == ALGO_FUSED) return launch_fused_stage<InT, MobT, SwT>(a, stage, st);
+  if (stage == last) return launch_reduce<InT>(a, st);
   if (stage == 0) return launch_mob_low<InT, MobT>(a, a.values, 1, st);
   if (stage <= a.n_mob_passes) return launch_mob_high<MobT>(a, stage - 1, st);
   hipLaunchKernelGGL((tile_kernel<MobT, MobT, SwT, false>), dim3(a.grid_tile), dim3(kTileThreads),

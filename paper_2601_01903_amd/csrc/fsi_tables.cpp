@@ -141,13 +141,75 @@ int64_t sweep_peak_entries(int b, int l) {
   return peak;
 }
 
-std::string build_class(int d, int l, int b, int algo, int index, int mobius_in, ClassHost* C) {
+std::string build_class(int d, int l, int b, int algo, int index, int mobius_in, ClassHost* C,
+                        bool sweep_tables) {
   if (!(1 <= l && l <= d && d <= kMaxD)) return "invalid (d, l)";
   if (!(1 <= b && b <= kMaxTileBits && b <= d)) return "invalid tile bits";
   const int h = d - b;
   C->d = d; C->l = l; C->b = b; C->h = h; C->algo = algo; C->mobius_in = mobius_in;
   if (mobius_in && algo != ALGO_FUSED) return "Moebius input needs the fused algorithm";
   C->M = (int)num_outputs(d, l);
+
+  C->out_masks = canonical_masks(d, l);
+
+  // ---- slots of the per-tile partial results ----
+  // fused:    (s_H, j_H), s_H in [0, min(l - s_L, h)], j_H in [0, s_H],
+  //           slot = s_H (s_H + 1) / 2 + j_H   (j_H = |S_H & U_H|)
+  // two-pass: s_H in [0, min(l - s_L, h)], slot = s_H
+  auto nslot = [&](int sL) {
+    const int top = std::min(l - sL, h);
+    if (top < 0) return 0;
+    return algo == ALGO_FUSED ? (top + 1) * (top + 2) / 2 : top + 1;
+  };
+  // ---- final-core weights per high popcount u ----
+  C->lam_soff.assign(l + 1, 0);
+  int off = 0;
+  for (int sL = 0; sL <= l; ++sL) {
+    C->lam_soff[sL] = off;
+    if (sL <= b) off += nslot(sL) * (b + 1);
+  }
+  C->lam_ublock = off;
+  C->lam.assign((size_t)(h + 1) * off, 0.0);
+  // two-pass: the weights also as double-doubles (their rounding error,
+  // for the compensated FP64 weight core)
+  if (algo != ALGO_FUSED) C->lam_lo.assign((size_t)(h + 1) * off, 0.0);
+  for (int u = 0; u <= h; ++u) {
+    for (int sL = 0; sL <= std::min(l, b); ++sL) {
+      double* blk = &C->lam[(size_t)u * off + C->lam_soff[sL]];
+      const int top = std::min(l - sL, h);
+      for (int sH = 0; sH <= top; ++sH) {
+        const int s = sL + sH;
+        if (algo == ALGO_FUSED) {
+          for (int j = 0; j <= sH; ++j) {
+            const int slot = sH * (sH + 1) / 2 + j;
+            if (mobius_in) {
+              // input already transformed: a tile with high index U_H feeds
+              // the outputs with S_H inside U_H (j = s_H) at t = t_L + |U_H|
+              const bool ok = j == sH && sH <= u;
+              for (int tL = sL; tL <= b; ++tL)
+                blk[slot * (b + 1) + tL] = ok ? (double)weight_q(s, tL + u, l, index) : 0.0;
+              continue;
+            }
+            const bool ok = j <= u && (sH - j) <= (h - u);
+            const int q = u + sH - j;
+            for (int tL = sL; tL <= b; ++tL)
+              blk[slot * (b + 1) + tL] = ok ? (double)lambda_q(s, tL, q, u, h, l, index) : 0.0;
+          }
+        } else {
+          double* blo = &C->lam_lo[(size_t)u * off + C->lam_soff[sL]];
+          for (int tL = sL; tL <= b; ++tL) {
+            const __float128 w = weight_q(s, tL + u, l, index);
+            blk[sH * (b + 1) + tL] = (double)w;
+            blo[sH * (b + 1) + tL] = (double)(w - (__float128)(double)w);
+          }
+        }
+      }
+    }
+  }
+
+  // the register-phase kernels have their own layouts (build_fast_class,
+  // build_high_class)
+  if (!sweep_tables) return "";
 
   // ---- counter states of the in-tile sweep (Sec. 4.3 state space) ----
   // Site k (k = 1..b) consumes tile bit b-k (most significant first). After
@@ -198,15 +260,6 @@ std::string build_class(int d, int l, int b, int algo, int index, int mobius_in,
   std::map<uint32_t, int32_t> final_base;  // S_L -> index of (S_L, t = s_L)
   for (size_t i = 0; i < sig_prev.size(); ++i) final_base[sig_prev[i]] = base_prev[i];
 
-  // ---- slots of the per-tile partial results ----
-  // fused:    (s_H, j_H), s_H in [0, min(l - s_L, h)], j_H in [0, s_H],
-  //           slot = s_H (s_H + 1) / 2 + j_H   (j_H = |S_H & U_H|)
-  // two-pass: s_H in [0, min(l - s_L, h)], slot = s_H
-  auto nslot = [&](int sL) {
-    const int top = std::min(l - sL, h);
-    if (top < 0) return 0;
-    return algo == ALGO_FUSED ? (top + 1) * (top + 2) / 2 : top + 1;
-  };
   const std::vector<uint32_t> low_masks = canonical_masks(b, std::min(l, b));
   std::map<uint32_t, int32_t> yoff;
   C->ytab.clear();
@@ -222,54 +275,7 @@ std::string build_class(int d, int l, int b, int algo, int index, int mobius_in,
   C->Ysize = (int)C->ytab.size();
   if (C->Ysize >= (1 << 24)) return "Y table too large";
 
-  // ---- final-core weights per high popcount u ----
-  C->lam_soff.assign(l + 1, 0);
-  int off = 0;
-  for (int sL = 0; sL <= l; ++sL) {
-    C->lam_soff[sL] = off;
-    if (sL <= b) off += nslot(sL) * (b + 1);
-  }
-  C->lam_ublock = off;
-  C->lam.assign((size_t)(h + 1) * off, 0.0);
-  // two-pass: the weights also as double-doubles (their rounding error,
-  // for the compensated FP64 weight core)
-  if (algo != ALGO_FUSED) C->lam_lo.assign((size_t)(h + 1) * off, 0.0);
-  for (int u = 0; u <= h; ++u) {
-    for (int sL = 0; sL <= std::min(l, b); ++sL) {
-      double* blk = &C->lam[(size_t)u * off + C->lam_soff[sL]];
-      const int top = std::min(l - sL, h);
-      for (int sH = 0; sH <= top; ++sH) {
-        const int s = sL + sH;
-        if (algo == ALGO_FUSED) {
-          for (int j = 0; j <= sH; ++j) {
-            const int slot = sH * (sH + 1) / 2 + j;
-            if (mobius_in) {
-              // input already transformed: a tile with high index U_H feeds
-              // the outputs with S_H inside U_H (j = s_H) at t = t_L + |U_H|
-              const bool ok = j == sH && sH <= u;
-              for (int tL = sL; tL <= b; ++tL)
-                blk[slot * (b + 1) + tL] = ok ? (double)weight_q(s, tL + u, l, index) : 0.0;
-              continue;
-            }
-            const bool ok = j <= u && (sH - j) <= (h - u);
-            const int q = u + sH - j;
-            for (int tL = sL; tL <= b; ++tL)
-              blk[slot * (b + 1) + tL] = ok ? (double)lambda_q(s, tL, q, u, h, l, index) : 0.0;
-          }
-        } else {
-          double* blo = &C->lam_lo[(size_t)u * off + C->lam_soff[sL]];
-          for (int tL = sL; tL <= b; ++tL) {
-            const __float128 w = weight_q(s, tL + u, l, index);
-            blk[sH * (b + 1) + tL] = (double)w;
-            blo[sH * (b + 1) + tL] = (double)(w - (__float128)(double)w);
-          }
-        }
-      }
-    }
-  }
-
   // ---- outputs ----
-  C->out_masks = canonical_masks(d, l);
   C->oinfo.resize(C->out_masks.size());
   C->osh.resize(C->out_masks.size());
   const uint32_t lowmask = (b >= 32) ? 0xFFFFFFFFu : ((1u << b) - 1);
@@ -299,14 +305,10 @@ int fast_output_slots(int d, int l) {
   return (int)(2 * (k == h ? t11::positions_needed(l, h) : t11::positions_blocked(l, k)));
 }
 
-std::string build_fast_class(const ClassHost& C, FastClassHost* F) {
+// Unit maps of the sweep phases and the final weights, for either kernel.
+static std::string build_phase_tables(const ClassHost& C, FastClassHost* F) {
   using namespace t11;
   const int l = C.l, b = C.b, h = C.h;
-  if (b != B) return "register-phase kernel needs 11-bit tiles";
-  if (C.algo != ALGO_FUSED) return "register-phase kernel needs the fused algorithm";
-  if (l > 4) return "register-phase kernel needs l <= 4";
-  F->mshift = meta_shift(l);
-  F->d = C.d; F->l = l; F->h = h; F->M = C.M; F->mobius_in = C.mobius_in;
   // phase-C units and their maps
   const int nu = n3(l);
   F->unit_mask.assign(nu, -1);
@@ -346,6 +348,19 @@ std::string build_fast_class(const ClassHost& C, FastClassHost* F) {
                 C.lam[(size_t)u * C.lam_ublock + C.lam_soff[sL] + slot * (b + 1) + sL + r];
         }
     }
+  return "";
+}
+
+std::string build_fast_class(const ClassHost& C, FastClassHost* F) {
+  using namespace t11;
+  const int l = C.l, b = C.b, h = C.h;
+  if (b != B) return "register-phase kernel needs 11-bit tiles";
+  if (C.algo != ALGO_FUSED) return "register-phase kernel needs the fused algorithm";
+  if (l > 4) return "register-phase kernel needs l <= 4";
+  F->mshift = meta_shift(l);
+  F->d = C.d; F->l = l; F->h = h; F->M = C.M; F->mobius_in = C.mobius_in;
+  const std::string err = build_phase_tables(C, F);
+  if (!err.empty()) return err;
   // partial sums: runs of two (S_L of ranks 2r and 2r + 1 among the S_L of
   // one size), taken by |S_L| (descending), then by what the run sums over
   // the high bits, then r, and dealt to wave units: unit u is position u / 4
@@ -444,6 +459,26 @@ std::string build_fast_class(const ClassHost& C, FastClassHost* F) {
         return "output slots are not one to one";
       F->sinv[slot] = (int32_t)k;
     }
+  }
+  return "";
+}
+
+std::string build_high_class(const ClassHost& C, FastClassHost* F) {
+  using namespace t11;
+  const int l = C.l, b = C.b;
+  if (b != B || C.algo != ALGO_FUSED) return "register-phase kernel needs fused 11-bit tiles";
+  if (l < kHighMinL || l > kHighMaxL) return "order outside the kernel's";
+  F->d = C.d; F->l = l; F->h = C.h; F->M = C.M; F->mobius_in = C.mobius_in;
+  const std::string err = build_phase_tables(C, F);
+  if (!err.empty()) return err;
+  if (ysize(l) >= 1 << 16) return "result word overflow";
+  const uint32_t lowmask = (1u << b) - 1;
+  for (const uint32_t S : C.out_masks) {
+    const uint32_t SL = S & lowmask, SH = S >> b;
+    const int sL = popc(SL), sH = popc(SH);
+    const int at = ybase(l, sL) + sH * (sH + 1) / 2 * nrp(sL) + rank_colex(SL);
+    F->hword.push_back((uint32_t)at | (uint32_t)nrp(sL) << 16);
+    F->hhigh.push_back(SH);
   }
   return "";
 }

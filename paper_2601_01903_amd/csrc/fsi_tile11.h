@@ -1,6 +1,6 @@
 // Compile-time layout of the 2^11-value register-phase tile (fused algorithm,
-// l <= 4), shared by the kernel (fsi_tile11.hip) and the host tables
-// (fsi_tables.cpp). Everything here depends only on l: the tile splits its
+// l <= 6), shared by the kernels (fsi_tile11.hip: l <= 4, fsi_tile_high.hip:
+// l = 5, 6) and the host tables (fsi_tables.cpp). Everything here depends only on l: the tile splits its
 // 11 low bits into phase A (bits 0-3), phase B (bits 4-7), phase C (bits 8-10).
 //
 // Counter states are stored by their counter RELATIVE to the popcount of
@@ -102,28 +102,29 @@ constexpr int unit_index(int L, int sa, int sb) {
   return cpop(sa) + cpop(sb) > L ? -1 : ubase(L, sb) + rankA(sa);
 }
 // element (i, unit, c) at ((2 i + c / 4) * s2u + unit) * 4 + c % 4, with the
-// unit count padded to s2u, a multiple of 8: the counter rows of one
+// unit count padded (by at least one) to s2u, a multiple of 8: the counter rows of one
 // (unit, c) lie a multiple of 64 elements apart, so their stores pair up
 // (two per instruction), and the two c-halves of a phase-B wave fall on
 // disjoint LDS banks
-constexpr int s2u(int L) { return (n3(L) + 7) & ~7; }
+constexpr int s2u(int L) { return (n3(L) + 8) & ~7; }
 // phase B writes the leaves of prefixes past the order to a padding unit
 // (n3 .. s2u - 1), which phase C never reads
-static_assert(s2u(1) > n3(1) && s2u(2) > n3(2) && s2u(3) > n3(3) && s2u(4) > n3(4),
-              "S2 needs a padding unit");
 constexpr int s2_elems(int L) { return (KAB + 1) * s2u(L) * NC; }
 
 // Phase-C thread map. Units in order of |sigma_AB| (stable). The heavy units
 // (|sigma_AB| <= L - 2: most output prefixes over the C bits) are split at the
 // first C output site: wave kCWaveH0 walks their sigma = 0 subtree, wave
 // kCWaveH1 (same lane) their sigma = 1 subtree. The other units fill waves
-// kCWaveR0 and kCWaveR1 whole. Thread t takes unit v[t] (-1: idle); every
+// kCWaveR0 and kCWaveR1 whole. Past order 4 (kFastMaxOrder) the heavy units outnumber a
+// wave and the units nearly fill the workgroup: every wave walks whole trees,
+// 64 units each in order. Thread t takes unit v[t] (-1: idle); every
 // unit of wave w has kmin[w] <= |sigma_AB| <= kmax[w] (kmin = L + 1 for a
 // wave without units) and wave w walks part[w] of the C-site tree (0: sigma
 // = 0 subtree, 1: sigma = 1 subtree, 2: all). The roles are placed so that
 // each SIMD's share of the per-tile work (one wave of each workgroup per
 // SIMD) comes out about even over the phases.
 constexpr int kCWaveH0 = 1, kCWaveH1 = 3, kCWaveR0 = 0, kCWaveR1 = 2;
+constexpr int kFastMaxOrder = 4;
 struct UnitOrder {
   int v[NT];
   int kmin[NT / 64], kmax[NT / 64], part[NT / 64];
@@ -133,19 +134,30 @@ constexpr UnitOrder mk_unit_order(int L) {
   UnitOrder o{};
   int units[NT] = {}, pop[NT] = {};
   int n = 0;
+  int base[NB] = {};
+  for (int sb = 0; sb < NB; ++sb) base[sb] = ubase(L, sb);
   for (int k = 0; k <= L; ++k)
     for (int sb = 0; sb < NB; ++sb)
       for (int r = 0; r < NA; ++r) {
-        const int sa = orderA(r);
+        const int sa = (int)((kOrderANibbles >> (4 * r)) & 15u);
         if (cpop(sa) + cpop(sb) == k) {
-          units[n] = ubase(L, sb) + r;
+          units[n] = base[sb] + r;
           pop[n] = k;
           ++n;
         }
       }
+  for (int t = 0; t < NT; ++t) o.v[t] = -1;
+  if (L > kFastMaxOrder) {
+    for (int i = 0; i < n; ++i) o.v[i] = units[i];
+    for (int w = 0; w < NT / 64; ++w) {
+      o.part[w] = 2;
+      o.kmin[w] = 64 * w < n ? pop[64 * w] : L + 1;
+      o.kmax[w] = 64 * w < n ? pop[imin(n, 64 * w + 64) - 1] : L + 1;
+    }
+    return o;
+  }
   int nh = 0;
   while (nh < n && pop[nh] <= L - 2) ++nh;
-  for (int t = 0; t < NT; ++t) o.v[t] = -1;
   for (int i = 0; i < nh; ++i) o.v[64 * kCWaveH0 + i] = o.v[64 * kCWaveH1 + i] = units[i];
   for (int i = nh; i < n; ++i)
     o.v[64 * (i - nh < 64 ? kCWaveR0 : kCWaveR1) + (i - nh) % 64] = units[i];
