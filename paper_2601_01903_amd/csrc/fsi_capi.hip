@@ -404,9 +404,15 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   // decreasing cost as they finish (the kernel's work queue); the reduction
   // reads every item's partial sums. Small items balance the end of the
   // launch, large ones write fewer partial sums.
-  int slots = n_cu;
-  for (size_t f = 0; f < P->fclasses.size(); ++f)
-    slots = std::max(slots, n_cu * fast_wgs_per_cu(prec, P->fclasses[f].l));
+  int fast_np[kFastMaxL + 1] = {0}, fast_orders = 0;
+  for (const FastClassHost& F : P->fclasses)
+    fast_np[F.l] = std::max(fast_np[F.l], (F.nkk + 1) / 2);
+  int fast_l = 0;   // the plan's only order, 0 if it has several
+  for (int l = 1; l <= kFastMaxL; ++l)
+    if (fast_np[l] > 0) { ++fast_orders; fast_l = l; }
+  if (fast_orders > 1) fast_l = 0;
+  const int fast_wgs = fast_orders > 0 ? fast_wgs_per_cu(prec, fast_l, fast_np[fast_l]) : 1;
+  const int slots = n_cu * fast_wgs;
   // tiles of one item of instance i at a nominal size c: any size inside a
   // one-block instance (its last item takes the rest), a power of two
   // dividing the block for an instance of several blocks
@@ -420,9 +426,13 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   };
   int64_t chunk = 1;
   {
-    static const double kTileUs[kFastMaxL + 1] = {0.0, 2.47, 3.03, 3.65, 3.79};
-    const double tile_scale = prec == PREC_F64 ? 2.3 : 1.0;
-    const double item_us = 6.0, red_base_us = 4.0, red_bytes_per_us = 3.0e6;
+    // us per tile of a workgroup at l = 1 .. 4, by the workgroups that share
+    // its CU (256 and 128 x d = 20, whole launches): the rows are the sweep in
+    // FP32 and FP64, the columns of a row 1, 2 and 3 workgroups
+    static const double kTileUs[2][3][kFastMaxL + 1] = {
+        {{0, 2.1, 2.5, 3.0, 3.2}, {0, 2.5, 3.0, 3.65, 3.9}, {0, 3.3, 4.2, 5.2, 5.2}},
+        {{0, 2.8, 3.3, 4.1, 4.4}, {0, 3.4, 4.5, 5.7, 6.5}, {0, 3.4, 4.5, 5.7, 6.5}}};
+    const double red_base_us = 4.0, red_bytes_per_us = 3.0e6;
     int64_t max_tiles = 1;
     for (int i = 0; i < n; ++i)
       if (P->fast_of[P->cls_of[i]] >= 0)
@@ -444,6 +454,9 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
           items += (ntile + item_tiles(i, c) - 1) / item_tiles(i, c);
         }
       if (items > 64 * (int64_t)slots && c != cand.back()) continue;
+      const int share = items <= n_cu ? 1 : std::min(fast_wgs, 3);
+      const double* tile_us = kTileUs[prec == PREC_F64][share - 1];
+      const double item_us = share == 3 ? 8.0 : share == 2 && prec == PREC_F64 ? 9.0 : 6.0;
       cost.clear();
       double part_bytes = 0.0;
       for (int i = 0; i < n; ++i) {
@@ -453,7 +466,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
         const int64_t ntile = (int64_t)1 << F.h, cs = item_tiles(i, c);
         for (int64_t tb = 0; tb < ntile; tb += cs) {
           const int64_t nt = std::min<int64_t>(cs, ntile - tb);
-          cost.push_back((double)nt * kTileUs[F.l] * tile_scale + item_us);
+          cost.push_back((double)nt * tile_us[F.l] + item_us);
           part_bytes += (double)F.nkk * kFastThreads * 8.0;
         }
       }
@@ -503,6 +516,12 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
       ptot += (int64_t)F.nkk * kFastThreads;
     }
   }
+  // a workgroup that has its CU to itself: the form without shared regions
+  // and held registers (a single d = 20, l = 3 instance in FP64: 19 us
+  // against 21)
+  if ((int64_t)fitems.size() <= n_cu)
+    for (int l = 1; l <= kFastMaxL; ++l)
+      if (fast_np[l] > 0) fast_np[l] = kFastRuns;
   // reduction of the register-phase partial sums of one-block instances, in
   // slot order (consecutive threads read consecutive slots of an item): one
   // slot per thread when no instance has more than two items, four item rows
@@ -735,23 +754,16 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     D.osh = reinterpret_cast<const uint32_t*>(A + co[c].osh);
   }
   std::memcpy(buf.data() + o_cls, cdev.data(), cdev.size() * sizeof(ClassDev));
-  size_t fast_lds[kFastMaxL + 1] = {0, 0, 0, 0, 0};
-  size_t fast_lds_max = 0;
   for (size_t f = 0; f < P->fclasses.size(); ++f) {
     const FastClassHost& F = P->fclasses[f];
     FastClassDev& D = fdev[f];
     D.d = F.d; D.l = F.l; D.h = F.h; D.M = F.M; D.nkk = F.nkk; D.mshift = F.mshift; D.kb = F.kb;
-    fast_lds[F.l] = fast_lds_bytes(prec, F.l);
-    fast_lds_max = std::max(fast_lds_max, fast_lds[F.l]);
     D.lam = reinterpret_cast<const double*>(A + fo[f].lam);
     D.meta = reinterpret_cast<const uint32_t*>(A + fo[f].meta);
     D.gs8 = reinterpret_cast<const uint32_t*>(A + fo[f].gs8);
     D.unit_mask = reinterpret_cast<const int32_t*>(A + fo[f].unit_mask);
     D.zrow = reinterpret_cast<const int32_t*>(A + fo[f].zrow);
     D.uperm = reinterpret_cast<const int32_t*>(A + fo[f].uperm);
-  }
-  if (fast_lds_max > 160 * 1024) {
-    return fail(FSI_ERR_INTERNAL, "register-phase kernel does not fit in LDS");
   }
   std::memcpy(buf.data() + o_fcls, fdev.data(), fdev.size() * sizeof(FastClassDev));
   for (int i = 0; i < n; ++i)
@@ -872,7 +884,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   a.fast = FastLaunch{};
   a.fast.n_items = (int)fitems.size();
   if (!fitems.empty()) {
-    e = configure_fast(prec, fast_lds);
+    e = configure_fast(prec, fast_np);
     if (e != hipSuccess) { return fail(FSI_ERR_HIP, std::string("configure_fast: ") + hipGetErrorString(e)); }
     a.fast.prec = prec;
     a.fast.classes = reinterpret_cast<const FastClassDev*>(A + o_fcls);
@@ -885,18 +897,12 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     a.fast.mobius_in = 0;
     for (const FastClassHost& F : P->fclasses)
       if (F.mobius_in) a.fast.mobius_in = 1;
-    int wgs = 1;
-    a.fast.lds_mixed = 0;
     for (int l = 0; l <= kFastMaxL; ++l) {
-      a.fast.lds[l] = fast_lds[l];
+      a.fast.np[l] = fast_np[l];
       const int nl = l >= 1 ? lbeg[l + 1] - lbeg[l] : 0;
-      a.fast.grid[l] = nl > 0 ? std::max(1, std::min(nl, n_cu * fast_wgs_per_cu(prec, l))) : 0;
-      if (nl > 0) {
-        wgs = std::max(wgs, fast_wgs_per_cu(prec, l));
-        a.fast.lds_mixed = std::max(a.fast.lds_mixed, fast_lds[l]);
-      }
+      a.fast.grid[l] = nl > 0 ? std::max(1, std::min(nl, n_cu * fast_wgs_per_cu(prec, l, fast_np[l]))) : 0;
     }
-    a.fast.grid_mixed = std::max(1, std::min((int)fitems.size(), n_cu * wgs));
+    a.fast.grid_mixed = std::max(1, std::min((int)fitems.size(), slots));
   }
   P->sched.autotuned = 0;
   P->sched.fast_instances = 0;

@@ -44,9 +44,8 @@ struct FastLaunch {
   int n_items;
   int lbeg[kFastMaxL + 2];
   int grid[kFastMaxL + 1];
-  size_t lds[kFastMaxL + 1];
+  int np[kFastMaxL + 1];          // most gather positions of the plan's classes of order l
   int grid_mixed;                 // grid of the one launch over every order's items
-  size_t lds_mixed;               // its dynamic LDS (the largest order's)
   int mobius_in;                  // 1: the input is already the Moebius transform
   const void* vals32;
   const void* vals64;
@@ -58,8 +57,8 @@ struct FastLaunch {
   uint32_t* queue;
 };
 
-// lds[l]: dynamic LDS of the order-l kernel, 0 = not used by the plan.
-hipError_t configure_fast(int prec, const size_t* lds);
+// np[l]: most gather positions of the plan's classes of order l, 0 = none.
+hipError_t configure_fast(int prec, const int* np);
 hipError_t launch_fast_group(const FastLaunch& f, int l, hipStream_t st);
 // One launch over the items of every order (plans with more than one order).
 hipError_t launch_fast_mixed(const FastLaunch& f, hipStream_t st);
@@ -69,9 +68,9 @@ int fast_launches(const FastLaunch& f);
 // Orders l with work items, ascending; returns their number.
 int fast_groups(const FastLaunch& f, int* ls);
 bool fast_supported(int prec);
-// Dynamic LDS of the register-phase kernel for items of order l.
-size_t fast_lds_bytes(int prec, int l);
-int fast_wgs_per_cu(int prec, int l);
+// Workgroups per CU of the register-phase kernel for classes of order l with
+// up to np gather positions (l = 0: the kernel over every order).
+int fast_wgs_per_cu(int prec, int l, int np);
 
 // Register-phase kernel of orders 5 and 6 (fsi_tile_high.hip): per-tile
 // results in memory, summed over the tiles by high_reduce_kernel. Items are

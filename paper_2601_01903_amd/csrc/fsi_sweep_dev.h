@@ -217,7 +217,8 @@ constexpr int kSAHiMax = cpop(orderA(15));  // |sigma_A| of rank 15
 template <int L, int SAMIN, int SAMAX, int HALF, typename SwT, bool BAR = false>
 __device__ __forceinline__ void phase_b(const SwT* S1, SwT* S2w, int sA, int p2r, int p2c) {
   if constexpr (SAMIN <= L) {
-    if (SAMAX > L && sA > L) return;
+    const bool off = SAMAX > L && sA > L;   // nothing to write
+    if (!BAR && off) return;
     using V = typename Vec4<SwT>::type;
     constexpr int VN = Vec4<SwT>::n;
     constexpr int H = NB / 2;
@@ -246,6 +247,7 @@ __device__ __forceinline__ void phase_b(const SwT* S1, SwT* S2w, int sA, int p2r
       }
     }
     if constexpr (BAR) __syncthreads();
+    if (BAR && off) return;
     if constexpr (HALF == 0) {
       SwT Y0[NRB + 1][H];
 #pragma unroll

@@ -56,36 +56,62 @@ namespace t11 {
 // --------------------------------------------------------------- LDS plan
 constexpr int align256(int x) { return (x + 255) & ~255; }
 constexpr int imax2(int a, int b) { return a > b ? a : b; }
-template <int L, typename SwT, typename MobT>
+// Gather positions a kernel of order L is compiled for: few of them (the
+// accumulators of the larger instances cost registers, and with them
+// workgroups per CU) or the most its outputs need.
+constexpr int np_few(int L) { return L == 3 ? 4 : L == 4 ? 7 : np_order(L); }
+constexpr int np_compiled(int L, int np) { return np <= np_few(L) ? np_few(L) : np_order(L); }
+
+// Workgroups per CU (4 waves each, one per SIMD) the registers are held to.
+// FP32 sweep: 3 at l <= 2 and, with few accumulators, at l = 3 (168 VGPRs),
+// else 2 (256); FP64: 2 at l <= 2 and l = 3 with few accumulators, else 1
+// (LDS at l = 4, registers at l = 3).
+template <typename SwT> constexpr int wgs_of(int L, int NP) {
+  const bool light = L <= 2 || (L == 3 && NP <= np_few(3));
+  return sizeof(SwT) == 4 ? (light ? 3 : 2) : (light ? 2 : 1);
+}
+// Whether the sweep's phases share one region (each phase's inputs in
+// registers, a barrier, then its stores over them): where the separate
+// regions do not leave room for wgs_of workgroups.
+template <typename SwT> constexpr bool shared_of(int L, int NP) {
+  return L == 3 && NP <= np_few(3);
+}
+
+template <int L, typename SwT, typename MobT, bool SHARED>
 struct Lds {
-  // region 1: the raw-tile transposes at 0 and the partial results Y after
-  // them (disjoint, so the next tile's loads and first transpose may start
-  // while slower waves still gather this tile's Y); phase B's states S2
-  // overlay both
-  static constexpr int yoff = align256((int)(r_elems * sizeof(MobT)));
-  static constexpr int reg1 = align256(imax2((int)(s2_elems(L) * sizeof(SwT)), yoff + ysize(L) * 8));
-  static constexpr int reg2 = align256(
-      imax2(rows1(L) * row1_stride<SwT>() * (int)sizeof(SwT),
-            (nzrows(L) + 1) * ZROW * (int)sizeof(SwT)));
+  static constexpr int rend = align256((int)(r_elems * sizeof(MobT)));
+  static constexpr int s1b = rows1(L) * row1_stride<SwT>() * (int)sizeof(SwT);
+  static constexpr int s2b = s2_elems(L) * (int)sizeof(SwT);
+  static constexpr int zb = align256((nzrows(L) + 1) * ZROW * (int)sizeof(SwT));
+  static constexpr int yb = ysize(L) * 8;
+  // separate: region 1 holds the raw-tile transposes at 0 and the partial
+  // results Y after them (disjoint, so the next tile's loads and first
+  // transpose may start while slower waves still gather this tile's Y), and
+  // phase B's states S2 over both; region 2 S1, then Z.
+  // shared: the transposes at 0, S1 after them, S2 over both, Z over S2, Y
+  // past Z and the transposes.
+  static constexpr int yoff = SHARED ? imax2(rend, zb) : rend;
+  static constexpr int reg1 = align256(SHARED ? imax2(rend + s1b, imax2(s2b, yoff + yb))
+                                              : imax2(s2b, yoff + yb));
+  static constexpr int s1off = SHARED ? rend : reg1;
+  static constexpr int zoff = SHARED ? 0 : reg1;
+  static constexpr int reg2 = SHARED ? 0 : align256(imax2(s1b, zb));
   static constexpr int reg3 = align256(lamblock(L) * 8);   // weights of the current |U_H|
-  // zeros, read in place of the counter rows past a prefix's range by the
-  // waves that run the general sweep code (their row loads then need no
-  // branch and issue back to back)
-  static constexpr int zeros = 128;
-  static constexpr int bytes = reg1 + reg2 + reg3 + zeros;
+  static constexpr int lamoff_ = reg1 + reg2;
+  static constexpr int end = reg1 + reg2 + reg3;
 };
-// The zero row sits at one offset past the regions of every order, so one
-// kernel can run items of different orders (each item uses its order's
-// regions below that offset) and the row is written once per workgroup.
+// Past the regions: zeros, read in place of the counter rows past a prefix's
+// range by the waves that run the general sweep code (their row loads then
+// need no branch and issue back to back), and the words that lanes past a
+// weight task's rows write.
+constexpr int kLdsZeros = 128, kLdsTail = kLdsZeros + 128;
+// A kernel of one order places them at that order's end; the kernel that runs
+// items of every order at one offset past the regions of all of them.
 template <typename SwT, typename MobT>
 struct LdsAll {
-  static constexpr int zoff =
-      imax2(imax2(Lds<1, SwT, MobT>::reg1 + Lds<1, SwT, MobT>::reg2 + Lds<1, SwT, MobT>::reg3,
-                  Lds<2, SwT, MobT>::reg1 + Lds<2, SwT, MobT>::reg2 + Lds<2, SwT, MobT>::reg3),
-            imax2(Lds<3, SwT, MobT>::reg1 + Lds<3, SwT, MobT>::reg2 + Lds<3, SwT, MobT>::reg3,
-                  Lds<4, SwT, MobT>::reg1 + Lds<4, SwT, MobT>::reg2 + Lds<4, SwT, MobT>::reg3));
-  static constexpr int zeros = 128;
-  static constexpr int bytes = zoff + zeros;
+  static constexpr int end =
+      imax2(imax2(Lds<1, SwT, MobT, false>::end, Lds<2, SwT, MobT, false>::end),
+            imax2(Lds<3, SwT, MobT, false>::end, Lds<4, SwT, MobT, false>::end));
 };
 
 // ------------------------------------------------------------ weight core
@@ -271,7 +297,8 @@ constexpr int prio_c(int w) {
 constexpr int kPrioTwoWave = 1;
 
 // ------------------------------------------------------------------ item
-template <int L, typename SwT, typename MobT, bool IN64, bool MOBIN>
+// TAIL: LDS offset of the zeros. NPC: gather positions.
+template <int L, typename SwT, typename MobT, bool IN64, bool MOBIN, int NPC, bool SHARED, int TAIL>
 __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, const InstDev& I,
                                          const FastItem& W, const float* __restrict__ vals32,
                                          const double* __restrict__ vals64,
@@ -279,17 +306,17 @@ __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, con
                                          double* __restrict__ partial,
                                          void* __restrict__ out, unsigned char* smem) {
   static_assert(kFastRuns == kRuns, "gather positions");
-  constexpr int NP = np_order(L);     // gather positions of this order
+  constexpr int NP = NPC;             // gather positions
   constexpr int KMAX = 2 * NP;        // output slots
   constexpr int LB = K<L>::LB;
-  using LD = Lds<L, SwT, MobT>;
+  using LD = Lds<L, SwT, MobT, SHARED>;
   MobT* R = reinterpret_cast<MobT*>(smem);
   SwT* S2 = reinterpret_cast<SwT*>(smem);
   double* Y = reinterpret_cast<double*>(smem + LD::yoff);
-  SwT* S1 = reinterpret_cast<SwT*>(smem + LD::reg1);
-  SwT* Z = reinterpret_cast<SwT*>(smem + LD::reg1);
-  double* lamL = reinterpret_cast<double*>(smem + LD::reg1 + LD::reg2);
-  const SwT* zrow = reinterpret_cast<const SwT*>(smem + LdsAll<SwT, MobT>::zoff);
+  SwT* S1 = reinterpret_cast<SwT*>(smem + LD::s1off);
+  SwT* Z = reinterpret_cast<SwT*>(smem + LD::zoff);
+  double* lamL = reinterpret_cast<double*>(smem + LD::lamoff_);
+  const SwT* zrow = reinterpret_cast<const SwT*>(smem + TAIL);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -305,10 +332,15 @@ __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, con
   const int u3r = C->uperm[tid];
   const bool c_on = u3r >= 0;   // this thread has a phase-C unit
   const int u3 = c_on ? u3r : 0;
-  const int sAB = __popc(C->unit_mask[u3]);
+  int sAB = __popc(C->unit_mask[u3]);
   int zr[NC];
 #pragma unroll
   for (int sc = 0; sc < NC; ++sc) zr[sc] = C->zrow[u3 * NC + sc];
+  if (SHARED && !c_on) {   // runs unit 0 into the dump row
+    sAB = KAB;
+#pragma unroll
+    for (int sc = 0; sc < NC; ++sc) zr[sc] = nzrows(L);
+  }
   // cross-tile sum (the output metadata is re-read per tile from L1/L2 so it
   // holds no registers during the sweep phases)
   double acc[KMAX];
@@ -435,19 +467,19 @@ __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, con
     switch (wave) {
       case 0:
         wave_prio<kPrioB[0]>();
-        phase_b<L, 0, kSALoMax, 0, SwT>(S1, S2 + wb, sA, p2r, p2c);
+        phase_b<L, 0, kSALoMax, 0, SwT, SHARED>(S1, S2 + wb, sA, p2r, p2c);
         break;
       case 1:
         wave_prio<kPrioB[1]>();
-        phase_b<L, kSAHi, kSAHiMax, 0, SwT>(S1, S2 + wb, sA, p2r, p2c);
+        phase_b<L, kSAHi, kSAHiMax, 0, SwT, SHARED>(S1, S2 + wb, sA, p2r, p2c);
         break;
       case 2:
         wave_prio<kPrioB[2]>();
-        phase_b<L, 0, kSALoMax, 1, SwT>(S1, S2 + wb, sA, p2r, p2c);
+        phase_b<L, 0, kSALoMax, 1, SwT, SHARED>(S1, S2 + wb, sA, p2r, p2c);
         break;
       default:
         wave_prio<kPrioB[3]>();
-        phase_b<L, kSAHi, kSAHiMax, 1, SwT>(S1, S2 + wb, sA, p2r, p2c);
+        phase_b<L, kSAHi, kSAHiMax, 1, SwT, SHARED>(S1, S2 + wb, sA, p2r, p2c);
         break;
     }
     wave_prio<0>();
@@ -455,24 +487,25 @@ __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, con
     // ---- phase C: thread per unit sigma_AB (units in order of |sigma_AB|,
     // the heavy ones split between two waves), counters relative to
     // |sigma_AB| ----
-    if (c_on) {
+    // (shared region: every thread runs it, for its barrier)
+    if (c_on || SHARED) {
       using O = UO<L>;
       switch (wave) {
         case 0:
           wave_prio<prio_c(0)>();
-          phase_c<L, O::o.kmin[0], O::o.kmax[0], O::o.part[0], SwT>(S2, Z, zr, sAB, u3, zrow);
+          phase_c<L, O::o.kmin[0], O::o.kmax[0], O::o.part[0], SwT, SHARED>(S2, Z, zr, sAB, u3, zrow);
           break;
         case 1:
           wave_prio<prio_c(1)>();
-          phase_c<L, O::o.kmin[1], O::o.kmax[1], O::o.part[1], SwT>(S2, Z, zr, sAB, u3, zrow);
+          phase_c<L, O::o.kmin[1], O::o.kmax[1], O::o.part[1], SwT, SHARED>(S2, Z, zr, sAB, u3, zrow);
           break;
         case 2:
           wave_prio<prio_c(2)>();
-          phase_c<L, O::o.kmin[2], O::o.kmax[2], O::o.part[2], SwT>(S2, Z, zr, sAB, u3, zrow);
+          phase_c<L, O::o.kmin[2], O::o.kmax[2], O::o.part[2], SwT, SHARED>(S2, Z, zr, sAB, u3, zrow);
           break;
         default:
           wave_prio<prio_c(3)>();
-          phase_c<L, O::o.kmin[3], O::o.kmax[3], O::o.part[3], SwT>(S2, Z, zr, sAB, u3, zrow);
+          phase_c<L, O::o.kmin[3], O::o.kmax[3], O::o.part[3], SwT, SHARED>(S2, Z, zr, sAB, u3, zrow);
           break;
       }
       wave_prio<0>();
@@ -490,9 +523,7 @@ __device__ __forceinline__ void run_item(const FastClassDev* __restrict__ C, con
     // ---- final weight core -> Y ----
     {
       const cdptr lamg = (cdptr)(C->lam + (int64_t)u_prev * LB);
-      // lanes past a task's rows write here: the transpose region, dead
-      // between phase C and the next tile
-      double* dump = reinterpret_cast<double*>(smem);
+      double* dump = reinterpret_cast<double*>(smem + TAIL + kLdsZeros);
       switch (wave) {
         case 0: lam_wave<L, 0, SwT>(lane, Z, Y, lamL, lamg, dump); break;
         case 1: lam_wave<L, 1, SwT>(lane, Z, Y, lamL, lamg, dump); break;
@@ -583,27 +614,23 @@ __device__ __forceinline__ void queue_done(uint32_t* queue, int n_items) {
 }
 
 // One kernel per order l (the items of a launch all have that order).
-// FP32 sweep: two workgroups per CU (2 waves per SIMD), so at most 256 VGPRs
-// per thread; the FP64 sweep's LDS allows one workgroup per CU.
-template <int L, typename SwT, typename MobT, bool IN64, int WPE, bool MOBIN>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE)))
+template <int L, typename SwT, typename MobT, bool IN64, bool MOBIN, int NP>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(wgs_of<SwT>(L, NP))))
 tile11_kernel(const FastClassDev* __restrict__ classes, const InstDev* __restrict__ insts,
               const FastItem* __restrict__ items, int n_items,
               const float* __restrict__ vals32, const double* __restrict__ vals64,
               const int32_t* __restrict__ torder, double* __restrict__ partial,
               void* __restrict__ out, uint32_t* __restrict__ queue) {
   extern __shared__ __align__(16) unsigned char smem[];
-  {
-    using LA = LdsAll<SwT, MobT>;
-    uint32_t* z = reinterpret_cast<uint32_t*>(smem + LA::zoff);
-    if (threadIdx.x < LA::zeros / 4) z[threadIdx.x] = 0u;
-    __syncthreads();
-  }
+  constexpr bool SHARED = shared_of<SwT>(L, NP);
+  constexpr int TAIL = Lds<L, SwT, MobT, SHARED>::end;
+  if (threadIdx.x < kLdsZeros / 4) reinterpret_cast<uint32_t*>(smem + TAIL)[threadIdx.x] = 0u;
+  __syncthreads();
   for (int item = blockIdx.x; item < n_items; item = next_item(queue, n_items)) {
     const FastItem W = items[item];
     const InstDev I = insts[W.inst];
-    run_item<L, SwT, MobT, IN64, MOBIN>(classes + I.fcls, I, W, vals32, vals64, torder, partial,
-                                        out, smem);
+    run_item<L, SwT, MobT, IN64, MOBIN, NP, SHARED, TAIL>(classes + I.fcls, I, W, vals32, vals64,
+                                                          torder, partial, out, smem);
     __syncthreads();
   }
   queue_done(queue, n_items);
@@ -612,165 +639,120 @@ tile11_kernel(const FastClassDev* __restrict__ classes, const InstDev* __restric
 // Items of every order in one launch (a batch of instances with different
 // l): each item runs the code compiled for its instance's order; the
 // regions of all orders share one allocation (LdsAll).
-template <typename SwT, typename MobT, bool IN64, int WPE, bool MOBIN>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE)))
+template <typename SwT, typename MobT, bool IN64, bool MOBIN>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(SwT) == 4 ? 2 : 1)))
 tile11_mixed_kernel(const FastClassDev* __restrict__ classes, const InstDev* __restrict__ insts,
                     const FastItem* __restrict__ items, int n_items,
                     const float* __restrict__ vals32, const double* __restrict__ vals64,
                     const int32_t* __restrict__ torder, double* __restrict__ partial,
                     void* __restrict__ out, uint32_t* __restrict__ queue) {
   extern __shared__ __align__(16) unsigned char smem[];
-  {
-    using LA = LdsAll<SwT, MobT>;
-    uint32_t* z = reinterpret_cast<uint32_t*>(smem + LA::zoff);
-    if (threadIdx.x < LA::zeros / 4) z[threadIdx.x] = 0u;
-    __syncthreads();
-  }
+  constexpr int TAIL = LdsAll<SwT, MobT>::end;
+  if (threadIdx.x < kLdsZeros / 4) reinterpret_cast<uint32_t*>(smem + TAIL)[threadIdx.x] = 0u;
+  __syncthreads();
   for (int item = blockIdx.x; item < n_items; item = next_item(queue, n_items)) {
     const FastItem W = items[item];
     const InstDev I = insts[W.inst];
     const FastClassDev* C = classes + I.fcls;
     const int l = __builtin_amdgcn_readfirstlane(C->l);
     switch (l) {
-      case 1: run_item<1, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
-      case 2: run_item<2, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
-      case 3: run_item<3, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
-      default: run_item<4, SwT, MobT, IN64, MOBIN>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
+      case 1: run_item<1, SwT, MobT, IN64, MOBIN, np_order(1), false, TAIL>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
+      case 2: run_item<2, SwT, MobT, IN64, MOBIN, np_order(2), false, TAIL>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
+      case 3: run_item<3, SwT, MobT, IN64, MOBIN, np_order(3), false, TAIL>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
+      default: run_item<4, SwT, MobT, IN64, MOBIN, np_order(4), false, TAIL>(C, I, W, vals32, vals64, torder, partial, out, smem); break;
     }
     __syncthreads();
   }
   queue_done(queue, n_items);
 }
 
-// Every order's kernel places the zero row past the regions of all orders
-// (LdsAll), so each allocates the same size.
-template <typename SwT, typename MobT>
-constexpr int lds_bytes_for(int) {
-  return LdsAll<SwT, MobT>::bytes;
-}
-
 }  // namespace t11
 
+using namespace t11;
+
 // ------------------------------------------------------------------ launcher
-template <typename SwT> constexpr int wpe_for() { return sizeof(SwT) == 4 ? 2 : 1; }
-
-// Plans whose input is already the Moebius transform run their own
-// instantiations.
+// Kernel, LDS bytes and workgroups per CU of one form.
+struct FastForm {
+  const void* fn;
+  int lds, wgs;
+};
+constexpr int lds_wgs(int lds, int wgs) {
+  const int by_lds = 160 * 1024 / lds;
+  return by_lds < 1 ? 1 : by_lds < wgs ? by_lds : wgs;
+}
+template <int L, typename SwT, typename MobT, bool IN64, bool MOBIN, int NP>
+static FastForm form_np() {
+  constexpr int lds = Lds<L, SwT, MobT, shared_of<SwT>(L, NP)>::end + kLdsTail;
+  static_assert(lds <= 160 * 1024, "register-phase kernel does not fit in LDS");
+  return FastForm{reinterpret_cast<const void*>(tile11_kernel<L, SwT, MobT, IN64, MOBIN, NP>), lds,
+                  lds_wgs(lds, wgs_of<SwT>(L, NP))};
+}
 template <int L, typename SwT, typename MobT, bool IN64, bool MOBIN>
-static hipError_t launch_t11_m(const FastLaunch& f, hipStream_t st) {
-  const int ib = f.lbeg[L], n = f.lbeg[L + 1] - f.lbeg[L];
-  if (n <= 0) return hipSuccess;
-  auto k = t11::tile11_kernel<L, SwT, MobT, IN64, wpe_for<SwT>(), MOBIN>;
-  hipLaunchKernelGGL(k, dim3(f.grid[L]), dim3(t11::NT), f.lds[L], st, f.classes, f.insts,
-                     f.items + ib, n, static_cast<const float*>(f.vals32),
-                     static_cast<const double*>(f.vals64), f.torder, f.partial, f.out, f.queue);
-  return hipGetLastError();
+static FastForm form_l(int np) {
+  if constexpr (np_few(L) != np_order(L))
+    if (np <= np_few(L)) return form_np<L, SwT, MobT, IN64, MOBIN, np_few(L)>();
+  return form_np<L, SwT, MobT, IN64, MOBIN, np_order(L)>();
 }
-
-template <int L, typename SwT, typename MobT, bool IN64>
-static hipError_t launch_t11(const FastLaunch& f, hipStream_t st) {
-  return f.mobius_in ? launch_t11_m<L, SwT, MobT, IN64, true>(f, st)
-                     : launch_t11_m<L, SwT, MobT, IN64, false>(f, st);
-}
-
-template <int L, typename SwT, typename MobT, bool IN64, bool MOBIN>
-static hipError_t config_t11_m(size_t lds) {
-  auto k = t11::tile11_kernel<L, SwT, MobT, IN64, wpe_for<SwT>(), MOBIN>;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
-template <int L, typename SwT, typename MobT, bool IN64>
-static hipError_t config_t11(size_t lds) {
-  hipError_t e = config_t11_m<L, SwT, MobT, IN64, false>(lds);
-  if (e != hipSuccess) return e;
-  return config_t11_m<L, SwT, MobT, IN64, true>(lds);
-}
-
-// One launch over the items of every order (the plan has several orders).
 template <typename SwT, typename MobT, bool IN64, bool MOBIN>
-static hipError_t launch_mixed_m(const FastLaunch& f, hipStream_t st) {
-  auto k = t11::tile11_mixed_kernel<SwT, MobT, IN64, wpe_for<SwT>(), MOBIN>;
-  hipLaunchKernelGGL(k, dim3(f.grid_mixed), dim3(t11::NT), f.lds_mixed, st, f.classes, f.insts,
-                     f.items, f.n_items, static_cast<const float*>(f.vals32),
-                     static_cast<const double*>(f.vals64), f.torder, f.partial, f.out, f.queue);
-  return hipGetLastError();
-}
-
-template <typename SwT, typename MobT, bool IN64>
-static hipError_t launch_mixed_t(const FastLaunch& f, hipStream_t st) {
-  return f.mobius_in ? launch_mixed_m<SwT, MobT, IN64, true>(f, st)
-                     : launch_mixed_m<SwT, MobT, IN64, false>(f, st);
-}
-
-template <typename SwT, typename MobT, bool IN64, bool MOBIN>
-static hipError_t config_mixed_m(size_t lds) {
-  auto k = t11::tile11_mixed_kernel<SwT, MobT, IN64, wpe_for<SwT>(), MOBIN>;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
-template <typename SwT, typename MobT, bool IN64>
-static hipError_t config_mixed_t(size_t lds) {
-  hipError_t e = config_mixed_m<SwT, MobT, IN64, false>(lds);
-  if (e != hipSuccess) return e;
-  return config_mixed_m<SwT, MobT, IN64, true>(lds);
-}
-
-template <typename SwT, typename MobT, bool IN64>
-static hipError_t launch_group_t(const FastLaunch& f, int l, hipStream_t st) {
+static FastForm form_t(int l, int np) {
   switch (l) {
-    case 1: return launch_t11<1, SwT, MobT, IN64>(f, st);
-    case 2: return launch_t11<2, SwT, MobT, IN64>(f, st);
-    case 3: return launch_t11<3, SwT, MobT, IN64>(f, st);
-    case 4: return launch_t11<4, SwT, MobT, IN64>(f, st);
+    case 1: return form_l<1, SwT, MobT, IN64, MOBIN>(np);
+    case 2: return form_l<2, SwT, MobT, IN64, MOBIN>(np);
+    case 3: return form_l<3, SwT, MobT, IN64, MOBIN>(np);
+    case 4: return form_l<4, SwT, MobT, IN64, MOBIN>(np);
   }
-  return hipErrorInvalidValue;
+  constexpr int lds = LdsAll<SwT, MobT>::end + kLdsTail;   // l = 0: every order
+  return FastForm{reinterpret_cast<const void*>(tile11_mixed_kernel<SwT, MobT, IN64, MOBIN>), lds,
+                  lds_wgs(lds, sizeof(SwT) == 4 ? 2 : 1)};
 }
-
-template <typename SwT, typename MobT, bool IN64>
-static hipError_t config_all_t(const size_t* lds) {
-  hipError_t e = hipSuccess;
-  size_t mx = 0;
-  int orders = 0;
-  for (int l = 1; l <= kFastMaxL; ++l)
-    if (lds[l]) { mx = std::max(mx, lds[l]); ++orders; }
-  if (orders > 1 && (e = config_mixed_t<SwT, MobT, IN64>(mx)) != hipSuccess) return e;
-  if (lds[1] && (e = config_t11<1, SwT, MobT, IN64>(lds[1])) != hipSuccess) return e;
-  if (lds[2] && (e = config_t11<2, SwT, MobT, IN64>(lds[2])) != hipSuccess) return e;
-  if (lds[3] && (e = config_t11<3, SwT, MobT, IN64>(lds[3])) != hipSuccess) return e;
-  if (lds[4] && (e = config_t11<4, SwT, MobT, IN64>(lds[4])) != hipSuccess) return e;
-  return e;
-}
-
-hipError_t configure_fast(int prec, const size_t* lds) {
+template <bool MOBIN>
+static FastForm form_m(int prec, int l, int np) {
   switch (prec) {
-    case PREC_F32: return config_all_t<float, float, false>(lds);
-    case PREC_F32_COMP: return config_all_t<float, t11::TwoF, false>(lds);
-    case PREC_F32_FP64MOB: return config_all_t<float, double, false>(lds);
-    case PREC_F64: return config_all_t<double, double, true>(lds);
+    case PREC_F32: return form_t<float, float, false, MOBIN>(l, np);
+    case PREC_F32_COMP: return form_t<float, TwoF, false, MOBIN>(l, np);
+    case PREC_F64: return form_t<double, double, true, MOBIN>(l, np);
+    default: return form_t<float, double, false, MOBIN>(l, np);
   }
-  return hipErrorInvalidValue;
+}
+// l = 0: the kernel over every order. Plans whose input is already the Moebius
+// transform run their own instantiations.
+static FastForm fast_form(int prec, int l, int np, int mobius_in) {
+  return mobius_in ? form_m<true>(prec, l, np) : form_m<false>(prec, l, np);
+}
+
+static hipError_t launch_items(const FastLaunch& f, int l, int ib, int n, int grid, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const FastForm form = fast_form(f.prec, l, f.np[l], f.mobius_in);
+  const FastItem* items = f.items + ib;
+  const float* v32 = static_cast<const float*>(f.vals32);
+  const double* v64 = static_cast<const double*>(f.vals64);
+  void* out = f.out;
+  void* args[] = {(void*)&f.classes, (void*)&f.insts, (void*)&items, (void*)&n, (void*)&v32,
+                  (void*)&v64, (void*)&f.torder, (void*)&f.partial, (void*)&out, (void*)&f.queue};
+  return hipLaunchKernel(form.fn, dim3(grid), dim3(NT), args, form.lds, st);
 }
 
 hipError_t launch_fast_mixed(const FastLaunch& f, hipStream_t st) {
-  switch (f.prec) {
-    case PREC_F32: return launch_mixed_t<float, float, false>(f, st);
-    case PREC_F32_COMP: return launch_mixed_t<float, t11::TwoF, false>(f, st);
-    case PREC_F32_FP64MOB: return launch_mixed_t<float, double, false>(f, st);
-    case PREC_F64: return launch_mixed_t<double, double, true>(f, st);
-  }
-  return hipErrorInvalidValue;
+  return launch_items(f, 0, 0, f.n_items, f.grid_mixed, st);
 }
 
 hipError_t launch_fast_group(const FastLaunch& f, int l, hipStream_t st) {
-  switch (f.prec) {
-    case PREC_F32: return launch_group_t<float, float, false>(f, l, st);
-    case PREC_F32_COMP: return launch_group_t<float, t11::TwoF, false>(f, l, st);
-    case PREC_F32_FP64MOB: return launch_group_t<float, double, false>(f, l, st);
-    case PREC_F64: return launch_group_t<double, double, true>(f, l, st);
+  return launch_items(f, l, f.lbeg[l], f.lbeg[l + 1] - f.lbeg[l], f.grid[l], st);
+}
+
+hipError_t configure_fast(int prec, const int* np) {
+  int orders = 0;
+  for (int l = 1; l <= kFastMaxL; ++l) orders += np[l] > 0;
+  for (int l = orders > 1 ? 0 : 1; l <= kFastMaxL; ++l) {
+    if (l > 0 && np[l] == 0) continue;
+    for (int m = 0; m < 2; ++m) {
+      const FastForm form = fast_form(prec, l, np[l], m);
+      const hipError_t e =
+          hipFuncSetAttribute(form.fn, hipFuncAttributeMaxDynamicSharedMemorySize, form.lds);
+      if (e != hipSuccess) return e;
+    }
   }
-  return hipErrorInvalidValue;
+  return hipSuccess;
 }
 
 int fast_groups(const FastLaunch& f, int* ls) {
@@ -793,22 +775,7 @@ bool fast_supported(int prec) {
          prec == PREC_F64;
 }
 
-size_t fast_lds_bytes(int prec, int l) {
-  switch (prec) {
-    case PREC_F32: return t11::lds_bytes_for<float, float>(l);
-    case PREC_F32_COMP: return t11::lds_bytes_for<float, t11::TwoF>(l);
-    case PREC_F32_FP64MOB: return t11::lds_bytes_for<float, double>(l);
-    case PREC_F64: return t11::lds_bytes_for<double, double>(l);
-  }
-  return 0;
-}
-
-// Workgroups of the register-phase kernel that fit on one CU.
-int fast_wgs_per_cu(int prec, int l) {
-  const size_t lds = fast_lds_bytes(prec, l);
-  const int by_lds = lds ? (int)((160 * 1024) / lds) : 1;
-  const int by_regs = prec == PREC_F64 ? 1 : 2;
-  return std::max(1, std::min(by_lds, by_regs));
-}
+// Workgroups of the kernel of order l (0: of every order) that fit on one CU.
+int fast_wgs_per_cu(int prec, int l, int np) { return fast_form(prec, l, np, 0).wgs; }
 
 }  // namespace fsi
