@@ -224,8 +224,7 @@ fsi_status fsi_plan(int d, int l, fsi_plan_t* out);
 fsi_status fsi_plan_ex(int d, int l, const fsi_plan_opts* opts, fsi_plan_t* out);
 
 /* Frees the plan's host tables, device tables and workspace. NULL is a
- * no-op. Waits first for the plan's work issued by the apply calls (an
- * event recorded on the apply's stream after each call, outside stream
+ * no-op. Waits first for the stream of the plan's last apply (outside stream
  * capture), not for the whole device. */
 fsi_status fsi_plan_destroy(fsi_plan_t plan);
 
