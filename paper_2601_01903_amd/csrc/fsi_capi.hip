@@ -874,7 +874,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   a.grid_wide = std::max(1, std::min<int>((int)witems.size(), n_cu * 4));
   a.wide_groups = reinterpret_cast<const WideGroup*>(A + o_wgroups);
   a.n_wide_groups = (int)wgroups.size();
-  a.grid_wide_groups = std::max(1, std::min<int>((int)wgroups.size() * (kWideOuts / 256), n_cu * 4));
+  a.grid_wide_groups = std::max(1, std::min<int>((int)wgroups.size() * (kWideOuts / 16), n_cu * 8));
   a.wide_partial = P->wide_partial;
   a.red_chunks = reinterpret_cast<const int2*>(A + o_red);
   a.n_red_chunks = (int)red_chunks.size();

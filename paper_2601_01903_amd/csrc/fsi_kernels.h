@@ -93,8 +93,13 @@ hipError_t launch_high_reduce(const HighLaunch& f, const double* Y, void* out, h
 // Wide gather (generic fused instances with many tiles): a work item is a
 // range of tiles and a group of up to kWideOuts outputs; each thread keeps
 // kWideK output accumulators in registers across the range. The partial
-// sums of a group's ranges are then added in range order.
-constexpr int kWideK = 16;
+// sums of a group's ranges are then added in a fixed order. Four outputs a
+// thread: their places (six words each) are read once per item, so the fewer
+// outputs an item has, the longer its range for the same number of items
+// (d = 27, l = 4: gather 40 us with 16 outputs and ranges of 8 blocks, 34 us with
+// 4 and 32; final pass 33 us over 128 ranges one output a thread, 5 us with 16 rows
+// of threads over 32).
+constexpr int kWideK = 4;
 constexpr int kWideOuts = 256 * kWideK;
 constexpr int kWideMinH = 10;      // instances with at least 2^10 tiles
 

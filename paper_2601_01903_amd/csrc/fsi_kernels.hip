@@ -283,17 +283,25 @@ __device__ __forceinline__ void wide_gather_blocks(const InstDev& I, const WideI
     s2[q] = I.osh2[kk];
     acc[q] = 0.0;
   }
-  for (int blk = w.t0; blk < w.t1; ++blk) {
-    for (int r = 0; r < I.ipb; ++r) {
-      const double* __restrict__ Pb = fpart + I.pbase + ((int64_t)blk * I.ipb + r) * I.pstride;
+  const int ipb = I.ipb;
+  const double* __restrict__ Pb = fpart + I.pbase + (int64_t)w.t0 * ipb * I.pstride;
+  int32_t o[kWideK];
+  int r = ipb, blk = w.t0;   // item r of block blk comes next
+#pragma unroll 4
+  for (int j = 0, n = (w.t1 - w.t0) * ipb; j < n; ++j, Pb += I.pstride) {
+    if (r == ipb) {
+      r = 0;
 #pragma unroll
       for (int q = 0; q < kWideK; ++q) {
-        const int j = __popc(s2[q] & (uint32_t)blk);
-        const int32_t o = j == 0 ? pj[q][0] : j == 1 ? pj[q][1] : j == 2 ? pj[q][2]
-                        : j == 3 ? pj[q][3] : pj[q][4];
-        acc[q] += Pb[o];
+        const int jj = __popc(s2[q] & (uint32_t)blk);
+        o[q] = jj == 0 ? pj[q][0] : jj == 1 ? pj[q][1] : jj == 2 ? pj[q][2]
+             : jj == 3 ? pj[q][3] : pj[q][4];
       }
+      ++blk;
     }
+    ++r;
+#pragma unroll
+    for (int q = 0; q < kWideK; ++q) acc[q] += Pb[o[q]];
   }
   double* P = partial + w.pofs;
 #pragma unroll
@@ -327,6 +335,7 @@ wide_gather_kernel(const ClassDev* __restrict__ classes, const InstDev* __restri
       acc[q] = 0.0;
     }
     const double* __restrict__ Yb = Y + I.yoff;
+#pragma unroll 4
     for (int U = w.t0; U < w.t1; ++U) {
       const double* __restrict__ Yt = Yb + (int64_t)U * Ys;
 #pragma unroll
@@ -343,19 +352,30 @@ __global__ void __launch_bounds__(256)
 wide_final_kernel(const WideGroup* __restrict__ groups, int n_groups,
                   const InstDev* __restrict__ insts, const int64_t* __restrict__ out_offset,
                   const double* __restrict__ partial, OutT* __restrict__ out) {
-  // a workgroup takes 256 consecutive outputs of one group
-  constexpr int kChunks = kWideOuts / 256;
+  // a workgroup takes kCols consecutive outputs of one group; row r of its
+  // threads adds the ranges r mod kRows in order, then the rows are added
+  // in order
+  constexpr int kRows = 16, kCols = 256 / kRows, kChunks = kWideOuts / kCols;
+  __shared__ double part[kRows][kCols];
+  const int c = threadIdx.x % kCols, row = threadIdx.x / kCols;
   for (int ci = blockIdx.x; ci < n_groups * kChunks; ci += gridDim.x) {
     const WideGroup G = groups[ci / kChunks];
     const InstDev I = insts[G.inst];
     const int M = (int)(out_offset[G.inst + 1] - out_offset[G.inst]);
-    const int j = (ci % kChunks) * 256 + (int)threadIdx.x;
+    const int j = (ci % kChunks) * kCols + c;
     const int k = G.group * kWideOuts + j;
-    if (k < M) {
-      double acc = 0.0;
-      for (int r = 0; r < G.nr; ++r) acc += partial[G.pofs + (int64_t)r * kWideOuts + j];
+    double acc = 0.0;
+    if (k < M)
+#pragma unroll 4
+      for (int r = row; r < G.nr; r += kRows) acc += partial[G.pofs + (int64_t)r * kWideOuts + j];
+    part[row][c] = acc;
+    __syncthreads();
+    if (row == 0 && k < M) {
+#pragma unroll
+      for (int r = 1; r < kRows; ++r) acc += part[r][c];
       out[I.ooff + k] = (OutT)acc;
     }
+    __syncthreads();
   }
 }
 
