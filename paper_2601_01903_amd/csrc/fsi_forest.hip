@@ -26,6 +26,7 @@
 
 #include "../../include/fsi_forest.h"
 #include "fsi_abi.h"
+#include "fsi_butterfly_dev.h"
 #include "fsi_internal.h"
 
 namespace fsi {
@@ -385,11 +386,12 @@ void launch_walk(const Node* prep, const double* value, const int32_t* roots, in
 // (unreachable if some f in I has alpha_f = 0), Q any subset of
 // Fr = {f: beta_f = 1, alpha_f = 0}, with sign (-1)^|Q|; value / B * (-1)^|Q|
 // is added at every such R.
+// Zeroes 2^d entries, 16 bytes a store (d = 0 does not occur).
 __global__ void __launch_bounds__(kThreads)
-fill_kernel(double* __restrict__ a, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
+fill_kernel(double2* __restrict__ a, int64_t n2) {
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n2;
        i += (int64_t)gridDim.x * kThreads)
-    a[i] = 0.0;
+    a[i] = double2{0.0, 0.0};
 }
 
 // One thread per path and group of kScatterBg backgrounds: the path's nodes
@@ -398,10 +400,19 @@ fill_kernel(double* __restrict__ a, int64_t n) {
 // one at the empty set), and FP64 atomics on one address serialise in
 // memory: a workgroup collects the sets of at most two players in LDS (index
 // 0, then 1 + i, then 1 + d + C(j, 2) + i for i < j) and adds each to memory
-// once at the end.
+// once at the end. Few (path, background) pairs are reachable at all, and they
+// have 1 to 2^|Fr| terms: the workgroup lists the reachable ones in LDS and
+// then gives kTermLanes lanes to each (looped over by the thread that found
+// them, the terms took 35 of 60 us at 200 depth-6 trees, d = 20, 100
+// backgrounds; now the kernel takes 45, half of it the atomics).
 constexpr int kScatterBg = 8;
-constexpr int kScatterGrid = 512;   // workgroups that collect and flush
+constexpr int kScatterGrid = 256;   // workgroups that collect and flush
 constexpr int kSmallSets = 1 + kMaxD + kMaxD * (kMaxD - 1) / 2;
+constexpr int kTermLanes = 4;   // the subsets of two members, see the loop
+struct PathTerms {       // a reachable path of one background
+  uint32_t I, Fr;
+  double c;
+};
 
 __global__ void __launch_bounds__(kThreads)
 mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __restrict__ steps,
@@ -411,6 +422,9 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
                       const double* __restrict__ bg, int n_bg, double* __restrict__ a) {
   __shared__ double small[kSmallSets];
   __shared__ double xs[kMaxD], zs[kScatterBg][kMaxD];
+  __shared__ PathTerms list[kThreads * kScatterBg];
+  __shared__ int n_list;
+  const int lane = threadIdx.x & 63;
   const int n_small = 1 + d + d * (d - 1) / 2;
   for (int i = threadIdx.x; i < n_small; i += kThreads) small[i] = 0.0;
   if ((int)threadIdx.x < d) xs[threadIdx.x] = x[threadIdx.x];
@@ -423,20 +437,22 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
     const int p = (int)(it - (int64_t)g * chunks) * kThreads + (int)threadIdx.x;
     const int b0 = g * kScatterBg;
     const int nb = min(kScatterBg, n_bg - b0);
-    if (g != g_prev) {   // uniform in the workgroup
-      __syncthreads();
+    __syncthreads();             // the previous list is used up
+    if (threadIdx.x == 0) n_list = 0;
+    if (g != g_prev) {           // uniform in the workgroup
       for (int i = threadIdx.x; i < kScatterBg * d; i += kThreads) {
         const int b = i / d;
         zs[b][i - b * d] = bg[(int64_t)(b0 + min(b, nb - 1)) * d + (i - b * d)];
       }
-      __syncthreads();
       g_prev = g;
     }
-    if (p >= n_paths) continue;
+    __syncthreads();
     uint32_t seen = 0, aok = ~0u, bok[kScatterBg];
 #pragma unroll
     for (int b = 0; b < kScatterBg; ++b) bok[b] = ~0u;
-    for (int s = path_off[p]; s < path_off[p + 1]; ++s) {
+    const bool on = p < n_paths;
+    const int s0 = on ? path_off[p] : 0, s1 = on ? path_off[p + 1] : 0;
+    for (int s = s0; s < s1; ++s) {
       const int e = steps[s];
       const int node = e >> 1;
       const bool dir = e & 1;
@@ -449,28 +465,45 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
       for (int b = 0; b < kScatterBg; ++b)
         if ((zs[b][f] >= th) != dir) bok[b] &= ~bit;
     }
-    const double c = value[path_leaf[p]] / (double)n_bg;
+    const double c = on ? value[path_leaf[p]] / (double)n_bg : 0.0;
 #pragma unroll
     for (int b = 0; b < kScatterBg; ++b) {
       const uint32_t I = seen & ~bok[b];
-      if (b >= nb || (I & ~aok)) continue;           // never reached
-      const uint32_t Fr = seen & bok[b] & ~aok;
-      uint32_t Q = 0;
+      const bool ok = on && b < nb && !(I & ~aok);    // reachable
+      const uint64_t m = __ballot(ok);
+      int base = 0;
+      if (lane == 0 && m) base = atomicAdd(&n_list, __popcll(m));
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (ok)
+        list[base + __popcll(m & ((1ull << lane) - 1ull))] =
+            PathTerms{I, seen & bok[b] & ~aok, c};
+    }
+    __syncthreads();
+    const int n = n_list;
+    for (int i = threadIdx.x / kTermLanes; i < n; i += kThreads / kTermLanes) {
+      const PathTerms t = list[i];
+      // lane j takes the subsets with bits j of the two lowest members of Fr
+      const uint32_t f0 = t.Fr & (0u - t.Fr), f01 = t.Fr & (t.Fr - 1u), f1 = f01 & (0u - f01);
+      const uint32_t rest = f01 ^ f1;
+      const uint32_t j = threadIdx.x % kTermLanes;
+      const uint32_t Q0 = ((j & 1u) ? f0 : 0u) | ((j & 2u) ? f1 : 0u);
+      if (((j & 1u) && !f0) || ((j & 2u) && !f1)) continue;
+      uint32_t H = 0;
       do {
-        const uint32_t R = I | Q;
-        const double v = (__popc(Q) & 1) ? -c : c;
+        const uint32_t Q = Q0 | H, R = t.I | Q;
+        const double v = (__popc(Q) & 1) ? -t.c : t.c;
         if (__popc(R) <= 2) {
           int k = 0;
           if (R) {
-            const int j = 31 - __clz((int)R), i = __ffs((int)R) - 1;
-            k = i == j ? 1 + i : 1 + d + j * (j - 1) / 2 + i;
+            const int hi = 31 - __clz((int)R), lo = __ffs((int)R) - 1;
+            k = lo == hi ? 1 + lo : 1 + d + hi * (hi - 1) / 2 + lo;
           }
           atomicAdd(small + k, v);
         } else {
           atomicAdd(a + R, v);
         }
-        Q = (Q - Fr) & Fr;
-      } while (Q != 0);
+        H = (H - rest) & rest;
+      } while (H != 0);
     }
   }
   __syncthreads();
@@ -488,72 +521,81 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
   }
 }
 
-// Subset sums (zeta transform, the inverse of the Moebius butterfly) over
-// the NB bits [bit0, bit0 + NB) of the index: each thread owns the 2^NB
-// entries of one column in registers. The last pass may write the result in
-// the output dtype instead of in place.
-// Small workgroups: a pass has only 2^(d-5) columns (32768 at d = 20), which
-// must still spread over every CU.
-constexpr int kZetaThreads = 64;
-
-template <int NB, typename OutT>
-__global__ void __launch_bounds__(kZetaThreads)
-zeta_pass_kernel(double* a, int d, int bit0, OutT* out) {   // out may equal a
-  const int64_t cols = (int64_t)1 << (d - NB);
-  const int64_t low = ((int64_t)1 << bit0) - 1;
-  for (int64_t t = (int64_t)blockIdx.x * kZetaThreads + threadIdx.x; t < cols;
-       t += (int64_t)gridDim.x * kZetaThreads) {
-    const int64_t base = (t & low) | ((t >> bit0) << (bit0 + NB));
-    double v[1 << NB];
-#pragma unroll
-    for (int k = 0; k < (1 << NB); ++k) v[k] = a[base + ((int64_t)k << bit0)];
-#pragma unroll
-    for (int bit = 0; bit < NB; ++bit)
-#pragma unroll
-      for (int k = 0; k < (1 << NB); ++k)
-        if (k & (1 << bit)) v[k] += v[k ^ (1 << bit)];
-#pragma unroll
-    for (int k = 0; k < (1 << NB); ++k) out[base + ((int64_t)k << bit0)] = (OutT)v[k];
-  }
-}
-
-// The low kZetaLow bits (or all d if fewer) in one pass: a workgroup loads a
-// contiguous tile of 2^lb entries into LDS, runs the lb butterfly levels
-// there and writes the tile back (coalesced both ways).
-constexpr int kZetaLow = 10;
+// Subset sums (zeta transform, the inverse of the Moebius butterfly): a pass
+// over the low 12 bits, then one over at most 8 more bits each; the last pass
+// may write the result in the output dtype instead of in place.
+struct ZetaAdd {
+  __device__ static double op(double hi, double lo) { return hi + lo; }
+};
 
 template <typename OutT>
-__global__ void __launch_bounds__(kThreads)
-zeta_low_kernel(const double* a, int lb, OutT* out) {        // out may equal a
-  __shared__ double t[1 << kZetaLow];
-  const int n = 1 << lb;
-  const int64_t base = (int64_t)blockIdx.x << lb;
-  for (int i = threadIdx.x; i < n; i += kThreads) t[i] = a[base + i];
-  __syncthreads();
-  for (int bit = 0; bit < lb; ++bit) {
-    for (int k = threadIdx.x; k < n / 2; k += kThreads) {
-      const int i0 = ((k >> bit) << (bit + 1)) | (k & ((1 << bit) - 1));
-      t[i0 | (1 << bit)] += t[i0];
-    }
-    __syncthreads();
+__global__ void __launch_bounds__(kMobThreads)
+zeta_low_kernel(const double* a, int d, OutT* out) {          // out may equal a
+  __shared__ double m[kMobLds];
+  const int nv = 1 << min(d, kMobTileBits);                   // valid elements
+  const int64_t base = (int64_t)blockIdx.x << kMobTileBits;
+  const int t = mob_field(threadIdx.x, 8);
+  double x[kMobElems];
+#pragma unroll
+  for (int k = 0; k < kMobElems; ++k) {
+    const int e = t | (k << 8);
+    x[k] = e < nv ? a[base + e] : 0.0;
   }
-  for (int i = threadIdx.x; i < n; i += kThreads) out[base + i] = (OutT)t[i];
+  mob_exchange<double>(m, x, 8, 0);
+  mob_levels<ZetaAdd>(x, 0);
+  mob_exchange<double>(m, x, 0, 4);
+  mob_levels<ZetaAdd>(x, 0);
+  mob_exchange<double>(m, x, 4, 8);
+  mob_levels<ZetaAdd>(x, 0);
+#pragma unroll
+  for (int k = 0; k < kMobElems; ++k) {
+    const int e = t | (k << 8);
+    if (e < nv) out[base + e] = (OutT)x[k];
+  }
 }
 
 template <typename OutT>
-void launch_zeta(double* a, int d, int bit0, int nb, OutT* out, hipStream_t st) {
-  const int64_t cols = (int64_t)1 << (d - nb);
-  const int grid = (int)std::min<int64_t>((cols + kZetaThreads - 1) / kZetaThreads, 32768);
-  switch (nb) {
-    case 1: zeta_pass_kernel<1, OutT><<<grid, kZetaThreads, 0, st>>>(a, d, bit0, out); break;
-    case 2: zeta_pass_kernel<2, OutT><<<grid, kZetaThreads, 0, st>>>(a, d, bit0, out); break;
-    case 3: zeta_pass_kernel<3, OutT><<<grid, kZetaThreads, 0, st>>>(a, d, bit0, out); break;
-    case 4: zeta_pass_kernel<4, OutT><<<grid, kZetaThreads, 0, st>>>(a, d, bit0, out); break;
-    default: zeta_pass_kernel<5, OutT><<<grid, kZetaThreads, 0, st>>>(a, d, bit0, out); break;
+__global__ void __launch_bounds__(kMobThreads)
+zeta_high_kernel(const double* a, int lo, int G, OutT* out) {  // out may equal a
+  __shared__ double m[kMobLds];
+  const int cb = kMobTileBits - G;
+  const int64_t block = blockIdx.x;
+  const int64_t base = ((block >> (lo - cb)) << (lo + G)) +
+                       ((block & (((int64_t)1 << (lo - cb)) - 1)) << cb);
+  const int p0 = min(cb, 8);
+  const int t0 = mob_field(threadIdx.x, p0), t1 = mob_field(threadIdx.x, 8);
+  double x[kMobElems];
+#pragma unroll
+  for (int k = 0; k < kMobElems; ++k) x[k] = a[base + mob_high_at(t0 | (k << p0), cb, lo)];
+  mob_levels<ZetaAdd>(x, cb - p0);
+  if (G > 4) {
+    mob_exchange<double>(m, x, p0, 8);
+    mob_levels<ZetaAdd>(x, cb - 4);
+  }
+#pragma unroll
+  for (int k = 0; k < kMobElems; ++k)
+    out[base + mob_high_at(t1 | (k << 8), cb, lo)] = (OutT)x[k];
+}
+
+// The subset sums of a (2^d), the last pass into out.
+template <typename OutT>
+void launch_zeta(double* a, int d, OutT* out, hipStream_t st) {
+  const int high = std::max(0, d - kMobTileBits);
+  const int grid = 1 << high;
+  if (high == 0) {
+    zeta_low_kernel<OutT><<<grid, kMobThreads, 0, st>>>(a, d, out);
+    return;
+  }
+  zeta_low_kernel<double><<<grid, kMobThreads, 0, st>>>(a, d, a);
+  const int np = (high + kMobGroup - 1) / kMobGroup;
+  for (int p = 0, lo = kMobTileBits; p < np; ++p) {
+    const int G = (d - lo + np - p - 1) / (np - p);
+    if (p + 1 < np) zeta_high_kernel<double><<<grid, kMobThreads, 0, st>>>(a, lo, G, a);
+    else zeta_high_kernel<OutT><<<grid, kMobThreads, 0, st>>>(a, lo, G, out);
+    lo += G;
   }
 }
 
-constexpr int kZetaBits = 5;        // bits per zeta pass
 constexpr int kMaxFreeSplits = 24;  // longest path the Moebius route expands
 constexpr int64_t kMaxPathSteps = (int64_t)1 << 26;
 
@@ -807,9 +849,9 @@ fsi_status fsi_forest_mobius(fsi_forest_t F, const double* x_dev, int n_bg, cons
   if (F->n_paths < 0)
     return ffail(FSI_ERR_UNSUPPORTED, "the Moebius route needs at most 2^26 root-to-leaf paths "
                                       "of at most 24 splits (or d <= 24)");
-  const int64_t n_coal = (int64_t)1 << F->d;
-  fill_kernel<<<(int)std::min<int64_t>((n_coal + kThreads - 1) / kThreads, 8192), kThreads, 0,
-                stream>>>(a_dev, n_coal);
+  const int64_t n2 = (int64_t)1 << (F->d - 1);
+  fill_kernel<<<(int)std::min<int64_t>((n2 + 4 * kThreads - 1) / (4 * kThreads), 2048), kThreads, 0,
+                stream>>>(reinterpret_cast<double2*>(a_dev), n2);
   const int64_t work = (int64_t)((n_bg + kScatterBg - 1) / kScatterBg) *
                        ((F->n_paths + kThreads - 1) / kThreads);
   mobius_scatter_kernel<<<(int)std::min<int64_t>(work, kScatterGrid), kThreads, 0, stream>>>(
@@ -834,26 +876,10 @@ fsi_status fsi_forest_values_mobius(fsi_forest_t F, const double* x_dev, int n_b
     return ffail(FSI_ERR_INVALID_ARG, "an FP32 output needs its own FP64 workspace");
   fsi_status st = fsi_forest_mobius(F, x_dev, n_bg, bg_dev, work_dev, stream);
   if (st != FSI_OK) return st;
-  const int d = F->d;
-  const int lb = std::min(d, kZetaLow);
-  if (lb == d) {
-    if (dtype == FSI_DTYPE_F32)
-      zeta_low_kernel<float><<<1, kThreads, 0, stream>>>(work_dev, lb, (float*)v_dev);
-    else
-      zeta_low_kernel<double><<<1, kThreads, 0, stream>>>(work_dev, lb, (double*)v_dev);
-  } else {
-    zeta_low_kernel<double><<<1 << (d - lb), kThreads, 0, stream>>>(work_dev, lb, work_dev);
-  }
-  for (int bit0 = lb; bit0 < d; bit0 += kZetaBits) {
-    const int nb = std::min(kZetaBits, d - bit0);
-    const bool last = bit0 + nb >= d;
-    if (last && dtype == FSI_DTYPE_F32)
-      launch_zeta<float>(work_dev, d, bit0, nb, (float*)v_dev, stream);
-    else if (last)
-      launch_zeta<double>(work_dev, d, bit0, nb, (double*)v_dev, stream);
-    else
-      launch_zeta<double>(work_dev, d, bit0, nb, work_dev, stream);
-  }
+  if (dtype == FSI_DTYPE_F32)
+    launch_zeta<float>(work_dev, F->d, (float*)v_dev, stream);
+  else
+    launch_zeta<double>(work_dev, F->d, (double*)v_dev, stream);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ffail(FSI_ERR_HIP, std::string("forest launch: ") + hipGetErrorString(e));
   return FSI_OK;

@@ -17,6 +17,7 @@
 #include <cstdint>
 
 #include "fsi_kernels.h"
+#include "fsi_butterfly_dev.h"
 
 namespace fsi {
 
@@ -423,52 +424,9 @@ fast_reduce_kernel(const InstDev* __restrict__ insts, const int2* __restrict__ c
 }
 
 // ---------------------------------------------------------------- Moebius (two-pass)
-// One pass of the butterfly over the G bits [lo, lo + G) of one instance. A
-// work item is a tile of 2^kMobTileBits elements: 2^cb consecutive low
-// indices (cb = kMobTileBits - G; 0 for the low pass, lo = 0) for each
-// setting of the G bits, at one setting of the other bits. A thread holds 16
-// elements of the tile, i.e. four of its bits, in registers, runs those
-// levels there and hands the tile to the next four through LDS, so a pass
-// reads and writes each value once with one exchange for G <= 8 and three for
-// the low pass. (One level per LDS round trip and barrier, as before, held a
-// pass over 2^24 FP64 values at 64 us where memory allows 40.)
-//
-// Every layout is an affine map of the thread: mob_field(t, P) | k << P puts
-// the four register bits k at tile bits P .. P + 3. Global accesses use
-// P >= 4, whose waves touch runs of at least 16 consecutive elements. The
-// levels run in ascending order of their bits.
-constexpr int kMobElems = 16;                       // per thread
-constexpr int kMobThreads = (1 << kMobTileBits) / kMobElems;
-
-// LDS place of tile element e: one element of padding per 16, so that lanes
-// 16 and 256 elements apart meet different banks.
-__device__ __forceinline__ int mob_pad(int e) { return e + (e >> 4); }
-constexpr int kMobLds = (1 << kMobTileBits) + (1 << kMobTileBits >> 4);
-__device__ __forceinline__ int mob_field(int t, int p) {
-  return (t & ((1 << p) - 1)) | ((t >> p) << (p + 4));
-}
-// levels [j0, 4) of the four register bits
-template <typename T>
-__device__ __forceinline__ void mob_levels(T (&x)[kMobElems], int j0) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (j >= j0) {
-#pragma unroll
-      for (int k = 0; k < kMobElems; ++k)
-        if (k & (1 << j)) x[k] = Num<T>::sub(x[k], x[k ^ (1 << j)]);
-    }
-}
-// the tile from layout `from` to layout `to`
-template <typename T>
-__device__ __forceinline__ void mob_exchange(T* m, T (&x)[kMobElems], int from, int to) {
-  const int a = mob_field(threadIdx.x, from), b = mob_field(threadIdx.x, to);
-#pragma unroll
-  for (int k = 0; k < kMobElems; ++k) m[mob_pad(a | (k << from))] = x[k];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kMobElems; ++k) x[k] = m[mob_pad(b | (k << to))];
-  __syncthreads();
-}
+struct MobSub {   // the Moebius butterfly
+  template <typename T> __device__ static T op(T hi, T lo) { return Num<T>::sub(hi, lo); }
+};
 
 // Low pass: kMobTileBits consecutive bits from 0 (all d of them where d is
 // smaller: the elements past 2^d are neither read nor written, and no valid
@@ -493,11 +451,11 @@ mobius_low_kernel(const InstDev* __restrict__ insts, const MobItem* __restrict__
       x[k] = e < nv ? Num<MobT>::from_in(s[e]) : Num<MobT>::zero();
     }
     mob_exchange<MobT>(m, x, 8, 0);
-    mob_levels<MobT>(x, 0);
+    mob_levels<MobSub>(x, 0);
     mob_exchange<MobT>(m, x, 0, 4);
-    mob_levels<MobT>(x, 0);
+    mob_levels<MobSub>(x, 0);
     mob_exchange<MobT>(m, x, 4, 8);
-    mob_levels<MobT>(x, 0);
+    mob_levels<MobSub>(x, 0);
 #pragma unroll
     for (int k = 0; k < kMobElems; ++k) {
       const int e = a | (k << 8);
@@ -520,23 +478,21 @@ mobius_high_kernel(const InstDev* __restrict__ insts, const MobItem* __restrict_
     const int64_t cl = w.block & (((int64_t)1 << (lo - cb)) - 1);   // which run of low indices
     const int64_t rest = w.block >> (lo - cb);                      // the bits above the group
     MobT* base = data + I.woff + (rest << (lo + G)) + (cl << cb);
-    const int cmask = (1 << cb) - 1;
-    auto at = [&](int e) { return ((int64_t)(e >> cb) << lo) + (e & cmask); };
-    // the lowest (at most) four group bits at p0 .. 11, then those above
+      // the lowest (at most) four group bits at p0 .. 11, then those above
     // them, the last of tile bits 8 .. 11
     const int p0 = min(cb, 8);
     MobT x[kMobElems];
     const int a0 = mob_field(threadIdx.x, p0);
 #pragma unroll
-    for (int k = 0; k < kMobElems; ++k) x[k] = base[at(a0 | (k << p0))];
-    mob_levels<MobT>(x, cb - p0);
+    for (int k = 0; k < kMobElems; ++k) x[k] = base[mob_high_at(a0 | (k << p0), cb, lo)];
+    mob_levels<MobSub>(x, cb - p0);
     if (G > 4) {
       mob_exchange<MobT>(m, x, p0, 8);
-      mob_levels<MobT>(x, cb - 4);
+      mob_levels<MobSub>(x, cb - 4);
     }
     const int a1 = mob_field(threadIdx.x, 8);
 #pragma unroll
-    for (int k = 0; k < kMobElems; ++k) base[at(a1 | (k << 8))] = x[k];
+    for (int k = 0; k < kMobElems; ++k) base[mob_high_at(a1 | (k << 8), cb, lo)] = x[k];
   }
 }
 
