@@ -152,18 +152,96 @@ __device__ __forceinline__ int list_leaves(const Node* __restrict__ P, const dou
   }
 }
 
+// Leaves of a pair reachable by any coalition at all, over the d bits: in must
+// be in S, out must not. Entry i of pair g at i * pairs + g, counts in cnt
+// (past kReach: not listed). Made once per call, so a block only picks the
+// ones its shared bits allow instead of walking the tree again.
+constexpr int kReach = 24;
+struct alignas(16) Reach {
+  uint32_t in, out;
+  double value;
+};
+struct ReachLists {
+  const Reach* leaf;
+  const int32_t* cnt;      // null: no lists
+};
+
+// A wave per pair: each lane takes a root-to-leaf path of the tree (64 at a
+// time) and keeps it if no feature fails both the explained point and the
+// background.
+__global__ void __launch_bounds__(kThreads)
+reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
+             const int32_t* __restrict__ tree_path, const int32_t* __restrict__ path_off,
+             const int32_t* __restrict__ steps, const int32_t* __restrict__ path_leaf, int n_trees,
+             int n_nodes, int64_t pairs, Reach* __restrict__ leaf, int32_t* __restrict__ cnt) {
+  const int lane = threadIdx.x & 63;
+  const int64_t wave0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
+  for (int64_t g = wave0; g < pairs; g += (int64_t)gridDim.x * (kThreads / 64)) {
+    const int b = (int)(g / n_trees), t = (int)(g - (int64_t)b * n_trees);
+    const Node* P = prep + (int64_t)(b / kBgChunk) * n_nodes;
+    const int jb = b % kBgChunk;
+    int n = 0;
+    for (int p0 = tree_path[t]; p0 < tree_path[t + 1]; p0 += 64) {
+      const int p = p0 + lane;
+      const bool on = p < tree_path[t + 1];
+      uint32_t seen = 0, aok = ~0u, bok = ~0u;
+      const int s1 = on ? path_off[p + 1] : 0;
+      for (int s = on ? path_off[p] : 0; s < s1; ++s) {
+        const int e = steps[s];
+        const Node w = P[e >> 1];
+        const uint32_t dir = e & 1, bit = 1u << ((uint32_t)w.code & 255u);
+        seen |= bit;
+        if ((((uint32_t)w.code >> 8) & 1u) != dir) aok &= ~bit;
+        if (((w.bits >> jb) & 1u) != dir) bok &= ~bit;
+      }
+      const uint32_t in = seen & ~bok;
+      const bool ok = on && !(in & ~aok);
+      const uint64_t m = __ballot(ok);
+      const int at = n + __popcll(m & ((1ull << lane) - 1ull));
+      if (ok && at < kReach)
+        leaf[(int64_t)at * pairs + g] = Reach{in, seen & bok & ~aok, value[path_leaf[p]]};
+      n += __popcll(m);
+    }
+    if (lane == 0) cnt[g] = n;
+  }
+}
+
 // One chunk: pairs [g0, g0 + np) of the (background, tree) sequence.
 template <int NP, int NK>
 __device__ __forceinline__ void build_lists(const Node* __restrict__ prep, const double* __restrict__ value,
                                             const int32_t* __restrict__ roots, int n_trees,
-                                            int n_nodes, int64_t g0, int np, int m,
-                                            uint32_t shared_bits, LeafLists<NP, NK>& L) {
+                                            int n_nodes, const ReachLists& reach, int64_t pairs,
+                                            int64_t g0, int np, int m, uint32_t shared_bits,
+                                            LeafLists<NP, NK>& L) {
   const int p = threadIdx.x;
   if (p >= np) return;
   const int64_t g = g0 + p;
   const int b = (int)(g / n_trees);
   const int root = roots[(int)(g - (int64_t)b * n_trees)];
   uint32_t* row = L.need() + p * LeafLists<NP, NK>::kNeedRow;
+  const int all = reach.cnt ? reach.cnt[g] : kReach + 1;
+  if (all <= kReach) {
+    double* vrow = L.val + p * LeafLists<NP, NK>::kValRow;
+    const uint32_t low = (1u << m) - 1u;
+    int n = 0;
+    for (int i = 0; i < all; i += 4) {
+      Reach e[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e[q] = reach.leaf[(int64_t)min(i + q, all - 1) * pairs + g];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (i + q >= all || (e[q].in & ~low & ~shared_bits) || (e[q].out & ~low & shared_bits)) continue;
+        if (n < NK) {
+          row[n] = (e[q].in & low) | (e[q].out & low) << 16;
+          vrow[n] = e[q].value;
+        }
+        ++n;
+      }
+    }
+    row[NK] = (uint32_t)min(n, NK + 1);
+    row[NK + 1] = (uint32_t)root;
+    return;
+  }
   row[NK] = (uint32_t)list_leaves<NK>(prep + (int64_t)(b / kBgChunk) * n_nodes, value, root,
                                       b % kBgChunk, m, shared_bits, row,
                                       L.val + p * LeafLists<NP, NK>::kValRow);
@@ -219,8 +297,8 @@ constexpr int kWideNK = 12;
 template <typename OutT, int KP>
 __global__ void __launch_bounds__(kThreads)
 walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
-                 const int32_t* __restrict__ roots, int n_trees, int n_nodes, int n_bg, int d, int m,
-                 OutT* __restrict__ v) {
+                 const int32_t* __restrict__ roots, int n_trees, int n_nodes, ReachLists reach, int n_bg,
+                 int d, int m, OutT* __restrict__ v) {
   constexpr int NP = kThreads, NK = kWideNK;
   __shared__ LeafLists<NP, NK> L;
   const uint32_t base = (uint32_t)blockIdx.x * (kThreads * KP);
@@ -237,7 +315,7 @@ walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value
   const int64_t total = (int64_t)n_bg * n_trees;
   for (int64_t g0 = 0; g0 < total; g0 += NP) {
     const int np = (int)min((int64_t)NP, total - g0);
-    build_lists<NP, NK>(prep, value, roots, n_trees, n_nodes, g0, np, m, base, L);
+    build_lists<NP, NK>(prep, value, roots, n_trees, n_nodes, reach, total, g0, np, m, base, L);
     __syncthreads();
     for (int p0 = 0; p0 < np; p0 += 64) {
       const LaneLists ll = lane_lists<NP, NK>(L, min(p0 + lane, np - 1));
@@ -253,10 +331,17 @@ walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value
           for (int j = 0; j < KP; ++j)
             acc[j] += value[walk_one(P, root, b % kBgChunk, base | (nx[j] >> 16))];
         } else {
+          const double* row = L.val + p * LeafLists<NP, NK>::kValRow;
+          if (n == 1) {   // the whole block takes one leaf
+            const double x = row[0];
+#pragma unroll
+            for (int j = 0; j < KP; ++j) acc[j] += x;
+            continue;
+          }
           int idx[KP];
           match<NP, NK, KP>(L, ll, p, q, n, nx, idx);
 #pragma unroll
-          for (int j = 0; j < KP; ++j) acc[j] += L.val[p * LeafLists<NP, NK>::kValRow + idx[j]];
+          for (int j = 0; j < KP; ++j) acc[j] += row[idx[j]];
         }
       }
     }
@@ -269,22 +354,32 @@ walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value
   }
 }
 
-// Few coalitions: a workgroup owns 64 of them and its waves split the pairs.
-// Each wave matches 64 pairs of a chunk and leaves the leaf indexes (one byte
-// per pair and coalition) in LDS; one wave then adds the outputs in the
-// order of the pairs.
-constexpr int kNarrowNK = 16;
-constexpr int kNarrowThreads = 512;
+// Few coalitions: a workgroup owns 64 of them and runs the pairs as a
+// pipeline over three buffers of lists: in one step four waves list a chunk,
+// six match the chunk before (leaving each coalition's leaf in LDS, one byte
+// per pair: its offset in the list) and one adds the outputs of the chunk
+// before that, in the order of the pairs. The sums are one chain per coalition
+// (5000 additions at 50 trees and 100 backgrounds) and a wave issues an
+// instruction every four to five clocks, so that wave shares its SIMD with a
+// listing wave only (the roles go by wave number, SIMD = wave % 4), and the
+// matching waves the other three. 50 trees, d = 14, 100 backgrounds: 185 us
+// with the three parts in turns, 142 with a matching wave beside the adding
+// one, now 114.
+constexpr int kNarrowNK = 12;
+constexpr int kNarrowPairs = 256;
+constexpr int kNarrowThreads = 768;
+constexpr int kAddWave = 4;        // waves 0-3 list, 8 idles, the other six match
 template <typename OutT>
 __global__ void __launch_bounds__(kNarrowThreads)
 walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
-                   const int32_t* __restrict__ roots, int n_trees, int n_nodes, int n_bg, int d,
-                   OutT* __restrict__ v) {
-  constexpr int NP = kNarrowThreads, NK = kNarrowNK;
+                   const int32_t* __restrict__ roots, int n_trees, int n_nodes, ReachLists reach, int n_bg,
+                   int d, OutT* __restrict__ v) {
+  constexpr int NP = kNarrowPairs, NK = kNarrowNK;
   constexpr int VR = LeafLists<NP, NK>::kValRow;
-  __shared__ LeafLists<NP, NK> L;
-  __shared__ uint32_t pick[NP / 4][64];   // bytes: leaf index of pairs 4 r .. 4 r + 3 (255: walk)
-  __shared__ uint32_t unlisted[NP / 16];  // pairs 16 r .. 16 r + 15 hold one without a list
+  __shared__ LeafLists<NP, NK> lists[3];
+  // byte i: 8 x leaf index of pair 16 r + i (255: walk)
+  __shared__ uint4 picks[2][NP / 16][64];
+  __shared__ uint32_t unlisted[2][NP / 16];   // pairs 16 r .. 16 r + 15 hold one without a list
   const int m = min(d, 6);
   const uint32_t base = (uint32_t)blockIdx.x << 6;
   const int lane = threadIdx.x & 63;
@@ -293,64 +388,83 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
   const uint32_t nx[1] = {(~low & 0xffffu) | (low << 16)};
   double acc = 0.0;
   const int64_t total = (int64_t)n_bg * n_trees;
-  for (int64_t g0 = 0; g0 < total; g0 += NP) {
-    const int np = (int)min((int64_t)NP, total - g0);
-    auto add_pair = [&](int p, int idx) {
-      if (idx != 255) {
-        acc += L.val[p * VR + idx];
-      } else {   // the pair has no list (uniform)
-        const int b = (int)((g0 + p) / n_trees);
-        const int root = (int)L.need()[p * LeafLists<NP, NK>::kNeedRow + NK + 1];
-        acc += value[walk_one(prep + (int64_t)(b / kBgChunk) * n_nodes, root, b % kBgChunk,
-                              base | low)];
-      }
-    };
-    build_lists<NP, NK>(prep, value, roots, n_trees, n_nodes, g0, np, m, base, L);
-    __syncthreads();
-    const int p0 = wave * 64;
-    if (p0 < np) {
-      const LaneLists ll = lane_lists<NP, NK>(L, min(p0 + lane, np - 1));
-      const int nq = min(64, np - p0);
-      for (int q0 = 0; q0 < nq; q0 += 4) {
-        uint32_t w = 0;
+  const int64_t chunks = (total + NP - 1) / NP;
+  for (int64_t it = 0; it < chunks + 2; ++it) {
+    if (wave < NP / 64) {
+      const int64_t g0 = it * NP;
+      if (it < chunks)
+        build_lists<NP, NK>(prep, value, roots, n_trees, n_nodes, reach, total, g0,
+                            (int)min((int64_t)NP, total - g0), m, base, lists[it % 3]);
+    } else if (wave % 4 != 0) {
+      // groups of 16 pairs, dealt to the six waves
+      const int64_t c = it - 1;
+      const int np = c >= 0 && c < chunks ? (int)min((int64_t)NP, total - c * NP) : 0;
+      LeafLists<NP, NK>& L = lists[(c + 3) % 3];
+      for (int p0 = 16 * (wave % 4 - 1 + 3 * (wave / 8)); p0 < np; p0 += 16 * 6) {
+        const LaneLists ll = lane_lists<NP, NK>(L, min(p0 + (lane & 15), np - 1));
+        const int nq = min(16, np - p0);
+        uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int q = min(q0 + i, nq - 1);
+        for (int i = 0; i < 16; ++i) {
+          const int q = min(i, nq - 1);
           const int n = __builtin_amdgcn_readlane((int)ll.cnt, q);
-          int idx[1] = {255};
-          if (n <= NK) match<NP, NK, 1>(L, ll, p0 + q, q, n, nx, idx);
-          w |= (uint32_t)idx[0] << (8 * i);
+          if (n > NK) {
+            w[i >> 2] |= 255u << (8 * (i & 3));
+          } else if (n > 1) {
+            int idx[1];
+            match<NP, NK, 1>(L, ll, p0 + q, q, n, nx, idx);
+            w[i >> 2] |= (uint32_t)idx[0] << (8 * (i & 3) + 3);
+          }
         }
-        pick[(p0 + q0) >> 2][lane] = w;
+        picks[c & 1][p0 >> 4][lane] = uint4{w[0], w[1], w[2], w[3]};
+        const uint64_t over = __ballot(lane < nq && ll.cnt > (uint32_t)NK);
+        if (lane == 0) unlisted[c & 1][p0 >> 4] = over != 0;
       }
-      const uint64_t over = __ballot(lane < nq && ll.cnt > (uint32_t)NK);
-      if (lane < 4) unlisted[(p0 >> 4) + lane] = (uint32_t)(over >> (16 * lane)) & 0xffffu;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      // groups of 16 pairs without an unlisted one: every LDS read of a group
-      // is issued before its additions (read by read, one pair waited for the
-      // one before: 400 of 558 us at 50 trees, d = 14, 100 backgrounds)
-      int p = 0;
-      for (; p + 16 <= np; p += 16) {
-        uint32_t w[4];
+    } else if (wave == kAddWave && it >= 2) {
+      const int64_t c = it - 2, g0 = c * NP;
+      const int np = (int)min((int64_t)NP, total - g0);
+      LeafLists<NP, NK>& L = lists[c % 3];
+      const uint4 (*pick)[64] = picks[c & 1];
+      // every LDS read of 16 pairs in flight while the 16 before are added
+      // (read by read, one pair waited for the one before: 400 us)
+      const bool plain = __ballot(lane < NP / 16 && lane * 16 < np && unlisted[c & 1][lane & (NP / 16 - 1)]) == 0;
+      const int full = plain ? np / 16 : 0;   // groups of 16 with a list for every pair
+      double x[2][16];
+      auto fetch = [&](int g, double (&y)[16]) {
+        const uint4 u = pick[g][lane];
+        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+        const unsigned char* row = reinterpret_cast<const unsigned char*>(L.val + g * 16 * VR);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = pick[(p >> 2) + i][lane];
-        if (unlisted[p >> 4]) {
-          for (int i = 0; i < 16; ++i) add_pair(p + i, (int)((w[i >> 2] >> (8 * (i & 3))) & 255u));
-          continue;
+        for (int i = 0; i < 16; ++i)
+          y[i] = *reinterpret_cast<const double*>(row + ((w[i >> 2] >> (8 * (i & 3))) & 255u) + i * VR * 8);
+      };
+      if (full > 0) fetch(0, x[0]);
+      for (int g = 0; g < full; g += 2) {
+        if (g + 1 < full) fetch(g + 1, x[1]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc += x[0][i];
+        if (g + 1 >= full) break;
+        if (g + 2 < full) fetch(g + 2, x[0]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc += x[1][i];
+      }
+      for (int p = full * 16; p < np; ++p) {
+        const uint4 u = pick[p >> 4][lane];
+        const uint32_t w = (p & 8) ? ((p & 4) ? u.w : u.z) : ((p & 4) ? u.y : u.x);
+        const uint32_t o = (w >> (8 * (p & 3))) & 255u;
+        if (o != 255u) {
+          acc += L.val[p * VR + (o >> 3)];
+        } else {   // the pair has no list (uniform)
+          const int b = (int)((g0 + p) / n_trees);
+          const int root = (int)L.need()[p * LeafLists<NP, NK>::kNeedRow + NK + 1];
+          acc += value[walk_one(prep + (int64_t)(b / kBgChunk) * n_nodes, root, b % kBgChunk,
+                                base | low)];
         }
-        double x[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = L.val[(p + i) * VR + ((w[i >> 2] >> (8 * (i & 3))) & 255u)];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc += x[i];
       }
-      for (; p < np; ++p) add_pair(p, (int)((pick[p >> 2][lane] >> (8 * (p & 3))) & 255u));
     }
     __syncthreads();
   }
-  if (wave == 0) {
+  if (wave == kAddWave) {
     const uint32_t s = base + (uint32_t)lane;
     if (s < (1u << d)) v[s] = (OutT)(acc / (double)n_bg);
   }
@@ -361,20 +475,20 @@ int walk_kp(int d) { return d >= 19 ? 4 : d >= 18 ? 2 : d >= 16 ? 1 : 0; }
 
 template <typename OutT>
 void launch_walk(const Node* prep, const double* value, const int32_t* roots, int n_trees,
-                 int n_nodes, int n_bg, int d, OutT* v, hipStream_t st) {
+                 int n_nodes, const ReachLists& reach, int n_bg, int d, OutT* v, hipStream_t st) {
   const int kp = walk_kp(d);
   if (kp == 0) {
     const int grid = d > 6 ? 1 << (d - 6) : 1;
     walk_narrow_kernel<OutT><<<grid, kNarrowThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes,
-                                                              n_bg, d, v);
+                                                              reach, n_bg, d, v);
     return;
   }
   const int m = kp == 4 ? 10 : kp == 2 ? 9 : 8;
   const int grid = 1 << (d - m);
   switch (kp) {
-    case 1: walk_wide_kernel<OutT, 1><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, n_bg, d, m, v); break;
-    case 2: walk_wide_kernel<OutT, 2><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, n_bg, d, m, v); break;
-    default: walk_wide_kernel<OutT, 4><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, n_bg, d, m, v); break;
+    case 1: walk_wide_kernel<OutT, 1><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
+    case 2: walk_wide_kernel<OutT, 2><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
+    default: walk_wide_kernel<OutT, 4><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
   }
 }
 
@@ -596,6 +710,11 @@ void launch_zeta(double* a, int d, OutT* out, hipStream_t st) {
   }
 }
 
+// Lists of reachable leaves are kept for forests that need at most this much
+// for them, and used from the size where several blocks share them.
+constexpr size_t kReachBytes = (size_t)64 << 20;
+constexpr int kReachMinD = 8;
+
 constexpr int kMaxFreeSplits = 24;  // longest path the Moebius route expands
 constexpr int64_t kMaxPathSteps = (int64_t)1 << 26;
 
@@ -619,6 +738,9 @@ struct fsi_forest_s {
   int32_t* path_off = nullptr;
   int32_t* steps = nullptr;        // node << 1 | went right
   int32_t* path_leaf = nullptr;
+  int32_t* tree_path = nullptr;    // first path of each tree, n_trees + 1
+  Reach* reach = nullptr;          // leaf lists of a walk call (null: not kept)
+  int32_t* reach_cnt = nullptr;
 };
 
 namespace {
@@ -632,7 +754,8 @@ void free_forest(fsi_forest_s* F) {
   if (!F) return;
   for (void* p : {(void*)F->feature, (void*)F->left, (void*)F->right, (void*)F->roots,
                   (void*)F->threshold, (void*)F->value, (void*)F->prep,
-                  (void*)F->path_off, (void*)F->steps, (void*)F->path_leaf})
+                  (void*)F->path_off, (void*)F->steps, (void*)F->path_leaf, (void*)F->tree_path,
+                  (void*)F->reach, (void*)F->reach_cnt})
     if (p) (void)hipFree(p);
   delete F;
 }
@@ -677,14 +800,17 @@ int forest_depth(int n_nodes, const int32_t* feature, const int32_t* left,
 // routes counts once per path). Returns false if the paths exceed the caps.
 bool enumerate_paths(const int32_t* feature, const int32_t* left, const int32_t* right,
                      const int32_t* roots, int n_trees, std::vector<int32_t>* off,
-                     std::vector<int32_t>* steps, std::vector<int32_t>* leaf) {
+                     std::vector<int32_t>* steps, std::vector<int32_t>* leaf,
+                     std::vector<int32_t>* tree) {
   off->assign(1, 0);
+  tree->clear();
   steps->clear();
   leaf->clear();
   std::vector<int32_t> path;
   // explicit DFS: (node, next child to visit: 0 left, 1 right, 2 done)
   std::vector<std::pair<int, int>> st;
   for (int k = 0; k < n_trees; ++k) {
+    tree->push_back((int32_t)leaf->size());
     st.assign(1, {roots[k], 0});
     path.clear();
     while (!st.empty()) {
@@ -710,6 +836,7 @@ bool enumerate_paths(const int32_t* feature, const int32_t* left, const int32_t*
       st.push_back({dir ? right[node] : left[node], 0});
     }
   }
+  tree->push_back((int32_t)leaf->size());
   return true;
 }
 
@@ -779,8 +906,8 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
     e = hipMalloc((void**)&F->prep, chunks * (size_t)n_nodes * sizeof(Node));
   }
   if (e == hipSuccess) {
-    std::vector<int32_t> poff, psteps, pleaf;
-    if (enumerate_paths(feat.data(), left, right, roots, n_trees, &poff, &psteps, &pleaf)) {
+    std::vector<int32_t> poff, psteps, pleaf, ptree;
+    if (enumerate_paths(feat.data(), left, right, roots, n_trees, &poff, &psteps, &pleaf, &ptree)) {
       F->n_paths = (int)pleaf.size();
       for (size_t p = 0; p + 1 < poff.size(); ++p)
         F->max_path = std::max(F->max_path, poff[p + 1] - poff[p]);
@@ -792,6 +919,12 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
       e = upload(&F->path_off, poff.data(), poff.size());
       if (e == hipSuccess) e = upload(&F->steps, psteps.data(), std::max<size_t>(psteps.size(), 1));
       if (e == hipSuccess) e = upload(&F->path_leaf, pleaf.data(), pleaf.size());
+      if (e == hipSuccess) e = upload(&F->tree_path, ptree.data(), ptree.size());
+      const size_t pairs = (size_t)max_bg * (size_t)n_trees;
+      if (e == hipSuccess && pairs * kReach * sizeof(Reach) <= kReachBytes) {
+        e = hipMalloc((void**)&F->reach, pairs * kReach * sizeof(Reach));
+        if (e == hipSuccess) e = hipMalloc((void**)&F->reach_cnt, pairs * sizeof(int32_t));
+      }
     }
   }
   if (e != hipSuccess) {
@@ -827,10 +960,19 @@ fsi_status fsi_forest_values(fsi_forest_t F, const double* x_dev, int n_bg, cons
   const int prep_grid = (int)std::min<int64_t>((prep_total + kThreads - 1) / kThreads, 4096);
   prep_kernel<<<prep_grid, kThreads, 0, stream>>>(F->feature, F->threshold, F->left, F->right,
                                                   F->n_nodes, F->d, x_dev, bg_dev, n_bg, F->prep);
+  ReachLists reach{nullptr, nullptr};
+  if (F->reach && F->d >= kReachMinD) {
+    const int64_t pairs = (int64_t)n_bg * F->n_trees;
+    const int grid = (int)std::min<int64_t>((pairs + kThreads / 64 - 1) / (kThreads / 64), 4096);
+    reach_kernel<<<grid, kThreads, 0, stream>>>(F->prep, F->value, F->tree_path, F->path_off, F->steps,
+                                                F->path_leaf, F->n_trees, F->n_nodes, pairs, F->reach,
+                                                F->reach_cnt);
+    reach = ReachLists{F->reach, F->reach_cnt};
+  }
   if (dtype == FSI_DTYPE_F64)
-    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, n_bg, F->d, (double*)v_dev, stream);
+    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, reach, n_bg, F->d, (double*)v_dev, stream);
   else
-    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, n_bg, F->d, (float*)v_dev, stream);
+    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, reach, n_bg, F->d, (float*)v_dev, stream);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ffail(FSI_ERR_HIP, std::string("forest launch: ") + hipGetErrorString(e));
   return FSI_OK;
