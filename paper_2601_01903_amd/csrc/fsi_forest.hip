@@ -470,8 +470,12 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
   }
 }
 
-// Coalitions per thread of the wide kernel, 0 for the narrow one.
-int walk_kp(int d) { return d >= 19 ? 4 : d >= 18 ? 2 : d >= 16 ? 1 : 0; }
+// Coalitions per thread of the wide kernel, 0 for the narrow one: four where
+// that still gives every CU four workgroups, and the narrow kernel, which
+// takes one workgroup per CU and 64 coalitions, up to four rounds of them (50
+// depth-4 trees, 100 backgrounds: d = 16 wide 818 us, narrow 445; d = 17 wide
+// 831, narrow 844).
+int walk_kp(int d) { return d >= 19 ? 4 : d >= 18 ? 2 : d >= 17 ? 1 : 0; }
 
 template <typename OutT>
 void launch_walk(const Node* prep, const double* value, const int32_t* roots, int n_trees,
@@ -711,9 +715,8 @@ void launch_zeta(double* a, int d, OutT* out, hipStream_t st) {
 }
 
 // Lists of reachable leaves are kept for forests that need at most this much
-// for them, and used from the size where several blocks share them.
+// for them.
 constexpr size_t kReachBytes = (size_t)64 << 20;
-constexpr int kReachMinD = 8;
 
 constexpr int kMaxFreeSplits = 24;  // longest path the Moebius route expands
 constexpr int64_t kMaxPathSteps = (int64_t)1 << 26;
@@ -961,7 +964,7 @@ fsi_status fsi_forest_values(fsi_forest_t F, const double* x_dev, int n_bg, cons
   prep_kernel<<<prep_grid, kThreads, 0, stream>>>(F->feature, F->threshold, F->left, F->right,
                                                   F->n_nodes, F->d, x_dev, bg_dev, n_bg, F->prep);
   ReachLists reach{nullptr, nullptr};
-  if (F->reach && F->d >= kReachMinD) {
+  if (F->reach) {
     const int64_t pairs = (int64_t)n_bg * F->n_trees;
     const int grid = (int)std::min<int64_t>((pairs + kThreads / 64 - 1) / (kThreads / 64), 4096);
     reach_kernel<<<grid, kThreads, 0, stream>>>(F->prep, F->value, F->tree_path, F->path_off, F->steps,
