@@ -470,12 +470,14 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
   }
 }
 
-// Coalitions per thread of the wide kernel, 0 for the narrow one: four where
-// that still gives every CU four workgroups, and the narrow kernel, which
+// Coalitions per thread of the wide kernel, 0 for the narrow one: eight or four
+// where that still gives every CU four workgroups (8 against 4: 100 depth-6
+// trees at d = 21 70 against 82 us, 200 at d = 20 101 against 90), and the
+// narrow kernel, which
 // takes one workgroup per CU and 64 coalitions, up to four rounds of them (50
 // depth-4 trees, 100 backgrounds: d = 16 wide 818 us, narrow 445; d = 17 wide
 // 831, narrow 844).
-int walk_kp(int d) { return d >= 19 ? 4 : d >= 18 ? 2 : d >= 17 ? 1 : 0; }
+int walk_kp(int d) { return d >= 21 ? 8 : d >= 19 ? 4 : d >= 18 ? 2 : d >= 17 ? 1 : 0; }
 
 template <typename OutT>
 void launch_walk(const Node* prep, const double* value, const int32_t* roots, int n_trees,
@@ -487,11 +489,12 @@ void launch_walk(const Node* prep, const double* value, const int32_t* roots, in
                                                               reach, n_bg, d, v);
     return;
   }
-  const int m = kp == 4 ? 10 : kp == 2 ? 9 : 8;
+  const int m = kp == 8 ? 11 : kp == 4 ? 10 : kp == 2 ? 9 : 8;
   const int grid = 1 << (d - m);
   switch (kp) {
     case 1: walk_wide_kernel<OutT, 1><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
     case 2: walk_wide_kernel<OutT, 2><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
+    case 8: walk_wide_kernel<OutT, 8><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
     default: walk_wide_kernel<OutT, 4><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
   }
 }

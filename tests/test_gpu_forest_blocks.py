@@ -28,8 +28,8 @@ def full_trees(d, n_trees, depth, rng):
             right.ravel(), value.ravel())
 
 
-# 5 .. 7: around one wave of coalitions; 15 .. 19: every kernel choice
-@pytest.mark.parametrize("d", [2, 5, 6, 7, 10, 15, 16, 17, 18, 19])
+# 5 .. 7: around one wave of coalitions; 15 .. 21: every kernel choice
+@pytest.mark.parametrize("d", [2, 5, 6, 7, 10, 15, 16, 17, 18, 19, 21])
 @pytest.mark.parametrize("undecided", [False, True])
 def test_blocks_and_full_lists(d, undecided):
     """undecided: x = 1 and background 0, so that no node is decided by the
