@@ -201,6 +201,15 @@ struct Sched {
   int algo = 0;         // FSI_ALGO_FUSED or FSI_ALGO_TWO_PASS; 0: the option's
 };
 
+// Device scratch of fsi_apply_batched_noalloc; a plan's schedule keeps within
+// it where that costs little, so that the entry point takes the plan.
+constexpr size_t kScratchBytes = size_t(64) << 20;
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+size_t scratch_need(const fsi_batch_plan_s* P) {
+  return align256(P->partial_bytes) + align256(P->y_bytes) + align256(P->wide_bytes) +
+         align256(P->work_bytes);
+}
+
 // FSI_ALGO_AUTO without the autotuner: the fused algorithm, unless every
 // instance has an order of at least kAutoTwoPassL (value input, no kernel
 // named: a named kernel is one of the fused algorithm's). Such
@@ -439,6 +448,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     return cs;
   };
   int64_t chunk = 1;
+  int run_wgs = fast_wgs;   // workgroups a CU runs
   {
     // us per tile of a workgroup at l = 1 .. 4, by the workgroups that share
     // its CU (256 and 128 x d = 20, whole launches): the rows are the sweep in
@@ -446,7 +456,10 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     static const double kTileUs[2][3][kFastMaxL + 1] = {
         {{0, 2.1, 2.5, 3.0, 3.2}, {0, 2.5, 3.0, 3.65, 3.9}, {0, 3.3, 4.2, 5.2, 5.2}},
         {{0, 2.8, 3.3, 4.1, 4.4}, {0, 3.4, 4.5, 5.7, 6.5}, {0, 3.4, 4.5, 5.7, 6.5}}};
+    static const double kItemUs[2][3] = {{5.0, 6.0, 7.0}, {6.0, 9.0, 9.0}};
     const double red_base_us = 4.0, red_bytes_per_us = 3.0e6;
+    const double queue_us = 3.0;   // a launch with more items than workgroups
+    const int64_t kFitBytes = (int64_t)kScratchBytes - ytot * 8;
     int64_t max_tiles = 1;
     for (int i = 0; i < n; ++i)
       if (P->fast_of[P->cls_of[i]] >= 0)
@@ -456,7 +469,17 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
       cand.push_back(c2);
       if (c2 >= 2 && c2 + c2 / 2 <= max_tiles) cand.push_back(c2 + c2 / 2);
     }
-    double best = -1.0;
+    // and the sizes that give every workgroup 1 .. 8 items (150 x d = 20,
+    // l = 4 in FP32: 735 -> 623 us)
+    for (int64_t k = 1; k <= 8; ++k) {
+      const int64_t c2 = (fast_tiles + slots * k - 1) / (slots * k);
+      if (c2 >= 1 && c2 <= max_tiles) cand.push_back(c2);
+    }
+    std::sort(cand.begin(), cand.end());
+    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
+    double best = -1.0, best_fit = -1.0;
+    int64_t chunk_fit = 0;
+    int wgs_fit = fast_wgs;
     std::vector<double> cost;
     for (int64_t c : cand) {
       // sizes that cut the batch into far more items than workgroups only
@@ -468,38 +491,62 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
           items += (ntile + item_tiles(i, c) - 1) / item_tiles(i, c);
         }
       if (items > 64 * (int64_t)slots && c != cand.back()) continue;
-      const int share = items <= n_cu ? 1 : std::min(fast_wgs, 3);
-      const double* tile_us = kTileUs[prec == PREC_F64][share - 1];
-      const double item_us = share == 3 ? 8.0 : share == 2 && prec == PREC_F64 ? 9.0 : 6.0;
-      cost.clear();
-      double part_bytes = 0.0;
-      for (int i = 0; i < n; ++i) {
-        const int f = P->fast_of[P->cls_of[i]];
-        if (f < 0) continue;
-        const FastClassHost& F = P->fclasses[f];
-        const int64_t ntile = (int64_t)1 << F.h, cs = item_tiles(i, c);
-        for (int64_t tb = 0; tb < ntile; tb += cs) {
-          const int64_t nt = std::min<int64_t>(cs, ntile - tb);
-          cost.push_back((double)nt * tile_us[F.l] + item_us);
-          part_bytes += (double)F.nkk * kFastThreads * 8.0;
+      // every number of workgroups per CU, up to the most that fit: fewer run
+      // their tiles faster, and the items may fill their rounds better (only
+      // the most where the launch has many rounds). 1000 x d = 13, l = 2 in
+      // FP32: 51 us at three, 40 at two
+      for (int w = items > 4 * (int64_t)slots ? fast_wgs : 1; w <= fast_wgs; ++w) {
+        // workgroups of the busiest CU and of the average one: a tile costs the
+        // mean of the two (items of even cost, 200 x d = 15 to 100 x d = 20)
+        const double wgs_max = (double)std::min<int64_t>((items + n_cu - 1) / n_cu, std::min(w, 3));
+        const double wgs = 0.5 * (wgs_max + std::min((double)items / n_cu, wgs_max));
+        const int s0 = std::max(0, (int)wgs - 1), s1 = std::min(s0 + 1, 2);
+        const double frac = std::max(0.0, wgs - 1 - s0);
+        auto at = [&](const double* row0, const double* row1) { return *row0 + frac * (*row1 - *row0); };
+        const auto& us = kTileUs[prec == PREC_F64];
+        double tile_us[kFastMaxL + 1];
+        for (int l = 0; l <= kFastMaxL; ++l) tile_us[l] = at(&us[s0][l], &us[s1][l]);
+        const double item_us = at(&kItemUs[prec == PREC_F64][s0], &kItemUs[prec == PREC_F64][s1]);
+        cost.clear();
+        double part_bytes = 0.0;
+        for (int i = 0; i < n; ++i) {
+          const int f = P->fast_of[P->cls_of[i]];
+          if (f < 0) continue;
+          const FastClassHost& F = P->fclasses[f];
+          const int64_t ntile = (int64_t)1 << F.h, cs = item_tiles(i, c);
+          for (int64_t tb = 0; tb < ntile; tb += cs) {
+            const int64_t nt = std::min<int64_t>(cs, ntile - tb);
+            cost.push_back((double)nt * tile_us[F.l] + item_us);
+            if (cs < ntile) part_bytes += (double)F.nkk * kFastThreads * 8.0;
+          }
+        }
+        std::sort(cost.begin(), cost.end(), std::greater<double>());
+        std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+        for (double x : cost) {
+          if ((int)busy.size() < n_cu * w) {
+            busy.push(x);
+          } else {
+            const double t = busy.top();
+            busy.pop();
+            busy.push(t + x);
+          }
+        }
+        double end = 0.0;
+        while (!busy.empty()) { end = std::max(end, busy.top()); busy.pop(); }
+        const double total = end + red_base_us + part_bytes / red_bytes_per_us +
+                             (items > n_cu * w ? queue_us : 0.0);
+        if (best < 0.0 || total < best) { best = total; chunk = c; run_wgs = w; }
+        if (part_bytes <= (double)kFitBytes && (best_fit < 0.0 || total < best_fit)) {
+          best_fit = total;
+          chunk_fit = c;
+          wgs_fit = w;
         }
       }
-      std::sort(cost.begin(), cost.end(), std::greater<double>());
-      std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
-      for (double x : cost) {
-        if ((int)busy.size() < slots) {
-          busy.push(x);
-        } else {
-          const double t = busy.top();
-          busy.pop();
-          busy.push(t + x);
-        }
-      }
-      double end = 0.0;
-      while (!busy.empty()) { end = std::max(end, busy.top()); busy.pop(); }
-      const double total = end + red_base_us + part_bytes / red_bytes_per_us;
-      if (best < 0.0 || total < best) { best = total; chunk = c; }
     }
+    // partial sums within the scratch of fsi_apply_batched_noalloc, unless
+    // that costs more than a tenth
+    if (chunk_fit > 0 && best_fit <= 1.1 * best) { chunk = chunk_fit; run_wgs = wgs_fit; }
+    if (sc.chunk_shift != 0) run_wgs = fast_wgs;
     if (sc.chunk_shift > 0) chunk <<= sc.chunk_shift;
     if (sc.chunk_shift < 0) chunk = std::max<int64_t>(1, chunk >> -sc.chunk_shift);
   }
@@ -527,7 +574,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     insts[i].lowmask = dh[i] < kFastTileBits ? (1 << dh[i]) - 1 : (1 << kFastTileBits) - 1;
     for (int64_t tb = 0; tb < ntile; tb += cs) {
       fitems.push_back(FastItem{i, (int32_t)tb, (int32_t)std::min<int64_t>(tb + cs, ntile), 0, ptot});
-      ptot += (int64_t)F.nkk * kFastThreads;
+      if (nit > 1) ptot += (int64_t)F.nkk * kFastThreads;
     }
   }
   // a workgroup that has its CU to itself: the form without shared regions
@@ -901,6 +948,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     e = configure_fast(prec, fast_np);
     if (e != hipSuccess) { return fail(FSI_ERR_HIP, std::string("configure_fast: ") + hipGetErrorString(e)); }
     a.fast.prec = prec;
+    a.fast.n_cu = n_cu;
     a.fast.classes = reinterpret_cast<const FastClassDev*>(A + o_fcls);
     a.fast.insts = a.insts;
     a.fast.items = reinterpret_cast<const FastItem*>(A + o_fitems);
@@ -914,9 +962,9 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     for (int l = 0; l <= kFastMaxL; ++l) {
       a.fast.np[l] = fast_np[l];
       const int nl = l >= 1 ? lbeg[l + 1] - lbeg[l] : 0;
-      a.fast.grid[l] = nl > 0 ? std::max(1, std::min(nl, n_cu * fast_wgs_per_cu(prec, l, fast_np[l]))) : 0;
+      a.fast.grid[l] = nl > 0 ? std::max(1, std::min(nl, n_cu * std::min(run_wgs, fast_wgs_per_cu(prec, l, fast_np[l])))) : 0;
     }
-    a.fast.grid_mixed = std::max(1, std::min((int)fitems.size(), slots));
+    a.fast.grid_mixed = std::max(1, std::min((int)fitems.size(), n_cu * run_wgs));
   }
   P->sched.autotuned = 0;
   P->sched.fast_instances = 0;
@@ -1112,7 +1160,7 @@ fsi_status build_tuned(int n, const int* dh, const int* lh, const fsi_plan_opts*
       }
   }
   if (two_pass) {
-    for (int g = 4; g <= 6; ++g)
+    for (int g = 4; g <= kMobGroup; g += 2)
       for (int tb = 0; tb >= (opts.tile_bits ? 0 : -1); --tb) {
         Sched s; s.mob_group = g; s.tb_shift = tb; s.algo = both ? FSI_ALGO_TWO_PASS : 0;
         cand.push_back(s);
@@ -1183,7 +1231,6 @@ fsi_status build_tuned(int n, const int* dh, const int* lh, const fsi_plan_opts*
 // same array, so such calls that overlap on one GPU race; the array keeps
 // the last call's contents (no kernel of an apply reads a workspace word
 // before the same apply has written it, so nothing needs clearing).
-constexpr size_t kScratchBytes = size_t(64) << 20;
 constexpr int kScratchMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -1206,13 +1253,6 @@ fsi_status scratch_address(int dev, unsigned char** out) {
   }
   *out = static_cast<unsigned char*>(g_scratch_ptr[dev]);
   return FSI_OK;
-}
-
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-size_t scratch_need(const fsi_batch_plan_s* P) {
-  return align256(P->partial_bytes) + align256(P->y_bytes) + align256(P->wide_bytes) +
-         align256(P->work_bytes);
 }
 
 // Notes the stream of the plan's work: destroying the plan waits for that

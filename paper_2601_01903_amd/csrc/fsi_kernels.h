@@ -42,6 +42,7 @@ struct FastLaunch {
   const InstDev* insts;
   const FastItem* items;
   int n_items;
+  int n_cu;
   int lbeg[kFastMaxL + 2];
   int grid[kFastMaxL + 1];
   int np[kFastMaxL + 1];          // most gather positions of the plan's classes of order l
