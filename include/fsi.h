@@ -165,7 +165,11 @@ typedef struct {
  * accumulators: a work item then covers a block of 2^6 tiles sharing their
  * top high bits, and the wide gather combines the blocks' partial sums;
  * every tile is still read and swept once. The generic LDS kernel covers
- * every (d, l). AUTO picks the register-phase kernel where it applies. */
+ * every (d, l). AUTO picks the register-phase kernel where it applies, and
+ * for orders 5 and 6 (tile_bits 0 or 11) the same phases with the per-tile
+ * results kept in memory, as the generic kernel keeps them: there only where
+ * they leave the plan within the scratch of fsi_apply_batched_noalloc or the
+ * generic kernel's would exceed it too. */
 typedef enum {
   FSI_KERNEL_AUTO = 0,
   FSI_KERNEL_GENERIC = 1,
@@ -234,7 +238,7 @@ fsi_status fsi_plan_destroy(fsi_plan_t plan);
 fsi_status fsi_output_masks(fsi_plan_t plan, uint32_t* host_masks);
 
 /* Schedule actually chosen, for reporting: tile bits b, the workgroup size
- * of the plan's tile kernel (256 on the register-phase kernel, 512 on the
+ * of the plan's tile kernel (256 on the register-phase kernels, 512 on the
  * generic one), algorithm, precision. Any pointer may be NULL. */
 fsi_status fsi_plan_info(fsi_plan_t plan, int* tile_bits, int* block_threads,
                          int* algo, int* precision);
@@ -307,10 +311,12 @@ fsi_status fsi_apply_batched_noalloc(fsi_batch_plan_t plan,
  * fused algorithm launches, in this order and each only if the plan has
  * such work: the register-phase tile kernel once (in-tile Moebius + counter
  * sweep + final weights + cross-tile sums per work item; one launch over
- * the items of every order l present), the generic tile kernel, the generic
+ * the items of every order l present), the tile kernels of orders 5 and 6
+ * (one each), the generic tile kernel, the generic
  * per-output reduction, the wide gather and its final pass (generic
  * instances with at least 2^10 tiles, register-phase instances of several
- * blocks), and the reduction of the register-phase partial sums of
+ * blocks), the reduction of the per-tile results of orders 5 and 6, and the
+ * reduction of the register-phase partial sums of
  * one-block instances of several work items (the tile kernel writes the
  * scores of an instance of one item). A batch whose instances all take the
  * register-phase kernel (l <= 4) and fit one block each (l <= 3, or d <= 20

@@ -199,6 +199,7 @@ struct Sched {
   int chunk_shift = 0;  // register-phase kernel: log2 tiles per item relative to the default
   int mob_group = 0;    // two-pass: most bits of a strided high Moebius pass (0: kMobGroup)
   int algo = 0;         // FSI_ALGO_FUSED or FSI_ALGO_TWO_PASS; 0: the option's
+  bool high = true;     // orders 5 and 6 may take the register phases (not tuned)
 };
 
 // Device scratch of fsi_apply_batched_noalloc; a plan's schedule keeps within
@@ -320,7 +321,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
       }
       // the same phases with the per-tile results in memory: orders 5 and 6,
       // where the kernel is left to the plan
-      const bool want_high = kern == FSI_KERNEL_AUTO && algo == ALGO_FUSED &&
+      const bool want_high = sc.high && kern == FSI_KERNEL_AUTO && algo == ALGO_FUSED &&
                              fast_supported(prec) && lh[i] >= kHighMinL && lh[i] <= kHighMaxL &&
                              (opts.tile_bits == 0 || opts.tile_bits == fb);
       const bool phased = want_fast || want_high;
@@ -728,6 +729,40 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
       lo += G;
     }
     n_passes = std::max(n_passes, np);
+  }
+
+  // orders 5 and 6 keep 26 and 53 KB of results a tile, several times the
+  // generic kernel's on small instances: where they exceed the scratch of
+  // fsi_apply_batched_noalloc and the generic kernel's do not, the plan takes
+  // the generic kernel, and so do calls without allocation
+  if (!P->hclasses.empty() &&
+      (size_t)(ytot + ptot + wptot) * sizeof(double) + 4 * 256 > kScratchBytes) {
+    int64_t gtot = 0;
+    std::vector<int64_t> gsize(P->classes.size(), 0);
+    for (int i = 0; i < n; ++i) {
+      if (!insts[i].high) continue;
+      int64_t& g = gsize[P->cls_of[i]];
+      if (g == 0) {
+        const int b = choose_tile_bits(dh[i], lh[i], prec, opts.tile_bits);
+        ClassHost G;
+        const std::string err = build_class(dh[i], lh[i], b, algo, opts.index, opts.input, &G);
+        if (!err.empty()) { return fail(FSI_ERR_INTERNAL, err); }
+        g = ((int64_t)1 << G.h) * G.Ysize;
+      }
+      gtot += g;
+    }
+    if ((size_t)(gtot + ptot) * sizeof(double) + 4 * 256 <= kScratchBytes) {
+      Sched gs = sc;
+      gs.high = false;
+      fsi_batch_plan_s* G = nullptr;
+      const fsi_status st = build_batch(n, dh, lh, &opts, single, &G, gs);
+      if (st != FSI_OK) return st;
+      if (scratch_need(G) <= kScratchBytes) {
+        *out = G;
+        return FSI_OK;   // the guard frees this one
+      }
+      free_batch(G);
+    }
   }
 
   // ---- device arena ----
@@ -1326,7 +1361,7 @@ fsi_status fsi_output_masks(fsi_plan_t plan, uint32_t* host_masks) {
 fsi_status fsi_plan_info(fsi_plan_t plan, int* tile_bits, int* block_threads, int* algo,
                          int* precision) {
   if (!plan) return fail(FSI_ERR_INVALID_ARG, "null plan");
-  const bool fast = plan->bp->sched.fast_instances > 0;
+  const bool fast = plan->bp->sched.fast_instances > 0 || !plan->bp->hclasses.empty();
   if (tile_bits) *tile_bits = plan->bp->classes[0].b;
   if (block_threads) *block_threads = fast ? kFastThreads : kTileThreads;
   if (algo) *algo = plan->bp->algo;

@@ -82,3 +82,29 @@ def test_batch_beside_the_other_kernels(dtype, tol):
         for r in (a, b, c):
             assert torch.equal(r, first * s)
     bp.close()
+
+
+@pytest.mark.parametrize("n,d,l", [(2700, 9, 5), (1300, 7, 6), (70, 16, 6)])
+def test_scratch_bound(n, d, l):
+    """Batches whose results of the register phases exceed the 64 MiB of the
+    call without allocation: the generic kernel where its results fit, so that
+    the call takes the plan; else the register phases, and the call refuses."""
+    from paper_2601_01903_amd import BatchPlan, FsiError
+    say(f"[case] high order scratch {n} x d={d} l={l}")
+    v = np.concatenate([values(d, 300 + i) for i in range(4)]).astype(np.float32)
+    x = torch.from_numpy(v).to(DEV).repeat(n // 4 + 1)[: n << d].contiguous()
+    bp = BatchPlan([d] * n, [l] * n, dtype="f32")
+    out = bp.apply(x)
+    m = bp.out_offset[1]
+    for i in range(4):
+        ref = oracle.fsi_c(v[i << d:(i + 1) << d].astype(np.float64), d, l, nthreads=16)
+        assert normwise(out[i * m:(i + 1) * m].double().cpu().numpy(), ref) < 1e-6
+        assert torch.equal(out[i * m:(i + 1) * m], out[(i + n // 4 * 4 - 4) * m:][:m])
+    got = torch.full_like(out, float("nan"))
+    if d <= 11:
+        bp.apply_noalloc(x, got)
+        assert torch.equal(got, out)
+    else:
+        with pytest.raises(FsiError, match="scratch"):
+            bp.apply_noalloc(x, got)
+    bp.close()
