@@ -167,9 +167,10 @@ typedef struct {
  * every tile is still read and swept once. The generic LDS kernel covers
  * every (d, l). AUTO picks the register-phase kernel where it applies, and
  * for orders 5 and 6 (tile_bits 0 or 11) the same phases with the per-tile
- * results kept in memory, as the generic kernel keeps them: there only where
- * they leave the plan within the scratch of fsi_apply_batched_noalloc or the
- * generic kernel's would exceed it too. */
+ * results kept in memory, as the generic kernel keeps them: there not
+ * for batches of more instances than the GPU has CUs at d <= 7 (FP64 sweep:
+ * d <= 9), and only where the results leave the plan within the scratch of
+ * fsi_apply_batched_noalloc or the generic kernel's would exceed it too. */
 typedef enum {
   FSI_KERNEL_AUTO = 0,
   FSI_KERNEL_GENERIC = 1,

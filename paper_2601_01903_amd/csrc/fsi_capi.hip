@@ -320,8 +320,13 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
                                              std::to_string(i));
       }
       // the same phases with the per-tile results in memory: orders 5 and 6,
-      // where the kernel is left to the plan
-      const bool want_high = sc.high && kern == FSI_KERNEL_AUTO && algo == ALGO_FUSED &&
+      // where the kernel is left to the plan. The tile of a smaller instance
+      // is mostly padding: past a workgroup per CU the generic kernel is
+      // faster up to d = 9 in FP64 (1200 x d = 8, l = 5: 27 against 36 us; at
+      // d = 10 78 against 39) and d = 7 in FP32 (2500 x l = 5: 29 against 36;
+      // at d = 8 38 against 37)
+      const int small_d = sweep_elem_bytes(prec) == 8 ? 10 : 8;
+      const bool want_high = sc.high && kern == FSI_KERNEL_AUTO && (dh[i] >= small_d || n <= n_cu) && algo == ALGO_FUSED &&
                              fast_supported(prec) && lh[i] >= kHighMinL && lh[i] <= kHighMaxL &&
                              (opts.tile_bits == 0 || opts.tile_bits == fb);
       const bool phased = want_fast || want_high;

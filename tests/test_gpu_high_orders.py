@@ -108,3 +108,23 @@ def test_scratch_bound(n, d, l):
         with pytest.raises(FsiError, match="scratch"):
             bp.apply_noalloc(x, got)
     bp.close()
+
+
+@pytest.mark.parametrize("dtype,tol", [("f64", 1e-12), ("f32", 1e-6)])
+@pytest.mark.parametrize("n", [256, 260])
+def test_many_small_instances(n, dtype, tol):
+    """On both sides of the line (one instance per CU) between the kernels."""
+    from paper_2601_01903_amd import BatchPlan
+    say(f"[case] high order small {n} {dtype}")
+    np_t = np.float64 if dtype == "f64" else np.float32
+    ds = [6, 7, 8, 9, 10] * (n // 5) + [6] * (n % 5)
+    ls = [5 + i % 2 for i in range(n)]
+    game = {d: values(d, 400 + d).astype(np_t) for d in set(ds)}
+    x = torch.from_numpy(np.concatenate([game[d] for d in ds])).to(DEV)
+    refs = {(d, l): oracle.fsi_c(game[d].astype(np.float64), d, l, nthreads=16)
+            for d, l in set(zip(ds, ls))}
+    bp = BatchPlan(ds, ls, dtype=dtype)
+    o = bp.apply(x).double().cpu().numpy()
+    for i, (d, l) in enumerate(zip(ds, ls)):
+        assert normwise(o[bp.out_offset[i]:bp.out_offset[i + 1]], refs[d, l]) < tol, (i, d, l)
+    bp.close()
