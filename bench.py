@@ -37,7 +37,8 @@ def log(*a):
 
 # Files of the dominant kernel's translation unit: the HBM counters stored in
 # profiles/ stay valid while these are unchanged.
-KERNEL_TU = ("fsi_tile11.hip", "fsi_tile11.h", "fsi_kernels.h", "fsi_internal.h")
+KERNEL_TU = ("fsi_tile11.hip", "fsi_sweep_dev.h", "fsi_tile11.h", "fsi_kernels.h",
+             "fsi_internal.h")
 
 
 def kernel_source_hash() -> str:

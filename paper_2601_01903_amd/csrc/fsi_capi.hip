@@ -217,8 +217,8 @@ size_t scratch_need(const fsi_batch_plan_s* P) {
 // instances run on the generic kernel, whose per-tile results feed a gather
 // over M outputs x 2^h tiles; the two-pass algorithm's counter sweep over
 // the Moebius transform does not grow that way with M (32 x d = 20 at
-// l = 8: 7.6 against 29 ms in FP32, 16 against 32 ms in FP64; at l = 6 the
-// two are within 15% either way, at l = 5 the fused one is faster).
+// l = 8: 7.0 against 29 ms in FP32, 16 against 32 ms in FP64; at l = 6, on
+// the register phases, the fused one takes 1.35 against 4.0 ms).
 constexpr int kAutoTwoPassL = 7;
 int auto_algo(int n, const int* lh, const fsi_plan_opts& o) {
   if (o.input != FSI_INPUT_VALUES || o.kernel != FSI_KERNEL_AUTO) return ALGO_FUSED;

@@ -42,6 +42,7 @@
 //   region 3: the final-core weights of the current |U_H| (per-lane reads
 //             of the |S_L| <= 1 pairs)
 //   a zero row read in place of counter rows past a unit's range
+// The forms of l = 3 that share a CU overlay regions 1 and 2 (struct Lds).
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <cstdint>
