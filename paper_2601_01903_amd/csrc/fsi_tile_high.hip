@@ -244,6 +244,14 @@ tile_high_kernel(const FastClassDev* __restrict__ classes, const InstDev* __rest
       SwT X1[1][NA];
 #pragma unroll
       for (int a = 0; a < NA; ++a) X1[0][a] = to_sw<SwT>(y[a]);
+      // d < 11: the coefficients past bit d - 1 are differences of equal
+      // values, zero unless those are infinite
+      const int lowmask = I.lowmask;
+      if (!MOBIN && lowmask < (1 << B) - 1) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+          if ((ta << PA | a) > lowmask) X1[0][a] = SwT(0);
+      }
       EmitS1<SwT, L> e1{S1 + ta};
       rsweep<PA, 0, 1, 0>(X1, e1);
     }

@@ -1,0 +1,34 @@
+"""Numerics at the edges of the kernel of orders 5 and 6: values that are not
+finite."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import say
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("dtype,prec", [("f64", "auto"), ("f32", "auto"), ("f32", "f32")])
+@pytest.mark.parametrize("d,l", [(5, 5), (6, 5), (8, 6), (10, 5), (11, 6)])
+def test_infinite_grand_coalition(d, l, dtype, prec):
+    """v infinite at the full set only: a(full) is the one infinite coefficient,
+    so a score it enters with weight W(s, d) is W times infinity, at sizes that
+    the 11-bit tile pads as well."""
+    from paper_2601_01903_amd import Plan
+    say(f"[case] infinite value d={d} l={l} {dtype} {prec}")
+    v = np.random.default_rng(d).standard_normal(1 << d)
+    v[-1] = np.inf
+    plan = Plan(d, l, dtype=dtype, precision=prec)
+    assert plan.info()["tile_bits"] == 11
+    x = torch.from_numpy(v).to(DEV, torch.float64 if dtype == "f64" else torch.float32)
+    got = plan.apply(x).cpu().numpy()
+    size = np.array([bin(int(m)).count("1") for m in oracle.output_masks(d, l)])
+    for s in range(l + 1):
+        w = oracle.index_weight_exact("fsi", s, d, l)
+        if w != 0:
+            assert (got[size == s] == np.inf * (1 if w > 0 else -1)).all(), s
+    plan.close()
