@@ -305,10 +305,13 @@ tile_high_kernel(const FastClassDev* __restrict__ classes, const InstDev* __rest
 // base + |S_H & U| * stride of its per-tile results (base and stride packed
 // in hword). A workgroup owns 256 / ROWS consecutive outputs; row r adds the
 // tiles U = r mod ROWS in increasing order, then the rows are added in order.
+// Moebius input (inside = ~0, else 0): only the tiles with S_H inside U hold
+// coefficients of supersets; the others' entries are sums of zero weights, NaN
+// where a coefficient is infinite.
 template <typename OutT, int ROWS>
 __global__ void __launch_bounds__(NT)
 high_reduce_kernel(const InstDev* __restrict__ insts, const int2* __restrict__ chunks, int n_chunks,
-                   const double* __restrict__ Yall, OutT* __restrict__ out) {
+                   uint32_t inside, const double* __restrict__ Yall, OutT* __restrict__ out) {
   constexpr int W = NT / ROWS;
   __shared__ double part[ROWS][W];
   const int o = threadIdx.x % W, r = threadIdx.x / W;
@@ -323,8 +326,10 @@ high_reduce_kernel(const InstDev* __restrict__ insts, const int2* __restrict__ c
       const double* Y = Yall + I.yoff + (word & 0xffffu);
       const uint32_t nt = 1u << I.nhigh;
 #pragma unroll 8
-      for (uint32_t U = r; U < nt; U += ROWS)
-        acc += Y[(int64_t)U * I.pstride + __popc(SH & U) * stride];
+      for (uint32_t U = r; U < nt; U += ROWS) {
+        const double y = Y[(int64_t)U * I.pstride + __popc(SH & U) * stride];
+        acc += (SH & ~U & inside) ? 0.0 : y;
+      }
     }
     if constexpr (ROWS > 1) {
       part[r][o] = acc;
@@ -381,15 +386,16 @@ template <typename OutT>
 static hipError_t launch_high_reduce_t(const HighLaunch& f, const double* Y, void* out, hipStream_t st) {
   const int grid = std::min(f.n_chunks, f.n_cu * 16);
   OutT* o = static_cast<OutT*>(out);
+  const uint32_t inside = f.mobius_in ? ~0u : 0u;
   if (f.red_rows == 1)
     hipLaunchKernelGGL((high_reduce_kernel<OutT, 1>), dim3(grid), dim3(NT), 0, st, f.insts, f.chunks,
-                       f.n_chunks, Y, o);
+                       f.n_chunks, inside, Y, o);
   else if (f.red_rows == 4)
     hipLaunchKernelGGL((high_reduce_kernel<OutT, 4>), dim3(grid), dim3(NT), 0, st, f.insts, f.chunks,
-                       f.n_chunks, Y, o);
+                       f.n_chunks, inside, Y, o);
   else
     hipLaunchKernelGGL((high_reduce_kernel<OutT, 16>), dim3(grid), dim3(NT), 0, st, f.insts, f.chunks,
-                       f.n_chunks, Y, o);
+                       f.n_chunks, inside, Y, o);
   return hipGetLastError();
 }
 hipError_t launch_high_reduce(const HighLaunch& f, const double* Y, void* out, hipStream_t st) {

@@ -32,3 +32,19 @@ def test_infinite_grand_coalition(d, l, dtype, prec):
         if w != 0:
             assert (got[size == s] == np.inf * (1 if w > 0 else -1)).all(), s
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("d,l", [(9, 5), (12, 5), (13, 6)])
+def test_infinite_coefficient_below(d, l, dtype):
+    """Moebius input with a(empty set) infinite: the empty set is a superset of
+    itself only, so every other score stays finite."""
+    from paper_2601_01903_amd import Plan
+    say(f"[case] infinite coefficient d={d} l={l} {dtype}")
+    a = np.random.default_rng(d).standard_normal(1 << d)
+    a[0] = np.inf
+    plan = Plan(d, l, dtype=dtype, input="mobius")
+    x = torch.from_numpy(a).to(DEV, torch.float64 if dtype == "f64" else torch.float32)
+    got = plan.apply(x).cpu().numpy()
+    assert np.isinf(got[0]) and np.isfinite(got[1:]).all()
+    plan.close()
