@@ -375,7 +375,7 @@ static hipError_t launch_high_t(const HighLaunch& f, int l, const void* vals, do
 hipError_t launch_high(const HighLaunch& f, int l, const void* vals, double* Y, hipStream_t st) {
   switch (f.prec) {
     case PREC_F32: return launch_high_t<float, float, false>(f, l, vals, Y, st);
-    case PREC_F32_COMP: return launch_high_t<float, TwoF, false>(f, l, vals, Y, st);
+    case PREC_F32_COMP: return launch_high_t<float, TwoFN, false>(f, l, vals, Y, st);
     case PREC_F32_FP64MOB: return launch_high_t<float, double, false>(f, l, vals, Y, st);
     case PREC_F64: return launch_high_t<double, double, true>(f, l, vals, Y, st);
   }
@@ -422,7 +422,7 @@ static hipError_t config_high_t() {
 hipError_t configure_high(int prec) {
   switch (prec) {
     case PREC_F32: return config_high_t<float, float, false>();
-    case PREC_F32_COMP: return config_high_t<float, TwoF, false>();
+    case PREC_F32_COMP: return config_high_t<float, TwoFN, false>();
     case PREC_F32_FP64MOB: return config_high_t<float, double, false>();
     case PREC_F64: return config_high_t<double, double, true>();
   }

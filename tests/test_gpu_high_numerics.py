@@ -1,5 +1,5 @@
 """Numerics at the edges of the kernel of orders 5 and 6: values that are not
-finite."""
+finite, and the two-float butterfly."""
 import numpy as np
 import pytest
 
@@ -47,4 +47,43 @@ def test_infinite_coefficient_below(d, l, dtype):
     x = torch.from_numpy(a).to(DEV, torch.float64 if dtype == "f64" else torch.float32)
     got = plan.apply(x).cpu().numpy()
     assert np.isinf(got[0]) and np.isfinite(got[1:]).all()
+    plan.close()
+
+
+def two_float_moebius(v, order):
+    """Butterfly over the bits in this order in renormalised pairs of FP32."""
+    f = np.float32
+    hi, lo = v.astype(f), np.zeros(v.size, f)
+    for i in order:
+        h, w = hi.reshape(-1, 2, 1 << i), lo.reshape(-1, 2, 1 << i)
+        a, b = h[:, 1].copy(), -h[:, 0]
+        s = a + b
+        t = s - a
+        e = ((a - (s - t)) + (b - t)) + (w[:, 1] - w[:, 0])
+        h[:, 1] = s + e
+        w[:, 1] = e - (h[:, 1] - s)
+    return hi + lo
+
+
+@pytest.mark.parametrize("seed", [0, 1])
+def test_two_float_form_is_renormalised(seed):
+    """Large values that cancel in every coefficient, beside values near their
+    last bit: the low words carry the result. The scores of 2 to 5 players of
+    the Shapley-Taylor index of order 6 are the coefficients themselves, rounded
+    once, in the kernel's order of the bits."""
+    from paper_2601_01903_amd import Plan
+    d, l = 11, 6
+    say(f"[case] two-float form seed={seed}")
+    S = np.arange(1 << d)
+    big = ((S[:, None] >> np.arange(d)) & 1) @ (1 - 2 * (np.arange(d) % 2)) * 2500001.0
+    small = np.random.default_rng(seed).standard_normal(1 << d) * 2.0 ** -5
+    v = np.where(big != 0, big, small).astype(np.float32)
+    plan = Plan(d, l, dtype="f32", precision="f32_compensated", index="stii")
+    assert plan.info()["tile_bits"] == 11
+    got = plan.apply(torch.from_numpy(v).to(DEV)).cpu().numpy()
+    masks = oracle.output_masks(d, l).astype(np.int64)
+    size = np.array([bin(int(m)).count("1") for m in masks])
+    keep = (size >= 2) & (size < l)
+    want = two_float_moebius(v, [8, 9, 10, 4, 5, 6, 7, 0, 1, 2, 3])
+    assert (got[keep] == want[masks[keep]]).all()
     plan.close()
