@@ -229,8 +229,8 @@ fsi_status fsi_plan(int d, int l, fsi_plan_t* out);
 fsi_status fsi_plan_ex(int d, int l, const fsi_plan_opts* opts, fsi_plan_t* out);
 
 /* Frees the plan's host tables, device tables and workspace. NULL is a
- * no-op. Waits first for the stream of the plan's last apply (outside stream
- * capture), not for the whole device. */
+ * no-op. Waits for the work of the plan's device first (hipFree does), on
+ * every stream: the streams of earlier applies need not exist any more. */
 fsi_status fsi_plan_destroy(fsi_plan_t plan);
 
 /* Writes the M output masks of the plan (the coalitions S, |S| <= l, of

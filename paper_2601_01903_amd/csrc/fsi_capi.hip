@@ -111,13 +111,6 @@ struct fsi_batch_plan_s {
   // scratch array instead
   size_t partial_bytes = 0, y_bytes = 0, wide_bytes = 0, work_bytes = 0;
   int64_t ylo_off = -1;            // two-pass FP64: low words at Y + ylo_off
-  // the stream of the last apply outside stream capture: destroying the plan
-  // records `done` there and waits for it, not for the whole device. (An
-  // event recorded after every apply is a packet of its own that the next
-  // kernel waits behind: 2.8 of 8.4 us of a d = 8 apply, back to back.)
-  hipEvent_t done = nullptr;
-  hipStream_t last_stream = nullptr;
-  bool applied = false;
   int tile_bits_reported = 0;
   fsi_schedule sched{};            // the schedule this plan was built with
   // graph cache
@@ -138,32 +131,19 @@ namespace {
 
 void free_batch(fsi_batch_plan_s* p) {
   if (!p) return;
-  if (p->done) {
-    if (p->applied) {
-      // a stream that is being captured, or was destroyed by its owner, takes
-      // no event; freeing the plan's memory then waits for the device
-      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(p->last_stream, &cs) == hipSuccess &&
-          cs == hipStreamCaptureStatusNone &&
-          hipEventRecord(p->done, p->last_stream) == hipSuccess)
-        (void)hipEventSynchronize(p->done);
-      else
-        (void)hipGetLastError();
-    }
-    (void)hipEventDestroy(p->done);
-  }
-  // an apply still replaying on the plan's capture stream, or a launch on a
-  // stream the completion event did not see (one being captured by the
-  // caller): the plan's own stream and the kernels it replayed finish first
-  if (p->cap_stream) (void)hipStreamSynchronize(p->cap_stream);
-  if (p->exec) (void)hipGraphExecDestroy(p->exec);
-  if (p->graph) (void)hipGraphDestroy(p->graph);
-  if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
+  // hipFree waits for the device's work, so the memory goes first: the plan's
+  // last apply has ended then on whatever stream it ran, also one that its
+  // owner has destroyed since, and the graph that it replayed is idle. (An
+  // event recorded after every apply, to wait for, is a packet of its own that
+  // the next kernel waits behind: 2.8 of 8.4 us of a d = 8 apply, back to back.)
   if (p->arena) (void)hipFree(p->arena);
   if (p->Y) (void)hipFree(p->Y);
   if (p->work) (void)hipFree(p->work);
   if (p->partial) (void)hipFree(p->partial);
   if (p->wide_partial) (void)hipFree(p->wide_partial);
+  if (p->exec) (void)hipGraphExecDestroy(p->exec);
+  if (p->graph) (void)hipGraphDestroy(p->graph);
+  if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   delete p;
 }
 
@@ -1019,8 +999,6 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   P->work_bytes = (algo == ALGO_TWO_PASS && !P->in_place)
                       ? (size_t)wtot * std::max(mob_elem_bytes(prec), (size_t)8)
                       : 0;
-  e = hipEventCreateWithFlags(&P->done, hipEventDisableTiming);
-  if (e != hipSuccess) { P->done = nullptr; return fail(FSI_ERR_HIP, "hipEventCreate failed"); }
   guard.p = nullptr;
   *out = P;
   return FSI_OK;
@@ -1295,17 +1273,6 @@ fsi_status scratch_address(int dev, unsigned char** out) {
   return FSI_OK;
 }
 
-// Notes the stream of the plan's work: destroying the plan waits for that
-// stream. Not while the stream is being captured (the caller's graph then
-// owns the ordering).
-void mark_done(fsi_batch_plan_s* P, hipStream_t stream) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
-    P->last_stream = stream;
-    P->applied = true;
-  }
-}
-
 fsi_status check_ptr(const void* p, const char* what) {
   if (!p) return fail(FSI_ERR_INVALID_ARG, std::string(what) + " is NULL");
   if (reinterpret_cast<uintptr_t>(p) & 15)
@@ -1382,7 +1349,6 @@ fsi_status fsi_apply(fsi_plan_t plan, const void* v_dev, void* out_dev, hipStrea
   if ((st = check_ptr(out_dev, "out_dev")) != FSI_OK) return st;
   LaunchArgs a = apply_args(plan->bp, v_dev, out_dev);
   HIP_TRY(launch_apply(a, stream));
-  mark_done(plan->bp, stream);
   return FSI_OK;
   FSI_ABI_CATCH
 }
@@ -1396,7 +1362,6 @@ fsi_status fsi_mobius(fsi_plan_t plan, void* a_dev, hipStream_t stream) {
   a.work = a_dev;
   a.prec = plan->bp->dtype == FSI_DTYPE_F64 ? PREC_F64 : PREC_F32;
   HIP_TRY(launch_mobius(a, stream));
-  mark_done(plan->bp, stream);
   return FSI_OK;
   FSI_ABI_CATCH
 }
@@ -1437,7 +1402,6 @@ fsi_status fsi_apply_batched_nograph(fsi_batch_plan_t plan, const void* values_d
   if ((st = check_ptr(out_dev, "out_dev")) != FSI_OK) return st;
   LaunchArgs a = apply_args(plan, values_dev, out_dev);
   HIP_TRY(launch_apply(a, stream));
-  mark_done(plan, stream);
   return FSI_OK;
   FSI_ABI_CATCH
 }
@@ -1473,7 +1437,6 @@ fsi_status fsi_apply_batched_noalloc(fsi_batch_plan_t plan, const void* values_d
   off += align256(plan->wide_bytes);
   if (plan->work_bytes) a.work = base + off;
   HIP_TRY(launch_apply(a, stream));
-  mark_done(plan, stream);
   return FSI_OK;
   FSI_ABI_CATCH
 }
@@ -1519,7 +1482,6 @@ fsi_status fsi_apply_batched(fsi_batch_plan_t plan, const void* values_dev, void
     plan->g_out = out_dev;
   }
   HIP_TRY(hipGraphLaunch(plan->exec, stream));
-  mark_done(plan, stream);
   return FSI_OK;
   FSI_ABI_CATCH
 }
@@ -1540,7 +1502,6 @@ fsi_status fsi_apply_batched_stage(fsi_batch_plan_t plan, const void* values_dev
     return fail(FSI_ERR_INVALID_ARG, "stage out of range");
   LaunchArgs a = apply_args(plan, values_dev, out_dev);
   HIP_TRY(launch_stage(a, stage, stream));
-  mark_done(plan, stream);
   return FSI_OK;
   FSI_ABI_CATCH
 }

@@ -1,0 +1,79 @@
+"""The library's host side on the CPU, against a stand-in for the HIP runtime
+(tests/host/mock_hip.cpp, loaded ahead of it in a child process): which runtime
+calls an entry point makes, and what it does when one fails."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2601_01903_amd", "_lib", "libfsi_mi355x.so")
+
+PRELUDE = r"""
+import ctypes as C
+mock = C.CDLL({mock!r}, mode=C.RTLD_GLOBAL)   # its symbols come first
+mock.mock_log.restype = C.c_char_p
+mock.mock_fail_malloc.argtypes = [C.c_size_t, C.c_int]
+lib = C.CDLL({lib!r})
+lib.fsi_last_error.restype = C.c_char_p
+vp, i32 = C.c_void_p, C.c_int
+for name in ("fsi_apply", "fsi_apply_batched", "fsi_apply_batched_nograph"):
+    getattr(lib, name).argtypes = [vp] * 4
+lib.fsi_forest_values.argtypes = [vp, vp, i32, vp, i32, vp, vp]
+for name in ("fsi_plan_destroy", "fsi_batch_plan_destroy", "fsi_forest_destroy"):
+    getattr(lib, name).argtypes = [vp]
+def log():
+    return mock.mock_log().decode().splitlines()
+def launches():
+    return [x.split(" ", 2)[1:] for x in log() if x.startswith("launch")]
+def ok(status):
+    assert status == 0, lib.fsi_last_error()
+def stream():
+    s = vp()
+    ok(mock.hipStreamCreateWithFlags(C.byref(s), 1))
+    return s
+def ints(x):
+    return (i32 * len(x))(*x)
+def batch(ds, ls, opts=None):
+    p = vp()
+    ok(lib.fsi_plan_batched(len(ds), ints(ds), ints(ls), opts, C.byref(p)))
+    return p
+buf = C.create_string_buffer((1 << 20) + 64)
+A = (C.addressof(buf) + 63) & ~63
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("mock") / "libmock_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-Wno-unused-result",
+                    os.path.join(ROOT, "tests", "host", "mock_hip.cpp"), "-o", so], check=True)
+
+    def go(code, **env):
+        src = PRELUDE.format(mock=so, lib=LIB) + code + "\nprint('done')\n"
+        r = subprocess.run([sys.executable, "-c", src], capture_output=True, text=True, timeout=120,
+                           env=dict(os.environ, **dict({"FSI_TUNE_CACHE": ""}, **env)))
+        assert r.returncode == 0 and r.stdout.strip().endswith("done"), r.stdout + r.stderr
+        return r.stdout
+    return go
+
+
+def test_destroy_after_the_stream(run):
+    """A plan outlives the streams it ran on: destroying it names none of them,
+    and the memory is freed (which waits for the device) before the graph."""
+    run(r"""
+for call in ("fsi_apply_batched", "fsi_apply_batched_nograph"):
+    p, s = batch([12, 9], [3, 2]), stream()
+    ok(getattr(lib, call)(p, A, A, s))
+    ok(mock.hipStreamDestroy(s))
+    log()
+    ok(lib.fsi_batch_plan_destroy(p))
+    calls = log()
+    assert not [x for x in calls if x.startswith("DEAD_STREAM")], calls
+    names = [x.split()[0] for x in calls]
+    if call == "fsi_apply_batched":
+        assert names.index("hipFree") < names.index("hipGraphExecDestroy"), calls
+    assert "hipFree" in names
+""")
