@@ -166,42 +166,59 @@ struct ReachLists {
   const int32_t* cnt;      // null: no lists
 };
 
-// A wave per pair: each lane takes a root-to-leaf path of the tree (64 at a
-// time) and keeps it if no feature fails both the explained point and the
-// background.
+// A wave per pair takes the tree level by level from its root: lane i holds
+// the i-th node that some coalition reaches on the level, with the bits that it
+// takes to get there, and a node whose feature is undecided gives two. A pair
+// with more than kReach of them has no list, and its wave stops: a pair costs
+// its depth in dependent loads, whatever the number of leaves (by root-to-leaf
+// paths, 64 at a time, a call with one depth-14 tree at d = 10 took 811 us; now 23).
 __global__ void __launch_bounds__(kThreads)
 reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
-             const int32_t* __restrict__ tree_path, const int32_t* __restrict__ path_off,
-             const int32_t* __restrict__ steps, const int32_t* __restrict__ path_leaf, int n_trees,
-             int n_nodes, int64_t pairs, Reach* __restrict__ leaf, int32_t* __restrict__ cnt) {
+             const int32_t* __restrict__ roots, int n_trees, int n_nodes, int64_t pairs,
+             Reach* __restrict__ leaf, int32_t* __restrict__ cnt) {
+  struct At { int32_t node; uint32_t in, out; };
+  __shared__ At next[kThreads / 64][2 * kReach];
+  static_assert(kReach < 64, "a lane per node");
   const int lane = threadIdx.x & 63;
+  At* N = next[threadIdx.x >> 6];
   const int64_t wave0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
   for (int64_t g = wave0; g < pairs; g += (int64_t)gridDim.x * (kThreads / 64)) {
     const int b = (int)(g / n_trees), t = (int)(g - (int64_t)b * n_trees);
     const Node* P = prep + (int64_t)(b / kBgChunk) * n_nodes;
     const int jb = b % kBgChunk;
-    int n = 0;
-    for (int p0 = tree_path[t]; p0 < tree_path[t + 1]; p0 += 64) {
-      const int p = p0 + lane;
-      const bool on = p < tree_path[t + 1];
-      uint32_t seen = 0, aok = ~0u, bok = ~0u;
-      const int s1 = on ? path_off[p + 1] : 0;
-      for (int s = on ? path_off[p] : 0; s < s1; ++s) {
-        const int e = steps[s];
-        const Node w = P[e >> 1];
-        const uint32_t dir = e & 1, bit = 1u << ((uint32_t)w.code & 255u);
-        seen |= bit;
-        if ((((uint32_t)w.code >> 8) & 1u) != dir) aok &= ~bit;
-        if (((w.bits >> jb) & 1u) != dir) bok &= ~bit;
+    At at{roots[t], 0u, 0u};
+    int n = 1;
+    while (n <= kReach) {
+      bool inner = false, both = false;
+      At dn{};                       // the other child, taken without the feature
+      if (lane < n) {
+        const Node w = P[at.node];
+        inner = w.code >= 0;
+        if (inner) {
+          const uint32_t bit = 1u << ((uint32_t)w.code & 255u);
+          const uint32_t dx = ((uint32_t)w.code >> 8) & 1u, db = (w.bits >> jb) & 1u;
+          both = dx != db && !((at.in | at.out) & bit);
+          dn = At{db ? w.right : w.left, at.in, both ? at.out | bit : at.out};
+          if (both) at.in |= bit;
+          at.node = ((at.out & bit) ? db : dx) ? w.right : w.left;
+        }
       }
-      const uint32_t in = seen & ~bok;
-      const bool ok = on && !(in & ~aok);
-      const uint64_t m = __ballot(ok);
-      const int at = n + __popcll(m & ((1ull << lane) - 1ull));
-      if (ok && at < kReach)
-        leaf[(int64_t)at * pairs + g] = Reach{in, seen & bok & ~aok, value[path_leaf[p]]};
+      if (!__ballot(inner)) break;   // all leaves
+      const uint64_t m = __ballot(both);
+      const int k = lane + __popcll(m & ((1ull << lane) - 1ull));
+      if (lane < n) {
+        N[k] = at;
+        if (both) N[k + 1] = dn;
+      }
+      // the wave reads what its own lanes wrote
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       n += __popcll(m);
+      if (lane < min(n, 2 * kReach)) at = N[lane];
+      __builtin_amdgcn_wave_barrier();
     }
+    if (n <= kReach && lane < n) leaf[(int64_t)lane * pairs + g] = Reach{at.in, at.out, value[at.node]};
     if (lane == 0) cnt[g] = n;
   }
 }
@@ -744,7 +761,6 @@ struct fsi_forest_s {
   int32_t* path_off = nullptr;
   int32_t* steps = nullptr;        // node << 1 | went right
   int32_t* path_leaf = nullptr;
-  int32_t* tree_path = nullptr;    // first path of each tree, n_trees + 1
   Reach* reach = nullptr;          // leaf lists of a walk call (null: not kept)
   int32_t* reach_cnt = nullptr;
 };
@@ -760,7 +776,7 @@ void free_forest(fsi_forest_s* F) {
   if (!F) return;
   for (void* p : {(void*)F->feature, (void*)F->left, (void*)F->right, (void*)F->roots,
                   (void*)F->threshold, (void*)F->value, (void*)F->prep,
-                  (void*)F->path_off, (void*)F->steps, (void*)F->path_leaf, (void*)F->tree_path,
+                  (void*)F->path_off, (void*)F->steps, (void*)F->path_leaf,
                   (void*)F->reach, (void*)F->reach_cnt})
     if (p) (void)hipFree(p);
   delete F;
@@ -806,17 +822,14 @@ int forest_depth(int n_nodes, const int32_t* feature, const int32_t* left,
 // routes counts once per path). Returns false if the paths exceed the caps.
 bool enumerate_paths(const int32_t* feature, const int32_t* left, const int32_t* right,
                      const int32_t* roots, int n_trees, std::vector<int32_t>* off,
-                     std::vector<int32_t>* steps, std::vector<int32_t>* leaf,
-                     std::vector<int32_t>* tree) {
+                     std::vector<int32_t>* steps, std::vector<int32_t>* leaf) {
   off->assign(1, 0);
-  tree->clear();
   steps->clear();
   leaf->clear();
   std::vector<int32_t> path;
   // explicit DFS: (node, next child to visit: 0 left, 1 right, 2 done)
   std::vector<std::pair<int, int>> st;
   for (int k = 0; k < n_trees; ++k) {
-    tree->push_back((int32_t)leaf->size());
     st.assign(1, {roots[k], 0});
     path.clear();
     while (!st.empty()) {
@@ -842,7 +855,6 @@ bool enumerate_paths(const int32_t* feature, const int32_t* left, const int32_t*
       st.push_back({dir ? right[node] : left[node], 0});
     }
   }
-  tree->push_back((int32_t)leaf->size());
   return true;
 }
 
@@ -912,8 +924,8 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
     e = hipMalloc((void**)&F->prep, chunks * (size_t)n_nodes * sizeof(Node));
   }
   if (e == hipSuccess) {
-    std::vector<int32_t> poff, psteps, pleaf, ptree;
-    if (enumerate_paths(feat.data(), left, right, roots, n_trees, &poff, &psteps, &pleaf, &ptree)) {
+    std::vector<int32_t> poff, psteps, pleaf;
+    if (enumerate_paths(feat.data(), left, right, roots, n_trees, &poff, &psteps, &pleaf)) {
       F->n_paths = (int)pleaf.size();
       for (size_t p = 0; p + 1 < poff.size(); ++p)
         F->max_path = std::max(F->max_path, poff[p + 1] - poff[p]);
@@ -925,12 +937,11 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
       e = upload(&F->path_off, poff.data(), poff.size());
       if (e == hipSuccess) e = upload(&F->steps, psteps.data(), std::max<size_t>(psteps.size(), 1));
       if (e == hipSuccess) e = upload(&F->path_leaf, pleaf.data(), pleaf.size());
-      if (e == hipSuccess) e = upload(&F->tree_path, ptree.data(), ptree.size());
-      const size_t pairs = (size_t)max_bg * (size_t)n_trees;
-      if (e == hipSuccess && pairs * kReach * sizeof(Reach) <= kReachBytes) {
-        e = hipMalloc((void**)&F->reach, pairs * kReach * sizeof(Reach));
-        if (e == hipSuccess) e = hipMalloc((void**)&F->reach_cnt, pairs * sizeof(int32_t));
-      }
+    }
+    const size_t pairs = (size_t)max_bg * (size_t)n_trees;
+    if (e == hipSuccess && pairs * kReach * sizeof(Reach) <= kReachBytes) {
+      e = hipMalloc((void**)&F->reach, pairs * kReach * sizeof(Reach));
+      if (e == hipSuccess) e = hipMalloc((void**)&F->reach_cnt, pairs * sizeof(int32_t));
     }
   }
   if (e != hipSuccess) {
@@ -970,9 +981,8 @@ fsi_status fsi_forest_values(fsi_forest_t F, const double* x_dev, int n_bg, cons
   if (F->reach) {
     const int64_t pairs = (int64_t)n_bg * F->n_trees;
     const int grid = (int)std::min<int64_t>((pairs + kThreads / 64 - 1) / (kThreads / 64), 4096);
-    reach_kernel<<<grid, kThreads, 0, stream>>>(F->prep, F->value, F->tree_path, F->path_off, F->steps,
-                                                F->path_leaf, F->n_trees, F->n_nodes, pairs, F->reach,
-                                                F->reach_cnt);
+    reach_kernel<<<grid, kThreads, 0, stream>>>(F->prep, F->value, F->roots, F->n_trees, F->n_nodes,
+                                                pairs, F->reach, F->reach_cnt);
     reach = ReachLists{F->reach, F->reach_cnt};
   }
   if (dtype == FSI_DTYPE_F64)
