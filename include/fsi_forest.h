@@ -41,9 +41,10 @@ typedef struct fsi_forest_s* fsi_forest_t;
  *  nodes on any root-to-leaf path.
  * Violations return FSI_ERR_INVALID_ARG before any device work; no gfx950
  * device gives FSI_ERR_UNSUPPORTED. The forest owns device copies of the
- * arrays and a workspace of ceil(max_bg / 32) * n_nodes * 16 bytes, and one of
- * max_bg * n_trees * 388 bytes where that is at most 64 MiB (the leaves each
- * tree and background can reach, listed once per fsi_forest_values call).
+ * arrays and a workspace of ceil(max_bg / 32) * n_nodes * 16 bytes, and one for
+ * the leaves that each tree and background can reach, listed once per
+ * fsi_forest_values call: max_bg * n_trees * (16 r + 4) bytes, r = 64 or as many
+ * as 64 MiB hold, none below r = 24.
  * *out receives the handle (NULL on failure). */
 fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nodes,
                              const int32_t* feature, const double* threshold,

@@ -22,6 +22,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/fsi_forest.h"
@@ -47,7 +48,8 @@ __global__ void __launch_bounds__(kThreads)
 prep_kernel(const int32_t* __restrict__ feature, const double* __restrict__ threshold,
             const int32_t* __restrict__ left, const int32_t* __restrict__ right,
             int n_nodes, int d, const double* __restrict__ x, const double* __restrict__ bg,
-            int n_bg, Node* __restrict__ out) {
+            int n_bg, Node* __restrict__ out, int32_t* __restrict__ over) {
+  if (over && blockIdx.x == 0 && threadIdx.x == 0) *over = 0;   // counted by reach_kernel
   const int n_chunks = (n_bg + kBgChunk - 1) / kBgChunk;
   const int64_t total = (int64_t)n_chunks * n_nodes;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total;
@@ -153,34 +155,47 @@ __device__ __forceinline__ int list_leaves(const Node* __restrict__ P, const dou
 }
 
 // Leaves of a pair reachable by any coalition at all, over the d bits: in must
-// be in S, out must not. Entry i of pair g at i * pairs + g, counts in cnt
-// (past kReach: not listed). Made once per call, so a block only picks the
-// ones its shared bits allow instead of walking the tree again.
-constexpr int kReach = 24;
+// be in S, out must not. Entry i of pair g at i * pairs + g, counts in cnt.
+// Made once per call, so a block only picks the ones its shared bits allow
+// instead of walking the tree again. A pair with more of them than there are
+// rows has no list, and its coalitions walk. (Listing such a pair's leaves in
+// every block instead, by one thread, is a chain of up to 13 walks that the block
+// waits for: 20 depth-12 trees at d = 20, x and background apart everywhere:
+// 337 us, 178 by plain walks.)
+constexpr int kReachMax = 64, kReachMin = 24;   // rows, as the workspace allows
+constexpr int kListMax = 12;     // leaves of a block's list
 struct alignas(16) Reach {
   uint32_t in, out;
   double value;
 };
 struct ReachLists {
   const Reach* leaf;
-  const int32_t* cnt;      // null: no lists
+  const int32_t* cnt;      // null: no lists (each block makes its own)
+  const int32_t* over;     // lists overflow in about over / kSamples pairs of a block
+  int rows;
 };
 
 // A wave per pair takes the tree level by level from its root: lane i holds
 // the i-th node that some coalition reaches on the level, with the bits that it
-// takes to get there, and a node whose feature is undecided gives two. A pair
-// with more than kReach of them has no list, and its wave stops: a pair costs
-// its depth in dependent loads, whatever the number of leaves (by root-to-leaf
-// paths, 64 at a time, a call with one depth-14 tree at d = 10 took 811 us; now 23).
+// takes to get there, and a node whose feature is undecided gives two. Past 64
+// of them the wave stops: a pair costs its depth in dependent loads, whatever
+// the number of leaves (by root-to-leaf paths, 64 at a time, a call with one
+// depth-14 tree at d = 10 took 811 us; now 23).
+//
+// What the lists of the blocks (m low bits) will hold is counted for kSamples
+// settings of their shared bits. Nodes above the leaves still multiply (by about
+// 1.5 a level at m = d / 2), so there a third of a list counts as too many.
+constexpr int kSamples = 4;
 __global__ void __launch_bounds__(kThreads)
 reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
-             const int32_t* __restrict__ roots, int n_trees, int n_nodes, int64_t pairs,
-             Reach* __restrict__ leaf, int32_t* __restrict__ cnt) {
+             const int32_t* __restrict__ roots, int n_trees, int n_nodes, int64_t pairs, int m,
+             int rows, Reach* __restrict__ leaf, int32_t* __restrict__ cnt, int32_t* __restrict__ over) {
   struct At { int32_t node; uint32_t in, out; };
-  __shared__ At next[kThreads / 64][2 * kReach];
-  static_assert(kReach < 64, "a lane per node");
+  __shared__ At next[kThreads / 64][128];
   const int lane = threadIdx.x & 63;
+  const uint32_t high = ~0u << m;
   At* N = next[threadIdx.x >> 6];
+  int32_t n_over = 0;
   const int64_t wave0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
   for (int64_t g = wave0; g < pairs; g += (int64_t)gridDim.x * (kThreads / 64)) {
     const int b = (int)(g / n_trees), t = (int)(g - (int64_t)b * n_trees);
@@ -188,7 +203,7 @@ reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
     const int jb = b % kBgChunk;
     At at{roots[t], 0u, 0u};
     int n = 1;
-    while (n <= kReach) {
+    while (n <= 64) {
       bool inner = false, both = false;
       At dn{};                       // the other child, taken without the feature
       if (lane < n) {
@@ -204,8 +219,8 @@ reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
         }
       }
       if (!__ballot(inner)) break;   // all leaves
-      const uint64_t m = __ballot(both);
-      const int k = lane + __popcll(m & ((1ull << lane) - 1ull));
+      const uint64_t two = __ballot(both);
+      const int k = lane + __popcll(two & ((1ull << lane) - 1ull));
       if (lane < n) {
         N[k] = at;
         if (both) N[k + 1] = dn;
@@ -214,13 +229,27 @@ reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      n += __popcll(m);
-      if (lane < min(n, 2 * kReach)) at = N[lane];
+      n += __popcll(two);
+      if (lane < n) at = N[lane];
       __builtin_amdgcn_wave_barrier();
     }
-    if (n <= kReach && lane < n) leaf[(int64_t)lane * pairs + g] = Reach{at.in, at.out, value[at.node]};
+    const bool rest = lane + 64 < n;           // nodes past the wave's lanes
+    const At at2 = rest ? N[lane + 64] : At{};
+    int overs = 0;
+    uint32_t s = (uint32_t)g * 0x9e3779b9u;
+#pragma unroll
+    for (int k = 0; k < kSamples; ++k) {
+      s = (s ^ (s >> 15)) * 0x85ebca6bu + 0x6a09e667u;
+      const uint32_t S = s ^ (s >> 13);
+      auto in_block = [&](const At& a) { return !(((a.in & ~S) | (a.out & S)) & high); };
+      const int hit = __popcll(__ballot(lane < n && in_block(at))) + __popcll(__ballot(rest && in_block(at2)));
+      overs += hit > (n <= 64 ? kListMax : kListMax / 3);
+    }
+    n_over += overs;
+    if (n <= rows && lane < n) leaf[(int64_t)lane * pairs + g] = Reach{at.in, at.out, value[at.node]};
     if (lane == 0) cnt[g] = n;
   }
+  if (lane == 0 && n_over) atomicAdd(over, n_over);
 }
 
 // One chunk: pairs [g0, g0 + np) of the (background, tree) sequence.
@@ -236,8 +265,8 @@ __device__ __forceinline__ void build_lists(const Node* __restrict__ prep, const
   const int b = (int)(g / n_trees);
   const int root = roots[(int)(g - (int64_t)b * n_trees)];
   uint32_t* row = L.need() + p * LeafLists<NP, NK>::kNeedRow;
-  const int all = reach.cnt ? reach.cnt[g] : kReach + 1;
-  if (all <= kReach) {
+  const int all = reach.cnt ? reach.cnt[g] : 0;
+  if (0 < all && all <= reach.rows) {
     double* vrow = L.val + p * LeafLists<NP, NK>::kValRow;
     const uint32_t low = (1u << m) - 1u;
     int n = 0;
@@ -259,21 +288,36 @@ __device__ __forceinline__ void build_lists(const Node* __restrict__ prep, const
     row[NK + 1] = (uint32_t)root;
     return;
   }
+  if (all > 0) {                 // walk
+    row[NK] = NK + 1;
+    row[NK + 1] = (uint32_t)root;
+    return;
+  }
   row[NK] = (uint32_t)list_leaves<NK>(prep + (int64_t)(b / kBgChunk) * n_nodes, value, root,
                                       b % kBgChunk, m, shared_bits, row,
                                       L.val + p * LeafLists<NP, NK>::kValRow);
   row[NK + 1] = (uint32_t)root;
 }
 
-// Plain walk of one coalition (pairs with more leaves than a list holds).
-__device__ __forceinline__ int walk_one(const Node* __restrict__ P, int root, int jb, uint32_t S) {
-  int node = root;
-  for (;;) {
-    const Node w = P[node];
-    if (w.code < 0) return node;
-    const uint32_t f = (uint32_t)w.code & 255u;
-    const uint32_t go = ((S >> f) & 1u) ? ((uint32_t)w.code >> 8) & 1u : (w.bits >> jb) & 1u;
-    node = go ? w.right : w.left;
+// Plain walks (pairs with more leaves than a list holds): K of them a thread, so
+// that their dependent loads overlap; at: the roots, then the leaves.
+template <int K>
+__device__ __forceinline__ void walk(const Node* const (&P)[K], const int (&jb)[K], const uint32_t (&S)[K],
+                                     int (&at)[K]) {
+  bool inner = true;
+  while (__any(inner)) {
+    Node w[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) w[j] = P[j][at[j]];
+    inner = false;
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+      if (w[j].code >= 0) {
+        const uint32_t f = (uint32_t)w[j].code & 255u;
+        const uint32_t go = ((S[j] >> f) & 1u) ? ((uint32_t)w[j].code >> 8) & 1u : (w[j].bits >> jb[j]) & 1u;
+        at[j] = go ? w[j].right : w[j].left;
+        inner = true;
+      }
   }
 }
 
@@ -309,14 +353,17 @@ __device__ __forceinline__ void match(LeafLists<NP, NK>& L, const LaneLists& ll,
   }
 }
 
-// Every thread owns KP coalitions, base + tid + j * kThreads.
-constexpr int kWideNK = 12;
+// Every thread owns KP coalitions, base + tid + j * kThreads. Pairs without a
+// list are walked, eight walks a thread at once where they follow each other
+// (d = 20, x and background apart everywhere: 20 depth-12 trees 614 us one walk at
+// a time and listed first, now 172, plain walks 178; 50 depth-10 trees 585, now
+// 340, 340).
 template <typename OutT, int KP>
 __global__ void __launch_bounds__(kThreads)
 walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
                  const int32_t* __restrict__ roots, int n_trees, int n_nodes, ReachLists reach, int n_bg,
                  int d, int m, OutT* __restrict__ v) {
-  constexpr int NP = kThreads, NK = kWideNK;
+  constexpr int NP = kThreads, NK = kListMax;
   __shared__ LeafLists<NP, NK> L;
   const uint32_t base = (uint32_t)blockIdx.x * (kThreads * KP);
   const int lane = threadIdx.x & 63;
@@ -341,12 +388,38 @@ walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value
         const int p = p0 + q;
         const int n = __builtin_amdgcn_readlane((int)ll.cnt, q);
         if (n > NK) {
-          const int b = (int)((g0 + p) / n_trees);
-          const int root = (int)L.need()[p * LeafLists<NP, NK>::kNeedRow + NK + 1];
-          const Node* P = prep + (int64_t)(b / kBgChunk) * n_nodes;
+          // where 8 / KP pairs in a row have no list, eight walks in flight
+          auto walk_pairs = [&](auto rc) {
+            constexpr int R = decltype(rc)::value;
+            const Node* P[R * KP];
+            int jb[R * KP], at[R * KP];
+            uint32_t S[R * KP];
 #pragma unroll
-          for (int j = 0; j < KP; ++j)
-            acc[j] += value[walk_one(P, root, b % kBgChunk, base | (nx[j] >> 16))];
+            for (int r = 0; r < R; ++r) {
+              const int b = (int)((g0 + p + r) / n_trees);
+              const int root = (int)L.need()[(p + r) * LeafLists<NP, NK>::kNeedRow + NK + 1];
+#pragma unroll
+              for (int j = 0; j < KP; ++j) {
+                P[r * KP + j] = prep + (int64_t)(b / kBgChunk) * n_nodes;
+                jb[r * KP + j] = b % kBgChunk;
+                at[r * KP + j] = root;
+                S[r * KP + j] = base | (nx[j] >> 16);
+              }
+            }
+            walk<R * KP>(P, jb, S, at);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+              for (int j = 0; j < KP; ++j) acc[j] += value[at[r * KP + j]];
+          };
+          constexpr int R = 8 / KP;
+          const uint64_t run = __ballot(lane < nq && ll.cnt > (uint32_t)NK) >> q;
+          if (R > 1 && (run & ((1u << R) - 1u)) == (1u << R) - 1u) {
+            walk_pairs(std::integral_constant<int, R>{});
+            q += R - 1;
+          } else {
+            walk_pairs(std::integral_constant<int, 1>{});
+          }
         } else {
           const double* row = L.val + p * LeafLists<NP, NK>::kValRow;
           if (n == 1) {   // the whole block takes one leaf
@@ -381,17 +454,23 @@ walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value
 // listing wave only (the roles go by wave number, SIMD = wave % 4), and the
 // matching waves the other three. 50 trees, d = 14, 100 backgrounds: 185 us
 // with the three parts in turns, 142 with a matching wave beside the adding
-// one, now 114.
-constexpr int kNarrowNK = 12;
+// one, now 114. Where many pairs have no list, the waves walk instead (see
+// kWalkShare; 50 depth-12 trees, two backgrounds, d = 16, x and background apart
+// everywhere: 1240 us by the adding wave, 433 by a kernel of plain walks, now 107).
 constexpr int kNarrowPairs = 256;
 constexpr int kNarrowThreads = 768;
 constexpr int kAddWave = 4;        // waves 0-3 list, 8 idles, the other six match
+// A pair without a list is walked by the adding wave alone, 4 us each; past one in
+// kWalkShare of them every wave walks, listed pairs too (1000 depth-3 trees and n
+// of depth 9 that overflow, two backgrounds, d = 14: 92 us at n = 5, 222 at 20;
+// with every wave walking 167 at 30, 312 without that).
+constexpr int kWalkShare = 50;
 template <typename OutT>
 __global__ void __launch_bounds__(kNarrowThreads)
 walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
                    const int32_t* __restrict__ roots, int n_trees, int n_nodes, ReachLists reach, int n_bg,
                    int d, OutT* __restrict__ v) {
-  constexpr int NP = kNarrowPairs, NK = kNarrowNK;
+  constexpr int NP = kNarrowPairs, NK = kListMax;
   constexpr int VR = LeafLists<NP, NK>::kValRow;
   __shared__ LeafLists<NP, NK> lists[3];
   // byte i: 8 x leaf index of pair 16 r + i (255: walk)
@@ -405,8 +484,46 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
   const uint32_t nx[1] = {(~low & 0xffffu) | (low << 16)};
   double acc = 0.0;
   const int64_t total = (int64_t)n_bg * n_trees;
-  const int64_t chunks = (total + NP - 1) / NP;
-  for (int64_t it = 0; it < chunks + 2; ++it) {
+  const bool walks = reach.over && (int64_t)*reach.over * kWalkShare > total * kSamples;
+  const int64_t chunks = walks ? 0 : (total + NP - 1) / NP;
+  if (walks) {
+    // every wave but the adding one walks 8 pairs at a time into LDS, while
+    // that one adds the pairs before
+    constexpr int W = kNarrowThreads / 64 - 1, PP = 8 * W;
+    static_assert(sizeof(double) * 2 * PP * 64 <= sizeof(lists), "leaf outputs over the lists");
+    double* out2 = reinterpret_cast<double*>(lists);
+    const int64_t steps = (total + PP - 1) / PP;
+    for (int64_t it = 0; it <= steps; ++it) {
+      const int64_t g0 = it * PP + 8 * (wave - (wave > kAddWave));
+      if (wave == kAddWave) {
+        const int np = (int)min((int64_t)PP, total - (it - 1) * PP);
+        const double* x = out2 + ((it - 1) & 1) * PP * 64 + lane;
+        if (it > 0) {
+#pragma unroll 8
+          for (int p = 0; p < np; ++p) acc += x[p * 64];
+        }
+      } else if (g0 < total) {
+        const Node* P[8];
+        int jb[8], at[8];
+        uint32_t S[8];
+        int b = (int)(g0 / n_trees), t = (int)(g0 - (int64_t)b * n_trees);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          P[q] = prep + (int64_t)(b / kBgChunk) * n_nodes;
+          jb[q] = b % kBgChunk;
+          at[q] = roots[t];
+          S[q] = base | low;
+          if (g0 + q + 1 < total && ++t == n_trees) { t = 0; ++b; }   // past the end: the last pair again
+        }
+        walk<8>(P, jb, S, at);
+        double* x = out2 + (it & 1) * PP * 64 + (int)(g0 - it * PP) * 64 + lane;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q * 64] = value[at[q]];
+      }
+      __syncthreads();
+    }
+  }
+  for (int64_t it = 0; it < chunks + 2 && !walks; ++it) {
     if (wave < NP / 64) {
       const int64_t g0 = it * NP;
       if (it < chunks)
@@ -444,8 +561,8 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
       const uint4 (*pick)[64] = picks[c & 1];
       // every LDS read of 16 pairs in flight while the 16 before are added
       // (read by read, one pair waited for the one before: 400 us)
-      const bool plain = __ballot(lane < NP / 16 && lane * 16 < np && unlisted[c & 1][lane & (NP / 16 - 1)]) == 0;
-      const int full = plain ? np / 16 : 0;   // groups of 16 with a list for every pair
+      const int full = np / 16;              // whole groups of 16 pairs
+      const uint32_t bad = (uint32_t)__ballot(lane < full && unlisted[c & 1][lane & (NP / 16 - 1)]);
       double x[2][16];
       auto fetch = [&](int g, double (&y)[16]) {
         const uint4 u = pick[g][lane];
@@ -455,28 +572,38 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
         for (int i = 0; i < 16; ++i)
           y[i] = *reinterpret_cast<const double*>(row + ((w[i >> 2] >> (8 * (i & 3))) & 255u) + i * VR * 8);
       };
-      if (full > 0) fetch(0, x[0]);
-      for (int g = 0; g < full; g += 2) {
-        if (g + 1 < full) fetch(g + 1, x[1]);
+      // the groups in runs that have a list for every pair, and pair by pair
+      // those that have not
+      for (int g = 0; g * 16 < np;) {
+        const int end = g >= full ? g : min(full, g + __builtin_ctz((bad >> g) | 0x10000u));
+        if (g < end) fetch(g, x[0]);
+        for (; g < end; g += 2) {
+          if (g + 1 < end) fetch(g + 1, x[1]);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc += x[0][i];
-        if (g + 1 >= full) break;
-        if (g + 2 < full) fetch(g + 2, x[0]);
+          for (int i = 0; i < 16; ++i) acc += x[0][i];
+          if (g + 1 >= end) break;
+          if (g + 2 < end) fetch(g + 2, x[0]);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc += x[1][i];
-      }
-      for (int p = full * 16; p < np; ++p) {
-        const uint4 u = pick[p >> 4][lane];
-        const uint32_t w = (p & 8) ? ((p & 4) ? u.w : u.z) : ((p & 4) ? u.y : u.x);
-        const uint32_t o = (w >> (8 * (p & 3))) & 255u;
-        if (o != 255u) {
-          acc += L.val[p * VR + (o >> 3)];
-        } else {   // the pair has no list (uniform)
-          const int b = (int)((g0 + p) / n_trees);
-          const int root = (int)L.need()[p * LeafLists<NP, NK>::kNeedRow + NK + 1];
-          acc += value[walk_one(prep + (int64_t)(b / kBgChunk) * n_nodes, root, b % kBgChunk,
-                                base | low)];
+          for (int i = 0; i < 16; ++i) acc += x[1][i];
         }
+        g = end;
+        for (int p = g * 16; p < min(np, g * 16 + 16); ++p) {
+          const uint4 u = pick[p >> 4][lane];
+          const uint32_t w = (p & 8) ? ((p & 4) ? u.w : u.z) : ((p & 4) ? u.y : u.x);
+          const uint32_t o = (w >> (8 * (p & 3))) & 255u;
+          if (o != 255u) {
+            acc += L.val[p * VR + (o >> 3)];
+          } else {   // the pair has no list (uniform)
+            const int b = (int)((g0 + p) / n_trees);
+            const Node* P[1] = {prep + (int64_t)(b / kBgChunk) * n_nodes};
+            const int jb[1] = {b % kBgChunk};
+            const uint32_t S[1] = {base | low};
+            int at[1] = {(int)L.need()[p * LeafLists<NP, NK>::kNeedRow + NK + 1]};
+            walk<1>(P, jb, S, at);
+            acc += value[at[0]];
+          }
+        }
+        ++g;
       }
     }
     __syncthreads();
@@ -496,6 +623,12 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
 // 831, narrow 844).
 int walk_kp(int d) { return d >= 21 ? 8 : d >= 19 ? 4 : d >= 18 ? 2 : d >= 17 ? 1 : 0; }
 
+// bits of a block's coalitions
+int walk_bits(int d) {
+  const int kp = walk_kp(d);
+  return kp == 0 ? std::min(d, 6) : kp == 8 ? 11 : kp == 4 ? 10 : kp == 2 ? 9 : 8;
+}
+
 template <typename OutT>
 void launch_walk(const Node* prep, const double* value, const int32_t* roots, int n_trees,
                  int n_nodes, const ReachLists& reach, int n_bg, int d, OutT* v, hipStream_t st) {
@@ -506,7 +639,7 @@ void launch_walk(const Node* prep, const double* value, const int32_t* roots, in
                                                               reach, n_bg, d, v);
     return;
   }
-  const int m = kp == 8 ? 11 : kp == 4 ? 10 : kp == 2 ? 9 : 8;
+  const int m = walk_bits(d);
   const int grid = 1 << (d - m);
   switch (kp) {
     case 1: walk_wide_kernel<OutT, 1><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
@@ -762,7 +895,8 @@ struct fsi_forest_s {
   int32_t* steps = nullptr;        // node << 1 | went right
   int32_t* path_leaf = nullptr;
   Reach* reach = nullptr;          // leaf lists of a walk call (null: not kept)
-  int32_t* reach_cnt = nullptr;
+  int reach_rows = 0;
+  int32_t* reach_cnt = nullptr;    // pairs, then the overflow count
 };
 
 namespace {
@@ -939,9 +1073,10 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
       if (e == hipSuccess) e = upload(&F->path_leaf, pleaf.data(), pleaf.size());
     }
     const size_t pairs = (size_t)max_bg * (size_t)n_trees;
-    if (e == hipSuccess && pairs * kReach * sizeof(Reach) <= kReachBytes) {
-      e = hipMalloc((void**)&F->reach, pairs * kReach * sizeof(Reach));
-      if (e == hipSuccess) e = hipMalloc((void**)&F->reach_cnt, pairs * sizeof(int32_t));
+    F->reach_rows = (int)std::min<size_t>(kReachMax, kReachBytes / (pairs * sizeof(Reach)));
+    if (e == hipSuccess && F->reach_rows >= kReachMin) {
+      e = hipMalloc((void**)&F->reach, pairs * F->reach_rows * sizeof(Reach));
+      if (e == hipSuccess) e = hipMalloc((void**)&F->reach_cnt, (pairs + 1) * sizeof(int32_t));
     }
   }
   if (e != hipSuccess) {
@@ -975,15 +1110,16 @@ fsi_status fsi_forest_values(fsi_forest_t F, const double* x_dev, int n_bg, cons
   const int n_chunks = (n_bg + kBgChunk - 1) / kBgChunk;
   const int64_t prep_total = (int64_t)n_chunks * F->n_nodes;
   const int prep_grid = (int)std::min<int64_t>((prep_total + kThreads - 1) / kThreads, 4096);
+  int32_t* over = F->reach ? F->reach_cnt + (int64_t)n_bg * F->n_trees : nullptr;
   prep_kernel<<<prep_grid, kThreads, 0, stream>>>(F->feature, F->threshold, F->left, F->right,
-                                                  F->n_nodes, F->d, x_dev, bg_dev, n_bg, F->prep);
-  ReachLists reach{nullptr, nullptr};
+                                                  F->n_nodes, F->d, x_dev, bg_dev, n_bg, F->prep, over);
+  ReachLists reach{nullptr, nullptr, nullptr, 0};
   if (F->reach) {
     const int64_t pairs = (int64_t)n_bg * F->n_trees;
     const int grid = (int)std::min<int64_t>((pairs + kThreads / 64 - 1) / (kThreads / 64), 4096);
     reach_kernel<<<grid, kThreads, 0, stream>>>(F->prep, F->value, F->roots, F->n_trees, F->n_nodes,
-                                                pairs, F->reach, F->reach_cnt);
-    reach = ReachLists{F->reach, F->reach_cnt};
+                                                pairs, walk_bits(F->d), F->reach_rows, F->reach, F->reach_cnt, over);
+    reach = ReachLists{F->reach, F->reach_cnt, over, F->reach_rows};
   }
   if (dtype == FSI_DTYPE_F64)
     launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, reach, n_bg, F->d, (double*)v_dev, stream);

@@ -61,3 +61,59 @@ def test_shared_nodes(undecided):
     x = np.ones(d) if undecided else rng.uniform(size=d)
     bgs = np.zeros((1, d)) if undecided else rng.uniform(size=(2, d))
     assert np.array_equal(gpu_values(d, forest, x, bgs), oracle.forest_values(d, *forest, x, bgs))
+
+
+def joined(a, b, at):
+    """The trees of b after every at trees of a."""
+    n = a[1].size
+    roots = []
+    take = iter(b[0])
+    for k, r in enumerate(a[0]):
+        roots.append(r)
+        if k % at == at - 1:
+            roots.extend(n + t for t in [next(take, None)] if t is not None)
+    arrays = [np.concatenate([u, v]) for u, v in zip(a[1:], b[1:])]
+    inner = b[1] >= 0
+    for i in (2, 3):                        # children
+        arrays[i][n:] = np.where(inner, b[i + 1] + n, 0)
+    return (np.array(roots, np.int32), *[np.ascontiguousarray(x) for x in arrays])
+
+
+# deep trees without a list among shallow ones that have one: one in 130 and in
+# 40 of them (below and past the share at which every wave walks), in pairs, all
+@pytest.mark.parametrize("d", [5, 9, 14, 16, 17, 18, 19, 21])
+@pytest.mark.parametrize("shallow,deep,at", [(260, 2, 130), (200, 5, 40), (40, 40, 1), (1, 30, 1)])
+def test_trees_without_a_list(d, shallow, deep, at):
+    say(f"[case] overflow d={d} {deep} of {shallow + deep}")
+    rng = np.random.default_rng(9400 + d)
+    forest = joined(full_trees(d, shallow, 3, rng), full_trees(d, deep, 9, rng), at)
+    x, bgs = np.ones(d), np.zeros((2, d))
+    bgs[1] = rng.uniform(size=d)            # a background that decides some nodes
+    got = gpu_values(d, forest, x, bgs, "f64")
+    if d <= 9:
+        assert np.array_equal(got, oracle.forest_values(d, *forest, x, bgs))
+        return
+    for S in np.concatenate([rng.integers(0, 1 << d, size=8), [0, (1 << d) - 1]]):
+        assert got[S] == oracle.forest_value_at(int(S), d, *forest, x, bgs), int(S)
+
+
+# ns per tree, background, level and coalition: plain walks take 0.0055 and
+# 0.0007 at these sizes, the bounds are about twice that
+@pytest.mark.parametrize("d,n_trees,depth,n_bg,bound", [(16, 50, 12, 2, 0.011), (20, 20, 12, 1, 0.0015)])
+def test_cost_where_lists_overflow(d, n_trees, depth, n_bg, bound):
+    forest = full_trees(d, n_trees, depth, np.random.default_rng(5))
+    us = walk_us(d, forest, np.ones(d), np.zeros((n_bg, d)))
+    say(f"[case] overflow cost d={d} depth={depth}: {us:.1f} us")
+    assert us * 1e3 < bound * n_trees * n_bg * depth * 2 ** d
+
+
+def test_blocks_list_where_the_lists_find_no_room():
+    """A forest made for so many backgrounds that it keeps no lists."""
+    d = 12
+    say("[case] forest without lists")
+    rng = np.random.default_rng(43)
+    forest = full_trees(d, 60, 6, rng)
+    x, bgs = rng.uniform(size=d), rng.uniform(size=(3, d))
+    for x, bgs in ((x, bgs), (np.ones(d), np.zeros((2, d)))):
+        got = gpu_values(d, forest, x, bgs, "f64", max_bg=4096)
+        assert np.array_equal(got, oracle.forest_values(d, *forest, x, bgs))
