@@ -300,12 +300,13 @@ __device__ __forceinline__ void build_lists(const Node* __restrict__ prep, const
 }
 
 // Plain walks (pairs with more leaves than a list holds): K of them a thread, so
-// that their dependent loads overlap; at: the roots, then the leaves.
+// that their dependent loads overlap; at: the roots, then the leaves. depth: the
+// forest's, after which every node is a leaf and need not be read.
 template <int K>
 __device__ __forceinline__ void walk(const Node* const (&P)[K], const int (&jb)[K], const uint32_t (&S)[K],
-                                     int (&at)[K]) {
+                                     int depth, int (&at)[K]) {
   bool inner = true;
-  while (__any(inner)) {
+  for (int lv = 0; lv < depth && __any(inner); ++lv) {
     Node w[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) w[j] = P[j][at[j]];
@@ -361,8 +362,8 @@ __device__ __forceinline__ void match(LeafLists<NP, NK>& L, const LaneLists& ll,
 template <typename OutT, int KP>
 __global__ void __launch_bounds__(kThreads)
 walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
-                 const int32_t* __restrict__ roots, int n_trees, int n_nodes, ReachLists reach, int n_bg,
-                 int d, int m, OutT* __restrict__ v) {
+                 const int32_t* __restrict__ roots, int n_trees, int n_nodes, int depth, ReachLists reach,
+                 int n_bg, int d, int m, OutT* __restrict__ v) {
   constexpr int NP = kThreads, NK = kListMax;
   __shared__ LeafLists<NP, NK> L;
   const uint32_t base = (uint32_t)blockIdx.x * (kThreads * KP);
@@ -406,7 +407,7 @@ walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value
                 S[r * KP + j] = base | (nx[j] >> 16);
               }
             }
-            walk<R * KP>(P, jb, S, at);
+            walk<R * KP>(P, jb, S, depth, at);
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -468,8 +469,8 @@ constexpr int kWalkShare = 50;
 template <typename OutT>
 __global__ void __launch_bounds__(kNarrowThreads)
 walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
-                   const int32_t* __restrict__ roots, int n_trees, int n_nodes, ReachLists reach, int n_bg,
-                   int d, OutT* __restrict__ v) {
+                   const int32_t* __restrict__ roots, int n_trees, int n_nodes, int depth, ReachLists reach,
+                   int n_bg, int d, OutT* __restrict__ v) {
   constexpr int NP = kNarrowPairs, NK = kListMax;
   constexpr int VR = LeafLists<NP, NK>::kValRow;
   __shared__ LeafLists<NP, NK> lists[3];
@@ -515,7 +516,7 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
           S[q] = base | low;
           if (g0 + q + 1 < total && ++t == n_trees) { t = 0; ++b; }   // past the end: the last pair again
         }
-        walk<8>(P, jb, S, at);
+        walk<8>(P, jb, S, depth, at);
         double* x = out2 + (it & 1) * PP * 64 + (int)(g0 - it * PP) * 64 + lane;
 #pragma unroll
         for (int q = 0; q < 8; ++q) x[q * 64] = value[at[q]];
@@ -599,7 +600,7 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
             const int jb[1] = {b % kBgChunk};
             const uint32_t S[1] = {base | low};
             int at[1] = {(int)L.need()[p * LeafLists<NP, NK>::kNeedRow + NK + 1]};
-            walk<1>(P, jb, S, at);
+            walk<1>(P, jb, S, depth, at);
             acc += value[at[0]];
           }
         }
@@ -614,39 +615,96 @@ walk_narrow_kernel(const Node* __restrict__ prep, const double* __restrict__ val
   }
 }
 
-// Coalitions per thread of the wide kernel, 0 for the narrow one: eight or four
-// where that still gives every CU four workgroups (8 against 4: 100 depth-6
-// trees at d = 21 70 against 82 us, 200 at d = 20 101 against 90), and the
-// narrow kernel, which
-// takes one workgroup per CU and 64 coalitions, up to four rounds of them (50
-// depth-4 trees, 100 backgrounds: d = 16 wide 818 us, narrow 445; d = 17 wide
-// 831, narrow 844).
-int walk_kp(int d) { return d >= 21 ? 8 : d >= 19 ? 4 : d >= 18 ? 2 : d >= 17 ? 1 : 0; }
+// A few short walks: two coalitions a thread, no lists (whose pass is a launch
+// of its own).
+constexpr int kPlainKP = 2;
+template <typename OutT>
+__global__ void __launch_bounds__(kThreads)
+walk_plain_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
+                  const int32_t* __restrict__ roots, int n_trees, int n_nodes, int depth, int n_bg,
+                  int d, OutT* __restrict__ v) {
+  constexpr int KP = kPlainKP;
+  const uint32_t s0 = blockIdx.x * (kThreads * KP) + threadIdx.x;
+  uint32_t S[KP];
+  double acc[KP];
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    S[j] = (s0 + j * kThreads) & ((1u << d) - 1u);   // past the end: a valid one, not stored
+    acc[j] = 0.0;
+  }
+  for (int b = 0; b < n_bg; ++b)
+    for (int t = 0; t < n_trees; ++t) {
+      const Node* P[KP];
+      int jb[KP], at[KP];
+#pragma unroll
+      for (int j = 0; j < KP; ++j) {
+        P[j] = prep + (int64_t)(b / kBgChunk) * n_nodes;
+        jb[j] = b % kBgChunk;
+        at[j] = roots[t];
+      }
+      walk<KP>(P, jb, S, depth, at);
+#pragma unroll
+      for (int j = 0; j < KP; ++j) acc[j] += value[at[j]];
+    }
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    const uint32_t s = s0 + j * kThreads;
+    if (s < (1u << d)) v[s] = (OutT)(acc[j] / (double)n_bg);
+  }
+}
+
+// Plain walks for up to four pairs or 32 dependent loads in all, and for fewer
+// where the walks fill the machine (plain / with lists, in us: 8 depth-3 trees d = 3
+// to 18 11 to 13 / 13, 16 of them 18 to 24 / 13; 4 depth-6 trees 11 to 14 / 14; 4 of
+// depth 10 with x and background apart everywhere, d = 16, 21 / 25, uniform points
+// 21 / 15; d = 20: 8 depth-3 trees 22 / 13, 2 depth-6 trees 13 / 14 to 24).
+bool walk_plain(int d, int64_t pairs, int depth) {
+  const int64_t loads = pairs * std::max(depth, 1);
+  return d < 20 ? pairs <= 4 || loads <= 32 : loads <= 12 >> std::min(d - 20, 4);
+}
+
+// Coalitions per thread of the wide kernel, 0 for the narrow one: eight from
+// d = 21 on (100 depth-6 trees 70 us against 82 with four; 200 at d = 20 101
+// against 90), four from d = 19, and the narrow kernel, which takes one workgroup per
+// CU and 64 coalitions, up to four rounds of them (50 depth-4 trees, 100
+// backgrounds: d = 16 wide 818 us, narrow 445; d = 17 wide 831, narrow 844). Its
+// pipeline fills and drains in each round, so at two and four rounds (d = 15, 16)
+// it takes some pairs to be worth it (depth 6, d = 16: 16 trees narrow 29 us, wide 14,
+// 128 trees 43 and 34, where no list suffices 88 and 79; 64 such trees of depth
+// 10: 56 and 85. d = 15: 16 trees 20 and 14, 64 trees 23 and 24).
+int walk_kp(int d, int64_t pairs) {
+  if (d >= 21) return 8;
+  if (d >= 19) return 4;
+  if (d >= 18) return 2;
+  return d >= 17 || (d >= 15 && pairs <= (d == 15 ? 16 : 64)) ? 1 : 0;
+}
 
 // bits of a block's coalitions
-int walk_bits(int d) {
-  const int kp = walk_kp(d);
+int walk_bits(int d, int kp) {
   return kp == 0 ? std::min(d, 6) : kp == 8 ? 11 : kp == 4 ? 10 : kp == 2 ? 9 : 8;
 }
 
 template <typename OutT>
 void launch_walk(const Node* prep, const double* value, const int32_t* roots, int n_trees,
-                 int n_nodes, const ReachLists& reach, int n_bg, int d, OutT* v, hipStream_t st) {
-  const int kp = walk_kp(d);
+                 int n_nodes, int depth, const ReachLists& reach, bool plain, int kp, int n_bg, int d,
+                 OutT* v, hipStream_t st) {
+  if (plain) {
+    const int grid = ((1 << d) + kThreads * kPlainKP - 1) / (kThreads * kPlainKP);
+    walk_plain_kernel<OutT><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, depth, n_bg,
+                                                       d, v);
+    return;
+  }
   if (kp == 0) {
     const int grid = d > 6 ? 1 << (d - 6) : 1;
-    walk_narrow_kernel<OutT><<<grid, kNarrowThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes,
+    walk_narrow_kernel<OutT><<<grid, kNarrowThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, depth,
                                                               reach, n_bg, d, v);
     return;
   }
-  const int m = walk_bits(d);
-  const int grid = 1 << (d - m);
-  switch (kp) {
-    case 1: walk_wide_kernel<OutT, 1><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
-    case 2: walk_wide_kernel<OutT, 2><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
-    case 8: walk_wide_kernel<OutT, 8><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
-    default: walk_wide_kernel<OutT, 4><<<grid, kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, reach, n_bg, d, m, v); break;
-  }
+  const int m = walk_bits(d, kp);
+  auto* kernel = kp == 1 ? walk_wide_kernel<OutT, 1> : kp == 2 ? walk_wide_kernel<OutT, 2>
+               : kp == 4 ? walk_wide_kernel<OutT, 4> : walk_wide_kernel<OutT, 8>;
+  kernel<<<1 << (d - m), kThreads, 0, st>>>(prep, value, roots, n_trees, n_nodes, depth, reach, n_bg, d, m,
+                                            v);
 }
 
 // ---- Moebius route ----
@@ -881,7 +939,7 @@ using namespace fsi;
 using namespace fsi::forest;
 
 struct fsi_forest_s {
-  int d = 0, n_trees = 0, n_nodes = 0, max_bg = 0, device = 0;
+  int d = 0, n_trees = 0, n_nodes = 0, max_bg = 0, depth = 0, device = 0;
   int32_t* feature = nullptr;
   int32_t* left = nullptr;
   int32_t* right = nullptr;
@@ -1042,7 +1100,7 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
     fsi_forest_s* f;
     ~Guard() { free_forest(f); }
   } guard{F};
-  F->d = d; F->n_trees = n_trees; F->n_nodes = n_nodes; F->max_bg = max_bg;
+  F->d = d; F->n_trees = n_trees; F->n_nodes = n_nodes; F->max_bg = max_bg; F->depth = depth;
   F->device = dev;
   // leaves keep feature -1 on the device whatever negative value they had
   std::vector<int32_t> feat(feature, feature + n_nodes);
@@ -1110,21 +1168,25 @@ fsi_status fsi_forest_values(fsi_forest_t F, const double* x_dev, int n_bg, cons
   const int n_chunks = (n_bg + kBgChunk - 1) / kBgChunk;
   const int64_t prep_total = (int64_t)n_chunks * F->n_nodes;
   const int prep_grid = (int)std::min<int64_t>((prep_total + kThreads - 1) / kThreads, 4096);
-  int32_t* over = F->reach ? F->reach_cnt + (int64_t)n_bg * F->n_trees : nullptr;
+  const int64_t pairs = (int64_t)n_bg * F->n_trees;
+  const bool plain = walk_plain(F->d, pairs, F->depth);
+  const int kp = walk_kp(F->d, pairs);
+  int32_t* over = F->reach && !plain ? F->reach_cnt + pairs : nullptr;
   prep_kernel<<<prep_grid, kThreads, 0, stream>>>(F->feature, F->threshold, F->left, F->right,
                                                   F->n_nodes, F->d, x_dev, bg_dev, n_bg, F->prep, over);
   ReachLists reach{nullptr, nullptr, nullptr, 0};
-  if (F->reach) {
-    const int64_t pairs = (int64_t)n_bg * F->n_trees;
+  if (F->reach && !plain) {
     const int grid = (int)std::min<int64_t>((pairs + kThreads / 64 - 1) / (kThreads / 64), 4096);
     reach_kernel<<<grid, kThreads, 0, stream>>>(F->prep, F->value, F->roots, F->n_trees, F->n_nodes,
-                                                pairs, walk_bits(F->d), F->reach_rows, F->reach, F->reach_cnt, over);
+                                                pairs, walk_bits(F->d, kp), F->reach_rows, F->reach, F->reach_cnt, over);
     reach = ReachLists{F->reach, F->reach_cnt, over, F->reach_rows};
   }
   if (dtype == FSI_DTYPE_F64)
-    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, reach, n_bg, F->d, (double*)v_dev, stream);
+    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, F->depth, reach, plain, kp, n_bg,
+                F->d, (double*)v_dev, stream);
   else
-    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, reach, n_bg, F->d, (float*)v_dev, stream);
+    launch_walk(F->prep, F->value, F->roots, F->n_trees, F->n_nodes, F->depth, reach, plain, kp, n_bg,
+                F->d, (float*)v_dev, stream);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ffail(FSI_ERR_HIP, std::string("forest launch: ") + hipGetErrorString(e));
   return FSI_OK;

@@ -32,13 +32,14 @@ def walk_us(d, forest, x, bgs):
     return best
 
 
-def test_cost_of_a_deep_tree():
-    """One tree of 2^14 leaves against one of 2^6: the depths differ by 2.3."""
+@pytest.mark.parametrize("n_trees", [1, 6])
+def test_cost_of_a_deep_tree(n_trees):
+    """Trees of 2^14 leaves against trees of 2^6: the depths differ by 2.3."""
     d = 10
     x, bgs = np.ones(d), np.zeros((1, d))
     us = {}
     for depth in (6, 14):
-        forest = full_trees(d, 1, depth, np.random.default_rng(depth))
+        forest = full_trees(d, n_trees, depth, np.random.default_rng(depth))
         assert np.array_equal(gpu_values(d, forest, x, bgs), oracle.forest_values(d, *forest, x, bgs))
         us[depth] = walk_us(d, forest, x, bgs)
         say(f"[case] deep tree d={d} depth={depth}: {us[depth]:.1f} us")
@@ -117,3 +118,34 @@ def test_blocks_list_where_the_lists_find_no_room():
     for x, bgs in ((x, bgs), (np.ones(d), np.zeros((2, d)))):
         got = gpu_values(d, forest, x, bgs, "f64", max_bg=4096)
         assert np.array_equal(got, oracle.forest_values(d, *forest, x, bgs))
+
+
+# both sides of the lines between the kernels: plain walks (up to 32 loads, 12 at
+# d = 20, none past d = 23), and from d = 15 one or 64 coalitions a workgroup's lane
+@pytest.mark.parametrize("d,n_trees,depth", [(1, 4, 2), (9, 32, 1), (9, 33, 1), (10, 4, 11), (10, 5, 11),
+                                             (15, 16, 4), (15, 17, 4), (16, 64, 4), (16, 65, 4),
+                                             (20, 12, 1), (20, 13, 1), (23, 1, 1), (24, 1, 1)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_kernel_lines(d, n_trees, depth, dtype):
+    say(f"[case] walk lines d={d} trees={n_trees} depth={depth} {dtype}")
+    rng = np.random.default_rng(9500 + d)
+    forest = full_trees(d, n_trees, depth, rng)
+    x, bgs = rng.uniform(size=d), rng.uniform(size=(1, d))
+    got = gpu_values(d, forest, x, bgs, dtype)
+    cast = np.float64 if dtype == "f64" else np.float32
+    if d <= 10:
+        assert np.array_equal(got, oracle.forest_values(d, *forest, x, bgs).astype(cast))
+        return
+    for S in np.concatenate([rng.integers(0, 1 << d, size=16), [0, (1 << d) - 1]]):
+        assert got[S] == cast(oracle.forest_value_at(int(S), d, *forest, x, bgs)), int(S)
+
+
+def test_cost_of_few_trees():
+    """Ten depth-3 trees: d = 16 is a quarter of d = 18."""
+    us = {}
+    for d in (16, 18):
+        rng = np.random.default_rng(d)
+        forest = full_trees(d, 10, 3, rng)
+        us[d] = walk_us(d, forest, rng.uniform(size=d), rng.uniform(size=(1, d)))
+        say(f"[case] few trees d={d}: {us[d]:.1f} us")
+    assert us[16] < 1.6 * us[18]
