@@ -736,6 +736,7 @@ fill_kernel(double2* __restrict__ a, int64_t n2) {
 // backgrounds; now the kernel takes 45, half of it the atomics).
 constexpr int kScatterBg = 8;
 constexpr int kScatterGrid = 256;   // workgroups that collect and flush
+constexpr int kScatterFew = 32;     // work items below which the groups shrink
 constexpr int kSmallSets = 1 + kMaxD + kMaxD * (kMaxD - 1) / 2;
 constexpr int kTermLanes = 4;   // the subsets of two members, see the loop
 struct PathTerms {       // a reachable path of one background
@@ -748,7 +749,7 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
                       const int32_t* __restrict__ path_leaf, int n_paths,
                       const int32_t* __restrict__ feature, const double* __restrict__ threshold,
                       const double* __restrict__ value, int d, const double* __restrict__ x,
-                      const double* __restrict__ bg, int n_bg, double* __restrict__ a) {
+                      const double* __restrict__ bg, int n_bg, int per, double* __restrict__ a) {
   __shared__ double small[kSmallSets];
   __shared__ double xs[kMaxD], zs[kScatterBg][kMaxD];
   __shared__ PathTerms list[kThreads * kScatterBg];
@@ -758,14 +759,14 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
   for (int i = threadIdx.x; i < n_small; i += kThreads) small[i] = 0.0;
   if ((int)threadIdx.x < d) xs[threadIdx.x] = x[threadIdx.x];
   const int chunks = (n_paths + kThreads - 1) / kThreads;    // of paths, per group
-  const int groups = (n_bg + kScatterBg - 1) / kScatterBg;
+  const int groups = (n_bg + per - 1) / per;
   const int64_t total = (int64_t)chunks * groups;
   int g_prev = -1;
   for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
     const int g = (int)(it / chunks);
     const int p = (int)(it - (int64_t)g * chunks) * kThreads + (int)threadIdx.x;
-    const int b0 = g * kScatterBg;
-    const int nb = min(kScatterBg, n_bg - b0);
+    const int b0 = g * per;
+    const int nb = min(per, n_bg - b0);
     __syncthreads();             // the previous list is used up
     if (threadIdx.x == 0) n_list = 0;
     if (g != g_prev) {           // uniform in the workgroup
@@ -848,6 +849,16 @@ mobius_scatter_kernel(const int32_t* __restrict__ path_off, const int32_t* __res
     }
     atomicAdd(a + R, small[k]);
   }
+}
+
+// Backgrounds per group: fewer, down to one, where that makes up to kScatterFew
+// work items (10 depth-5 trees, 8 backgrounds, d = 16, x and background apart
+// everywhere: two items 38 us, 16 items 18; lines at 16, 128 and 256 items were no
+// better over 212 forests). More items flush the small sets more often.
+int scatter_bg(int n_bg, int chunks) {
+  int per = kScatterBg;
+  while (per > 1 && (int64_t)chunks * ((n_bg + per - 1) / per) < kScatterFew) per /= 2;
+  return per;
 }
 
 // Subset sums (zeta transform, the inverse of the Moebius butterfly): a pass
@@ -1208,11 +1219,12 @@ fsi_status fsi_forest_mobius(fsi_forest_t F, const double* x_dev, int n_bg, cons
   const int64_t n2 = (int64_t)1 << (F->d - 1);
   fill_kernel<<<(int)std::min<int64_t>((n2 + 4 * kThreads - 1) / (4 * kThreads), 2048), kThreads, 0,
                 stream>>>(reinterpret_cast<double2*>(a_dev), n2);
-  const int64_t work = (int64_t)((n_bg + kScatterBg - 1) / kScatterBg) *
-                       ((F->n_paths + kThreads - 1) / kThreads);
+  const int chunks = (F->n_paths + kThreads - 1) / kThreads;
+  const int per = scatter_bg(n_bg, chunks);
+  const int64_t work = (int64_t)((n_bg + per - 1) / per) * chunks;
   mobius_scatter_kernel<<<(int)std::min<int64_t>(work, kScatterGrid), kThreads, 0, stream>>>(
       F->path_off, F->steps, F->path_leaf, F->n_paths, F->feature, F->threshold, F->value, F->d,
-      x_dev, bg_dev, n_bg, a_dev);
+      x_dev, bg_dev, n_bg, per, a_dev);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ffail(FSI_ERR_HIP, std::string("forest launch: ") + hipGetErrorString(e));
   return FSI_OK;
