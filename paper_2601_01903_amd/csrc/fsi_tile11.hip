@@ -726,10 +726,13 @@ static FastForm fast_form(int prec, int l, int np, int mobius_in) {
 // LDS bytes of a launch: the form's, or more where the grid is smaller than the
 // machine holds, so that no CU takes more workgroups than an even spread gives
 // it (the dispatcher otherwise fills a CU before it goes to the next one: 500 x
-// d = 14, l = 3 in FP32 54 us on 167 CUs, 34 spread over all).
+// d = 14, l = 3 in FP32 54 us on 167 CUs, 34 spread over all). Not for a grid of at
+// most one workgroup per CU: the dispatcher spreads it by itself (single d = 20,
+// l = 4 in FP32 19.3 us with and without), and the launches of other streams find
+// room beside it (two streams of them 17.5 us an apply with, 12.0 without).
 static unsigned spread_lds(const FastForm& form, int grid, int n_cu) {
   const int share = (grid + n_cu - 1) / n_cu;
-  if (share >= form.wgs) return (unsigned)form.lds;
+  if (share == 1 || share >= form.wgs) return (unsigned)form.lds;
   return (unsigned)std::max(form.lds, 160 * 1024 / share - 2048);
 }
 

@@ -69,8 +69,8 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* m, hipStream_t* s
   *g = g_grid; *b = g_block; *m = g_shared; *s = g_stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* fn, dim3 g, dim3, void**, size_t, hipStream_t s) {
-  g_log += "launch " + std::to_string(g.x) + " " + g_kernel[fn] + "\n";
+hipError_t hipLaunchKernel(const void* fn, dim3 g, dim3, void**, size_t lds, hipStream_t s) {
+  g_log += "launch " + std::to_string(g.x) + " " + std::to_string(lds) + " " + g_kernel[fn] + "\n";
   return on_stream("on", s);
 }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }

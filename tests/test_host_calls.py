@@ -25,8 +25,8 @@ for name in ("fsi_plan_destroy", "fsi_batch_plan_destroy", "fsi_forest_destroy")
     getattr(lib, name).argtypes = [vp]
 def log():
     return mock.mock_log().decode().splitlines()
-def launches():
-    return [x.split(" ", 2)[1:] for x in log() if x.startswith("launch")]
+def launches():   # (grid, dynamic LDS bytes, kernel)
+    return [(int(g), int(b), k) for g, b, k in (x.split(" ", 3)[1:] for x in log() if x.startswith("launch"))]
 def ok(status):
     assert status == 0, lib.fsi_last_error()
 def stream():
@@ -76,4 +76,21 @@ for call in ("fsi_apply_batched", "fsi_apply_batched_nograph"):
     if call == "fsi_apply_batched":
         assert names.index("hipFree") < names.index("hipGraphExecDestroy"), calls
     assert "hipFree" in names
+""")
+
+
+def test_small_launches_leave_room(run):
+    """A launch of at most one workgroup per CU asks for its own LDS only, so that
+    another stream's fits beside it on the CU's 160 KB."""
+    run(r"""
+for d, l, n in [(14, 3, 1), (20, 4, 1), (11, 1, 250), (14, 3, 100)]:
+    opts = (i32 * 10)()
+    ok(lib.fsi_default_opts(opts))
+    opts[0] = 1                       # FP32 storage
+    p = batch([d] * n, [l] * n, opts)
+    log()
+    ok(lib.fsi_apply_batched_nograph(p, A, A, None))
+    tile = [x for x in launches() if "tile11" in x[2]]
+    assert len(tile) == 1 and tile[0][0] <= 256 and 2 * tile[0][1] <= 160 * 1024, (d, l, n, tile)
+    ok(lib.fsi_batch_plan_destroy(p))
 """)
