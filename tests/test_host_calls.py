@@ -83,7 +83,7 @@ def test_small_launches_leave_room(run):
     """A launch of at most one workgroup per CU asks for its own LDS only, so that
     another stream's fits beside it on the CU's 160 KB."""
     run(r"""
-for d, l, n in [(14, 3, 1), (20, 4, 1), (11, 1, 250), (14, 3, 100)]:
+for d, l, n in [(14, 3, 1), (20, 4, 1), (11, 1, 250), (14, 3, 30)]:
     opts = (i32 * 10)()
     ok(lib.fsi_default_opts(opts))
     opts[0] = 1                       # FP32 storage
