@@ -185,14 +185,15 @@ typedef struct fsi_batch_plan_s* fsi_batch_plan_t;
  * candidate schedule, times one apply of each on zero-filled scratch
  * buffers of the plan's size (allocated and freed inside the call) on a
  * private stream, and keeps the fastest. Candidates: for the fused
- * algorithm the register-phase kernel at 1/2x, 1x, 2x and 4x the default
- * tiles per work item and the generic kernel at the largest tile that fits
- * LDS and 1 or 2 bits less; for the two-pass algorithm 4, 5 or 6 bits per
- * strided high Moebius pass, with the largest tile or 1 bit less;
+ * algorithm the kernels of AUTO at 1/2x, 1x, 2x and 4x the default tiles per
+ * work item of the register-phase kernel, and the generic kernel at the largest
+ * tile that fits LDS and 1 or 2 bits less; for the two-pass algorithm at most 4, 6
+ * or 8 bits per strided high Moebius pass, with the largest tile or 1 bit less;
  * FSI_ALGO_AUTO takes the candidates of both algorithms when every instance
  * has l > 4, else those of the algorithm it resolves to. The
- * choice is cached per (device architecture and compute-unit count, dtype,
- * precision, algo, kernel, tile_bits, input, multiset of (d, l)) in the
+ * choice is cached per (device architecture and compute-unit count, version of
+ * the schedules, dtype, precision, algo, kernel, tile_bits, input, multiset of
+ * (d, l)) in the
  * process and in a JSON file read by later processes: the path in the
  * environment variable FSI_TUNE_CACHE (empty: no file), by default
  * $HOME/.cache/fsi_mi355x/autotune.json. A plan whose schedule comes from

@@ -1009,12 +1009,18 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
 // schedule, each candidate is timed on zero-filled device buffers of the
 // plan's size (the kernels' work does not depend on the values), and the
 // fastest is kept. Results are cached per (device architecture and compute
-// units, dtype, precision, algo, kernel, tile_bits, input, multiset of
+// units, meaning of a schedule, dtype, precision, algo, kernel, tile_bits, input, multiset of
 // (d, l)): in the process, and in a JSON file that later processes read
 // (the path in FSI_TUNE_CACHE, an empty value for none; by default
 // $HOME/.cache/fsi_mi355x/autotune.json). The file is an optimisation
 // only: a missing, unreadable or unwritable file changes nothing else.
 std::mutex g_tune_mu;
+// What the numbers of a stored schedule mean: part of every key, to be raised
+// when a kernel choice, a default that a shift is relative to or the candidates
+// change, so that entries of another meaning are left alone. (Keys without one:
+// orders 5 and 6 on the generic kernel or in two passes, at 3 to 5 times the time of
+// the present choice, and shifts of other default item sizes.)
+constexpr int kSchedVersion = 2;
 std::map<std::string, Sched>& tune_cache() {
   static std::map<std::string, Sched> m;
   return m;
@@ -1138,7 +1144,7 @@ fsi_status build_tuned(int n, const int* dh, const int* lh, const fsi_plan_opts*
     std::string why;
     // without a gfx950 device the plain build reports why
     if (!device_is_gfx950(&dev, &ncu, &why)) return build_batch(n, dh, lh, opts_in, single, out);
-    key = "gfx950-" + std::to_string(ncu) + "cu/" + key;
+    key = "gfx950-" + std::to_string(ncu) + "cu/s" + std::to_string(kSchedVersion) + "/" + key;
   }
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);

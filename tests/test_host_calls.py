@@ -94,3 +94,33 @@ for d, l, n in [(14, 3, 1), (20, 4, 1), (11, 1, 250), (14, 3, 30)]:
     assert len(tile) == 1 and tile[0][0] <= 256 and 2 * tile[0][1] <= 160 * 1024, (d, l, n, tile)
     ok(lib.fsi_batch_plan_destroy(p))
 """)
+
+
+def test_tune_entries_of_other_schedules(run, tmp_path):
+    """An entry written when the same numbers meant another schedule (its key has
+    no schedule version) is not taken: the plan is timed, and its own entry serves
+    the next process."""
+    path = tmp_path / "tune.json"
+    code = r"""
+import struct
+opts = (i32 * 10)()
+ok(lib.fsi_default_opts(opts))
+opts[5] = 1                       # autotune
+key = "gfx950-256cu/%d/%d/%d/%d/%d/%d;12,6x1" % tuple(opts[i] for i in (0, 1, 2, 6, 3, 8))
+p = batch([12], [6], opts)
+s = C.create_string_buffer(24)
+ok(lib.fsi_batch_schedule(p, s))
+print("KEY", key)
+print("SCHED", *struct.unpack("5if", s.raw))
+ok(lib.fsi_batch_plan_destroy(p))
+"""
+    def sched(out):
+        return [x.split()[1:] for x in out.splitlines() if x.startswith("SCHED")][0]
+    out = run(code, FSI_TUNE_CACHE=str(tmp_path / "other.json"))
+    key = [x[4:] for x in out.splitlines() if x.startswith("KEY")][0]
+    path.write_text('{"format": "fsi-autotune-1", "entries": [\n{"key": "%s", "kernel": 1, "tb_shift": '
+                    '-2, "chunk_shift": 0, "mob_group": 0, "algo": 1}\n]}\n' % key)
+    first = sched(run(code, FSI_TUNE_CACHE=str(path)))
+    assert first[0] == "1" and first[3] == "0" and float(first[5]) > 0
+    second = sched(run(code, FSI_TUNE_CACHE=str(path)))
+    assert second[0] == "1" and second[3] == "0" and float(second[5]) == 0
