@@ -965,7 +965,7 @@ struct fsi_forest_s {
   int32_t* path_leaf = nullptr;
   Reach* reach = nullptr;          // leaf lists of a walk call (null: not kept)
   int reach_rows = 0;
-  int32_t* reach_cnt = nullptr;    // pairs, then the overflow count
+  int32_t* reach_cnt = nullptr;    // past the lists: pairs, then the overflow count
 };
 
 namespace {
@@ -980,7 +980,7 @@ void free_forest(fsi_forest_s* F) {
   for (void* p : {(void*)F->feature, (void*)F->left, (void*)F->right, (void*)F->roots,
                   (void*)F->threshold, (void*)F->value, (void*)F->prep,
                   (void*)F->path_off, (void*)F->steps, (void*)F->path_leaf,
-                  (void*)F->reach, (void*)F->reach_cnt})
+                  (void*)F->reach})
     if (p) (void)hipFree(p);
   delete F;
 }
@@ -1141,11 +1141,18 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
       if (e == hipSuccess) e = upload(&F->steps, psteps.data(), std::max<size_t>(psteps.size(), 1));
       if (e == hipSuccess) e = upload(&F->path_leaf, pleaf.data(), pleaf.size());
     }
+    // the walk runs without the lists too, so a forest does without them where
+    // they find no room
     const size_t pairs = (size_t)max_bg * (size_t)n_trees;
     F->reach_rows = (int)std::min<size_t>(kReachMax, kReachBytes / (pairs * sizeof(Reach)));
     if (e == hipSuccess && F->reach_rows >= kReachMin) {
-      e = hipMalloc((void**)&F->reach, pairs * F->reach_rows * sizeof(Reach));
-      if (e == hipSuccess) e = hipMalloc((void**)&F->reach_cnt, (pairs + 1) * sizeof(int32_t));
+      const size_t lists = pairs * F->reach_rows * sizeof(Reach);
+      if (hipMalloc((void**)&F->reach, lists + (pairs + 1) * sizeof(int32_t)) == hipSuccess) {
+        F->reach_cnt = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(F->reach) + lists);
+      } else {
+        F->reach = nullptr;
+        (void)hipGetLastError();
+      }
     }
   }
   if (e != hipSuccess) {

@@ -124,3 +124,28 @@ ok(lib.fsi_batch_plan_destroy(p))
     assert first[0] == "1" and first[3] == "0" and float(first[5]) > 0
     second = sched(run(code, FSI_TUNE_CACHE=str(path)))
     assert second[0] == "1" and second[3] == "0" and float(second[5]) == 0
+
+
+def test_forest_without_room_for_its_lists(run):
+    """The leaf lists of the walk are optional: a forest whose device has no room
+    for them is made all the same, and its walk runs without the listing pass."""
+    run(r"""
+import math
+d, trees, bgs = 16, 40, 200
+D, F64 = C.c_double, C.c_double * (3 * trees)
+f, l, r = ints([0, -1, -1] * trees), ints([3 * k + 1 for k in range(trees) for _ in range(3)]), ints([3 * k + 2 for k in range(trees) for _ in range(3)])
+z = F64()
+def values(fail):
+    h = vp()
+    mock.mock_fail_malloc(1 << 20, fail)
+    ok(lib.fsi_forest_create(d, trees, ints(range(0, 3 * trees, 3)), 3 * trees, f, z, l, r, z, bgs, C.byref(h)))
+    mock.mock_fail_malloc(0, 0)
+    log()
+    ok(lib.fsi_forest_values(h, A, bgs, A, 0, A, None))
+    names = [k for _, _, k in launches()]
+    ok(lib.fsi_forest_destroy(h))
+    return names
+assert any("reach" in k for k in values(0))
+names = values(1)
+assert not any("reach" in k for k in names) and any("walk" in k for k in names), names
+""")
