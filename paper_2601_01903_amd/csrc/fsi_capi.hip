@@ -179,7 +179,8 @@ struct Sched {
   int chunk_shift = 0;  // register-phase kernel: log2 tiles per item relative to the default
   int mob_group = 0;    // two-pass: most bits of a strided high Moebius pass (0: kMobGroup)
   int algo = 0;         // FSI_ALGO_FUSED or FSI_ALGO_TWO_PASS; 0: the option's
-  bool high = true;     // orders 5 and 6 may take the register phases (not tuned)
+  int high = 0;         // orders 5 and 6 on the register phases: 0 where the results
+                        // fit (see build_batch), 1 always, -1 never (not tuned)
 };
 
 // Device scratch of fsi_apply_batched_noalloc; a plan's schedule keeps within
@@ -259,6 +260,58 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
   std::string why;
   if (!device_is_gfx950(&dev, &n_cu, &why)) return fail(FSI_ERR_UNSUPPORTED, why);
 
+  // Orders 5 and 6, where the kernel is left to the plan, run the phases of the
+  // l <= 4 kernel with the per-tile results in memory. The tile of a smaller
+  // instance is mostly padding: past a workgroup per CU the generic kernel is
+  // faster up to d = 9 in FP64 (1200 x d = 8, l = 5: 27 against 36 us; at
+  // d = 10 78 against 39) and d = 7 in FP32 (2500 x l = 5: 29 against 36;
+  // at d = 8 38 against 37)
+  const int kern = sc.kernel >= 0 ? sc.kernel : opts.kernel;
+  const int small_d = sweep_elem_bytes(prec) == 8 ? 10 : 8;
+  auto takes_high = [&](int d, int l) {
+    return sc.high >= 0 && kern == FSI_KERNEL_AUTO && (d >= small_d || n <= n_cu) && algo == ALGO_FUSED &&
+           fast_supported(prec) && l >= kHighMinL && l <= kHighMaxL &&
+           (opts.tile_bits == 0 || opts.tile_bits == kFastTileBits);
+  };
+  // Their results, 26 and 53 KB a tile, are several times the generic kernel's on
+  // small instances: where they exceed the scratch of
+  // fsi_apply_batched_noalloc and the generic kernel's do not, the plan takes
+  // the generic kernel, and so do calls without allocation. (Decided from the
+  // sizes before anything is built; the partial sums of other instances are
+  // known only then, and where they count the plan is built again.)
+  std::map<std::pair<int, int>, int64_t> generic_doubles;   // per instance of (d, l)
+  auto generic_results = [&](int d, int l) {
+    int64_t& g = generic_doubles[{d, l}];
+    if (g == 0) {
+      const int b = choose_tile_bits(d, l, prec, opts.tile_bits);
+      g = tile_results(d, l, b) << (d - b);
+    }
+    return g;
+  };
+  auto within_scratch = [](int64_t doubles) { return (size_t)doubles * sizeof(double) + 4 * 256 <= kScratchBytes; };
+  if (sc.high == 0) {
+    int64_t high = 0, generic = 0;
+    for (int i = 0; i < n; ++i)
+      if (takes_high(dh[i], lh[i])) {
+        high += (int64_t)t11::ysize(lh[i]) << std::max(0, dh[i] - kFastTileBits);
+        generic += generic_results(dh[i], lh[i]);
+      }
+    if (!within_scratch(high) && within_scratch(generic)) {
+      Sched gs = sc;
+      gs.high = -1;
+      fsi_batch_plan_s* G = nullptr;
+      const fsi_status st = build_batch(n, dh, lh, &opts, single, &G, gs);
+      if (st != FSI_OK) return st;
+      if (scratch_need(G) <= kScratchBytes) {
+        *out = G;
+        return FSI_OK;
+      }
+      free_batch(G);
+      gs.high = 1;
+      return build_batch(n, dh, lh, &opts, single, out, gs);
+    }
+  }
+
   auto* P = new (std::nothrow) fsi_batch_plan_s();
   if (!P) return fail(FSI_ERR_OUT_OF_MEMORY, "host allocation failed");
   // frees the partly built plan if a host allocation below throws
@@ -289,7 +342,6 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
       // set holding one of them and the weights W(s, t) do not depend on d,
       // so the outputs of the sets inside [d] are the instance's own
       const int fb = kFastTileBits;
-      const int kern = sc.kernel >= 0 ? sc.kernel : opts.kernel;
       const int dfast = std::max(dh[i], fb);
       const bool want_fast = kern != FSI_KERNEL_GENERIC && algo == ALGO_FUSED &&
                              fast_supported(prec) && lh[i] <= kFastMaxL &&
@@ -299,16 +351,7 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
         return fail(FSI_ERR_UNSUPPORTED, "register-phase kernel does not apply to instance " +
                                              std::to_string(i));
       }
-      // the same phases with the per-tile results in memory: orders 5 and 6,
-      // where the kernel is left to the plan. The tile of a smaller instance
-      // is mostly padding: past a workgroup per CU the generic kernel is
-      // faster up to d = 9 in FP64 (1200 x d = 8, l = 5: 27 against 36 us; at
-      // d = 10 78 against 39) and d = 7 in FP32 (2500 x l = 5: 29 against 36;
-      // at d = 8 38 against 37)
-      const int small_d = sweep_elem_bytes(prec) == 8 ? 10 : 8;
-      const bool want_high = sc.high && kern == FSI_KERNEL_AUTO && (dh[i] >= small_d || n <= n_cu) && algo == ALGO_FUSED &&
-                             fast_supported(prec) && lh[i] >= kHighMinL && lh[i] <= kHighMaxL &&
-                             (opts.tile_bits == 0 || opts.tile_bits == fb);
+      const bool want_high = takes_high(dh[i], lh[i]);
       const bool phased = want_fast || want_high;
       int b = phased ? fb : choose_tile_bits(dh[i], lh[i], prec, opts.tile_bits);
       if (!phased && opts.tile_bits == 0) b = std::max(1, b + sc.tb_shift);
@@ -467,14 +510,24 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     int64_t chunk_fit = 0;
     int wgs_fit = fast_wgs;
     std::vector<double> cost;
+    // instances by class: those of one class have the same items
+    std::vector<int> rep(P->classes.size(), -1), count(P->classes.size(), 0);
+    for (int i = 0; i < n; ++i) {
+      rep[P->cls_of[i]] = i;
+      ++count[P->cls_of[i]];
+    }
     for (int64_t c : cand) {
       // sizes that cut the batch into far more items than workgroups only
-      // add partial sums (the largest size is always simulated)
+      // add partial sums
       int64_t items = 0;
-      for (int i = 0; i < n; ++i)
-        if (P->fast_of[P->cls_of[i]] >= 0) {
-          const int64_t ntile = (int64_t)1 << P->classes[P->cls_of[i]].h;
-          items += (ntile + item_tiles(i, c) - 1) / item_tiles(i, c);
+      double part_bytes = 0.0;
+      for (size_t k = 0; k < P->classes.size(); ++k)
+        if (P->fast_of[k] >= 0) {
+          const FastClassHost& F = P->fclasses[P->fast_of[k]];
+          const int64_t ntile = (int64_t)1 << F.h, cs = item_tiles(rep[k], c);
+          const int64_t per = (ntile + cs - 1) / cs;
+          items += count[k] * per;
+          if (cs < ntile) part_bytes += (double)(count[k] * per) * ((double)F.nkk * kFastThreads * 8.0);
         }
       if (items > 64 * (int64_t)slots && c != cand.back()) continue;
       // every number of workgroups per CU, up to the most that fit: fewer run
@@ -493,18 +546,28 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
         double tile_us[kFastMaxL + 1];
         for (int l = 0; l <= kFastMaxL; ++l) tile_us[l] = at(&us[s0][l], &us[s1][l]);
         const double item_us = at(&kItemUs[prec == PREC_F64][s0], &kItemUs[prec == PREC_F64][s1]);
-        cost.clear();
-        double part_bytes = 0.0;
-        for (int i = 0; i < n; ++i) {
-          const int f = P->fast_of[P->cls_of[i]];
-          if (f < 0) continue;
-          const FastClassHost& F = P->fclasses[f];
-          const int64_t ntile = (int64_t)1 << F.h, cs = item_tiles(i, c);
-          for (int64_t tb = 0; tb < ntile; tb += cs) {
-            const int64_t nt = std::min<int64_t>(cs, ntile - tb);
-            cost.push_back((double)nt * tile_us[F.l] + item_us);
-            if (cs < ntile) part_bytes += (double)F.nkk * kFastThreads * 8.0;
+        const double fixed = red_base_us + part_bytes / red_bytes_per_us +
+                             (items > n_cu * w ? queue_us : 0.0);
+        const bool fits = part_bytes <= (double)kFitBytes;
+        // no schedule ends before its work is shared evenly or its longest item
+        // is done: sizes that cannot win are not simulated
+        double work = (double)items * item_us, longest = 0.0;
+        for (size_t k = 0; k < P->classes.size(); ++k)
+          if (P->fast_of[k] >= 0) {
+            const FastClassHost& F = P->fclasses[P->fast_of[k]];
+            work += (double)count[k] * (double)((int64_t)1 << F.h) * tile_us[F.l];
+            const int64_t cs = std::min<int64_t>(item_tiles(rep[k], c), (int64_t)1 << F.h);
+            longest = std::max(longest, (double)cs * tile_us[F.l] + item_us);
           }
+        const double least = (std::max(work / (n_cu * w), longest) + fixed) * (1.0 - 1e-9);
+        if (best >= 0.0 && least >= best && (!fits || (best_fit >= 0.0 && least >= best_fit))) continue;
+        cost.clear();
+        for (size_t k = 0; k < P->classes.size(); ++k) {
+          if (P->fast_of[k] < 0) continue;
+          const FastClassHost& F = P->fclasses[P->fast_of[k]];
+          const int64_t ntile = (int64_t)1 << F.h, cs = item_tiles(rep[k], c);
+          for (int64_t tb = 0; tb < ntile; tb += cs)
+            cost.insert(cost.end(), count[k], (double)std::min<int64_t>(cs, ntile - tb) * tile_us[F.l] + item_us);
         }
         std::sort(cost.begin(), cost.end(), std::greater<double>());
         std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
@@ -519,10 +582,9 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
         }
         double end = 0.0;
         while (!busy.empty()) { end = std::max(end, busy.top()); busy.pop(); }
-        const double total = end + red_base_us + part_bytes / red_bytes_per_us +
-                             (items > n_cu * w ? queue_us : 0.0);
+        const double total = end + fixed;
         if (best < 0.0 || total < best) { best = total; chunk = c; run_wgs = w; }
-        if (part_bytes <= (double)kFitBytes && (best_fit < 0.0 || total < best_fit)) {
+        if (fits && (best_fit < 0.0 || total < best_fit)) {
           best_fit = total;
           chunk_fit = c;
           wgs_fit = w;
@@ -716,29 +778,14 @@ fsi_status build_batch(int n, const int* dh, const int* lh, const fsi_plan_opts*
     n_passes = std::max(n_passes, np);
   }
 
-  // orders 5 and 6 keep 26 and 53 KB of results a tile, several times the
-  // generic kernel's on small instances: where they exceed the scratch of
-  // fsi_apply_batched_noalloc and the generic kernel's do not, the plan takes
-  // the generic kernel, and so do calls without allocation
-  if (!P->hclasses.empty() &&
-      (size_t)(ytot + ptot + wptot) * sizeof(double) + 4 * 256 > kScratchBytes) {
-    int64_t gtot = 0;
-    std::vector<int64_t> gsize(P->classes.size(), 0);
-    for (int i = 0; i < n; ++i) {
-      if (!insts[i].high) continue;
-      int64_t& g = gsize[P->cls_of[i]];
-      if (g == 0) {
-        const int b = choose_tile_bits(dh[i], lh[i], prec, opts.tile_bits);
-        ClassHost G;
-        const std::string err = build_class(dh[i], lh[i], b, algo, opts.index, opts.input, &G);
-        if (!err.empty()) { return fail(FSI_ERR_INTERNAL, err); }
-        g = ((int64_t)1 << G.h) * G.Ysize;
-      }
-      gtot += g;
-    }
-    if ((size_t)(gtot + ptot) * sizeof(double) + 4 * 256 <= kScratchBytes) {
+  // the same choice where the partial sums of other instances tip it
+  if (sc.high == 0 && !P->hclasses.empty() && !within_scratch(ytot + ptot + wptot)) {
+    int64_t generic = 0;
+    for (int i = 0; i < n; ++i)
+      if (insts[i].high) generic += generic_results(dh[i], lh[i]);
+    if (within_scratch(generic + ptot)) {
       Sched gs = sc;
-      gs.high = false;
+      gs.high = -1;
       fsi_batch_plan_s* G = nullptr;
       const fsi_status st = build_batch(n, dh, lh, &opts, single, &G, gs);
       if (st != FSI_OK) return st;

@@ -131,6 +131,8 @@ bool gfx950_device(int* dev, int* n_cu, std::string* why);
 double weight_full(int s, int t, int l, int index);
 // Largest sweep state of an in-tile sweep over b bits, in entries.
 int64_t sweep_peak_entries(int b, int l);
+// Per-tile results (doubles) of the fused generic kernel with tiles of b bits.
+int64_t tile_results(int d, int l, int b);
 // Builds the tables of one class: weights and outputs, and the generic
 // kernel's sweep and result tables unless sweep_tables is false. Returns "" or
 // an error message.

@@ -89,10 +89,10 @@ __float128 weight_q(int s, int t, int l, int index) {
 //   lambda = sum_{m=0}^{h-q} C(h-q, m) (-1)^(q+m-u) W(s, t_L + q + m),
 // i.e. the sum over all high supersets T_H of S_H union U_H of
 // (-1)^(|T_H|-|U_H|) W(s, t_L + |T_H|).
-__float128 lambda_q(int s, int tL, int q, int u, int h, int l, int index) {
+__float128 lambda_q(const __float128* w, int tL, int q, int u, int h) {
   __float128 acc = 0;
   for (int m = 0; m <= h - q; ++m) {
-    __float128 term = (__float128)binom(h - q, m) * weight_q(s, tL + q + m, l, index);
+    __float128 term = (__float128)binom(h - q, m) * w[tL + q + m];
     acc += ((q + m - u) & 1) ? -term : term;
   }
   return acc;
@@ -141,6 +141,15 @@ int64_t sweep_peak_entries(int b, int l) {
   return peak;
 }
 
+int64_t tile_results(int d, int l, int b) {
+  int64_t n = 0;
+  for (int s = 0; s <= std::min(l, b); ++s) {
+    const int top = std::min(l - s, d - b);
+    n += (int64_t)t11::cbinom(b, s) * ((top + 1) * (top + 2) / 2);
+  }
+  return n;
+}
+
 std::string build_class(int d, int l, int b, int algo, int index, int mobius_in, ClassHost* C,
                         bool sweep_tables) {
   if (!(1 <= l && l <= d && d <= kMaxD)) return "invalid (d, l)";
@@ -173,12 +182,16 @@ std::string build_class(int d, int l, int b, int algo, int index, int mobius_in,
   // two-pass: the weights also as double-doubles (their rounding error,
   // for the compensated FP64 weight core)
   if (algo != ALGO_FUSED) C->lam_lo.assign((size_t)(h + 1) * off, 0.0);
+  // W(s, t), evaluated once: the weights below sum or round them
+  std::vector<__float128> W((size_t)(l + 1) * (d + 1), 0);
+  for (int s = 0; s <= l; ++s)
+    for (int t = s; t <= d; ++t) W[(size_t)s * (d + 1) + t] = weight_q(s, t, l, index);
   for (int u = 0; u <= h; ++u) {
     for (int sL = 0; sL <= std::min(l, b); ++sL) {
       double* blk = &C->lam[(size_t)u * off + C->lam_soff[sL]];
       const int top = std::min(l - sL, h);
       for (int sH = 0; sH <= top; ++sH) {
-        const int s = sL + sH;
+        const __float128* w = &W[(size_t)(sL + sH) * (d + 1)];
         if (algo == ALGO_FUSED) {
           for (int j = 0; j <= sH; ++j) {
             const int slot = sH * (sH + 1) / 2 + j;
@@ -187,20 +200,19 @@ std::string build_class(int d, int l, int b, int algo, int index, int mobius_in,
               // the outputs with S_H inside U_H (j = s_H) at t = t_L + |U_H|
               const bool ok = j == sH && sH <= u;
               for (int tL = sL; tL <= b; ++tL)
-                blk[slot * (b + 1) + tL] = ok ? (double)weight_q(s, tL + u, l, index) : 0.0;
+                blk[slot * (b + 1) + tL] = ok ? (double)w[tL + u] : 0.0;
               continue;
             }
             const bool ok = j <= u && (sH - j) <= (h - u);
             const int q = u + sH - j;
             for (int tL = sL; tL <= b; ++tL)
-              blk[slot * (b + 1) + tL] = ok ? (double)lambda_q(s, tL, q, u, h, l, index) : 0.0;
+              blk[slot * (b + 1) + tL] = ok ? (double)lambda_q(w, tL, q, u, h) : 0.0;
           }
         } else {
           double* blo = &C->lam_lo[(size_t)u * off + C->lam_soff[sL]];
           for (int tL = sL; tL <= b; ++tL) {
-            const __float128 w = weight_q(s, tL + u, l, index);
-            blk[sH * (b + 1) + tL] = (double)w;
-            blo[sH * (b + 1) + tL] = (double)(w - (__float128)(double)w);
+            blk[sH * (b + 1) + tL] = (double)w[tL + u];
+            blo[sH * (b + 1) + tL] = (double)(w[tL + u] - (__float128)(double)w[tL + u]);
           }
         }
       }
@@ -305,6 +317,16 @@ int fast_output_slots(int d, int l) {
   return (int)(2 * (k == h ? t11::positions_needed(l, h) : t11::positions_blocked(l, k)));
 }
 
+// Colex ranks of the tile's masks among those of their size.
+static const std::vector<int>& tile_ranks() {
+  static const std::vector<int> rank = [] {
+    std::vector<int> r(1 << t11::B);
+    for (size_t m = 0; m < r.size(); ++m) r[m] = t11::rank_colex((uint32_t)m);
+    return r;
+  }();
+  return rank;
+}
+
 // Unit maps of the sweep phases and the final weights, for either kernel.
 static std::string build_phase_tables(const ClassHost& C, FastClassHost* F) {
   using namespace t11;
@@ -330,24 +352,30 @@ static std::string build_phase_tables(const ClassHost& C, FastClassHost* F) {
     }
   }
   F->zrow.assign((size_t)nu * NC, 0);
+  const std::vector<int>& rank = tile_ranks();
+  std::vector<int> zb(B + 2);
+  for (int s = 0; s <= B + 1; ++s) zb[s] = zbase(s);
   for (int u = 0; u < nu; ++u)
-    for (int sc = 0; sc < NC; ++sc)
-      F->zrow[(size_t)u * NC + sc] = zrow_of(l, (uint32_t)F->unit_mask[u] | ((uint32_t)sc << KAB));
+    for (int sc = 0; sc < NC; ++sc) {
+      const uint32_t SL = (uint32_t)F->unit_mask[u] | ((uint32_t)sc << KAB);
+      const int s = popc(SL);
+      F->zrow[(size_t)u * NC + sc] = s > l ? zb[l + 1] : zb[s] + rank[SL];   // zrow_of(l, SL)
+    }
   // weights: entry (u, s_L, slot, r) = the class's precontracted weight of
   // counter t = s_L + r (zero past t = 11 and for slots the class lacks)
   const int lb = lamblock(l);
   F->lam.assign((size_t)(h + 1) * lb, 0.0);
-  for (int u = 0; u <= h; ++u)
-    for (int sL = 0; sL <= l; ++sL) {
-      const int top = std::min(l - sL, h);
+  for (int sL = 0; sL <= l; ++sL) {
+    const int top = std::min(l - sL, h), lo = lamoff(l, sL);
+    for (int u = 0; u <= h; ++u)
       for (int sH = 0; sH <= top; ++sH)
         for (int j = 0; j <= sH; ++j) {
           const int slot = sH * (sH + 1) / 2 + j;
           for (int r = 0; sL + r <= b; ++r)
-            F->lam[(size_t)u * lb + lamoff(l, sL) + slot * ZROW + r] =
+            F->lam[(size_t)u * lb + lo + slot * ZROW + r] =
                 C.lam[(size_t)u * C.lam_ublock + C.lam_soff[sL] + slot * (b + 1) + sL + r];
         }
-    }
+  }
   return "";
 }
 
@@ -473,11 +501,18 @@ std::string build_high_class(const ClassHost& C, FastClassHost* F) {
   if (!err.empty()) return err;
   if (ysize(l) >= 1 << 16) return "result word overflow";
   const uint32_t lowmask = (1u << b) - 1;
+  const std::vector<int>& rank = tile_ranks();
+  int yb[kHighMaxL + 1], nr[kHighMaxL + 1];
+  for (int s = 0; s <= l; ++s) {
+    yb[s] = ybase(l, s);
+    nr[s] = nrp(s);
+  }
+  F->hword.reserve(C.out_masks.size());
+  F->hhigh.reserve(C.out_masks.size());
   for (const uint32_t S : C.out_masks) {
     const uint32_t SL = S & lowmask, SH = S >> b;
     const int sL = popc(SL), sH = popc(SH);
-    const int at = ybase(l, sL) + sH * (sH + 1) / 2 * nrp(sL) + rank_colex(SL);
-    F->hword.push_back((uint32_t)at | (uint32_t)nrp(sL) << 16);
+    F->hword.push_back((uint32_t)(yb[sL] + sH * (sH + 1) / 2 * nr[sL] + rank[SL]) | (uint32_t)nr[sL] << 16);
     F->hhigh.push_back(SH);
   }
   return "";

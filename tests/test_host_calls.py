@@ -149,3 +149,37 @@ assert any("reach" in k for k in values(0))
 names = values(1)
 assert not any("reach" in k for k in names) and any("walk" in k for k in names), names
 """)
+
+
+def test_plans_at_the_scratch_line_are_built_once(run):
+    """Orders 5 and 6 keep the generic kernel where only its results fit the scratch
+    of the call without allocation: making such a plan takes the time of a
+    generic one."""
+    run(r"""
+import time
+for d, l, n in [(18, 5, 24), (20, 5, 7)]:
+    best = [1e9, 1e9]
+    for _ in range(9):
+        for kernel in (0, 1):
+            opts = (i32 * 10)()
+            ok(lib.fsi_default_opts(opts))
+            opts[0], opts[6] = 1, kernel
+            t = time.perf_counter()
+            p = batch([d] * n, [l] * n, opts)
+            best[kernel] = min(best[kernel], time.perf_counter() - t)
+            log()
+            ok(lib.fsi_apply_batched_nograph(p, A, A, None))
+            assert not any("tile_high" in k for _, _, k in launches())
+            ok(lib.fsi_batch_plan_destroy(p))
+    assert best[0] < 1.8 * best[1], (d, l, n, best)
+""")
+
+
+def test_result_counts_of_the_generic_kernel(tmp_path):
+    csrc = os.path.join(ROOT, "paper_2601_01903_amd", "csrc")
+    exe = str(tmp_path / "check")
+    subprocess.run(["hipcc", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
+                    os.path.join(ROOT, "tests", "host", "check_tile_results.cpp"),
+                    os.path.join(csrc, "fsi_tables.cpp"), "-o", exe], check=True, capture_output=True)
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout
