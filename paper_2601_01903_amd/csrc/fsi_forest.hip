@@ -951,6 +951,7 @@ using namespace fsi::forest;
 
 struct fsi_forest_s {
   int d = 0, n_trees = 0, n_nodes = 0, max_bg = 0, depth = 0, device = 0;
+  unsigned char* arena = nullptr;  // holds the arrays up to path_leaf
   int32_t* feature = nullptr;
   int32_t* left = nullptr;
   int32_t* right = nullptr;
@@ -977,11 +978,8 @@ fsi_status ffail(fsi_status st, const std::string& msg) {
 
 void free_forest(fsi_forest_s* F) {
   if (!F) return;
-  for (void* p : {(void*)F->feature, (void*)F->left, (void*)F->right, (void*)F->roots,
-                  (void*)F->threshold, (void*)F->value, (void*)F->prep,
-                  (void*)F->path_off, (void*)F->steps, (void*)F->path_leaf,
-                  (void*)F->reach})
-    if (p) (void)hipFree(p);
+  if (F->arena) (void)hipFree(F->arena);
+  if (F->reach) (void)hipFree(F->reach);
   delete F;
 }
 
@@ -1061,11 +1059,13 @@ bool enumerate_paths(const int32_t* feature, const int32_t* left, const int32_t*
   return true;
 }
 
+// Appends an aligned block to a host staging buffer and returns its offset.
 template <typename T>
-hipError_t upload(T** dst, const T* src, size_t n) {
-  hipError_t e = hipMalloc((void**)dst, n * sizeof(T));
-  if (e != hipSuccess) return e;
-  return hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice);
+size_t stage(std::vector<unsigned char>& buf, const T* data, size_t n) {
+  const size_t off = (buf.size() + 255) & ~(size_t)255;
+  buf.resize(off + n * sizeof(T));
+  if (n) std::memcpy(buf.data() + off, data, n * sizeof(T));
+  return off;
 }
 
 }  // namespace
@@ -1116,36 +1116,48 @@ fsi_status fsi_forest_create(int d, int n_trees, const int32_t* roots, int n_nod
   // leaves keep feature -1 on the device whatever negative value they had
   std::vector<int32_t> feat(feature, feature + n_nodes);
   for (auto& f : feat) f = f < 0 ? -1 : f;
-  hipError_t e = upload(&F->feature, feat.data(), (size_t)n_nodes);
-  if (e == hipSuccess) e = upload(&F->left, left, (size_t)n_nodes);
-  if (e == hipSuccess) e = upload(&F->right, right, (size_t)n_nodes);
-  if (e == hipSuccess) e = upload(&F->roots, roots, (size_t)n_trees);
-  if (e == hipSuccess) e = upload(&F->threshold, threshold, (size_t)n_nodes);
-  if (e == hipSuccess) e = upload(&F->value, value, (size_t)n_nodes);
-  if (e == hipSuccess) {
-    const size_t chunks = (size_t)((max_bg + kBgChunk - 1) / kBgChunk);
-    e = hipMalloc((void**)&F->prep, chunks * (size_t)n_nodes * sizeof(Node));
+  std::vector<int32_t> poff, psteps, pleaf;
+  if (enumerate_paths(feat.data(), left, right, roots, n_trees, &poff, &psteps, &pleaf)) {
+    F->n_paths = (int)pleaf.size();
+    for (size_t p = 0; p + 1 < poff.size(); ++p)
+      F->max_path = std::max(F->max_path, poff[p + 1] - poff[p]);
+    if (std::min(F->max_path, d) > kMaxFreeSplits) F->n_paths = -1;
+  } else {
+    F->n_paths = -1;
   }
+  if (F->n_paths < 0) { poff.clear(); psteps.clear(); pleaf.clear(); }
+  // one allocation and one copy (ten and nine of them took 100 us more)
+  std::vector<unsigned char> buf;
+  buf.reserve((size_t)n_nodes * 28 + (poff.size() + psteps.size() + pleaf.size() + n_trees) * 4 + 10 * 256);
+  const size_t o_feature = stage(buf, feat.data(), feat.size());
+  const size_t o_left = stage(buf, left, (size_t)n_nodes), o_right = stage(buf, right, (size_t)n_nodes);
+  const size_t o_roots = stage(buf, roots, (size_t)n_trees);
+  const size_t o_threshold = stage(buf, threshold, (size_t)n_nodes);
+  const size_t o_value = stage(buf, value, (size_t)n_nodes);
+  const size_t o_off = stage(buf, poff.data(), poff.size());
+  const size_t o_steps = stage(buf, psteps.data(), psteps.size());
+  const size_t o_leaf = stage(buf, pleaf.data(), pleaf.size());
+  const size_t chunks = (size_t)((max_bg + kBgChunk - 1) / kBgChunk);
+  const size_t o_prep = (buf.size() + 255) & ~(size_t)255;
+  hipError_t e = hipMalloc((void**)&F->arena, o_prep + chunks * (size_t)n_nodes * sizeof(Node));
+  if (e == hipSuccess) e = hipMemcpy(F->arena, buf.data(), buf.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) {
-    std::vector<int32_t> poff, psteps, pleaf;
-    if (enumerate_paths(feat.data(), left, right, roots, n_trees, &poff, &psteps, &pleaf)) {
-      F->n_paths = (int)pleaf.size();
-      for (size_t p = 0; p + 1 < poff.size(); ++p)
-        F->max_path = std::max(F->max_path, poff[p + 1] - poff[p]);
-      if (std::min(F->max_path, d) > kMaxFreeSplits) F->n_paths = -1;
-    } else {
-      F->n_paths = -1;
-    }
-    if (F->n_paths > 0) {
-      e = upload(&F->path_off, poff.data(), poff.size());
-      if (e == hipSuccess) e = upload(&F->steps, psteps.data(), std::max<size_t>(psteps.size(), 1));
-      if (e == hipSuccess) e = upload(&F->path_leaf, pleaf.data(), pleaf.size());
-    }
+    auto ints = [&](size_t off) { return reinterpret_cast<int32_t*>(F->arena + off); };
+    F->feature = ints(o_feature);
+    F->left = ints(o_left);
+    F->right = ints(o_right);
+    F->roots = ints(o_roots);
+    F->threshold = reinterpret_cast<double*>(F->arena + o_threshold);
+    F->value = reinterpret_cast<double*>(F->arena + o_value);
+    F->path_off = ints(o_off);
+    F->steps = ints(o_steps);
+    F->path_leaf = ints(o_leaf);
+    F->prep = reinterpret_cast<Node*>(F->arena + o_prep);
     // the walk runs without the lists too, so a forest does without them where
     // they find no room
     const size_t pairs = (size_t)max_bg * (size_t)n_trees;
     F->reach_rows = (int)std::min<size_t>(kReachMax, kReachBytes / (pairs * sizeof(Reach)));
-    if (e == hipSuccess && F->reach_rows >= kReachMin) {
+    if (F->reach_rows >= kReachMin) {
       const size_t lists = pairs * F->reach_rows * sizeof(Reach);
       if (hipMalloc((void**)&F->reach, lists + (pairs + 1) * sizeof(int32_t)) == hipSuccess) {
         F->reach_cnt = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(F->reach) + lists);

@@ -124,7 +124,8 @@ def test_blocks_list_where_the_lists_find_no_room():
 # d = 20, none past d = 23), and from d = 15 one or 64 coalitions a workgroup's lane
 @pytest.mark.parametrize("d,n_trees,depth", [(1, 4, 2), (9, 32, 1), (9, 33, 1), (10, 4, 11), (10, 5, 11),
                                              (15, 16, 4), (15, 17, 4), (16, 64, 4), (16, 65, 4),
-                                             (20, 12, 1), (20, 13, 1), (23, 1, 1), (24, 1, 1)])
+                                             (20, 12, 1), (20, 13, 1), (23, 1, 1), (24, 1, 1),
+                                             (9, 3, 0), (9, 40, 0), (20, 13, 0)])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_kernel_lines(d, n_trees, depth, dtype):
     say(f"[case] walk lines d={d} trees={n_trees} depth={depth} {dtype}")
