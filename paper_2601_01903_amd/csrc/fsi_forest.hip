@@ -157,11 +157,12 @@ __device__ __forceinline__ int list_leaves(const Node* __restrict__ P, const dou
 // Leaves of a pair reachable by any coalition at all, over the d bits: in must
 // be in S, out must not. Entry i of pair g at i * pairs + g, counts in cnt.
 // Made once per call, so a block only picks the ones its shared bits allow
-// instead of walking the tree again. A pair with more of them than there are
-// rows has no list, and its coalitions walk. (Listing such a pair's leaves in
-// every block instead, by one thread, is a chain of up to 13 walks that the block
-// waits for: 20 depth-12 trees at d = 20, x and background apart everywhere:
-// 337 us, 178 by plain walks.)
+// instead of walking the tree again. A pair with more than 64 of them has no
+// list, and its coalitions walk. (Listing such a pair's leaves in every block
+// instead, by one thread, is a chain of up to 13 walks that the block waits for:
+// 20 depth-12 trees at d = 20, x and background apart everywhere: 337 us, 178 by
+// plain walks.) The blocks do list those of up to 64 that find no row where the
+// pairs are too many for 64 rows each.
 constexpr int kReachMax = 64, kReachMin = 24;   // rows, as the workspace allows
 constexpr int kListMax = 12;     // leaves of a block's list
 struct alignas(16) Reach {
@@ -183,8 +184,7 @@ struct ReachLists {
 // depth-14 tree at d = 10 took 811 us; now 23).
 //
 // What the lists of the blocks (m low bits) will hold is counted for kSamples
-// settings of their shared bits. Nodes above the leaves still multiply (by about
-// 1.5 a level at m = d / 2), so there a third of a list counts as too many.
+// settings of their shared bits.
 constexpr int kSamples = 4;
 __global__ void __launch_bounds__(kThreads)
 reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
@@ -233,17 +233,14 @@ reach_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
       if (lane < n) at = N[lane];
       __builtin_amdgcn_wave_barrier();
     }
-    const bool rest = lane + 64 < n;           // nodes past the wave's lanes
-    const At at2 = rest ? N[lane + 64] : At{};
     int overs = 0;
     uint32_t s = (uint32_t)g * 0x9e3779b9u;
 #pragma unroll
     for (int k = 0; k < kSamples; ++k) {
       s = (s ^ (s >> 15)) * 0x85ebca6bu + 0x6a09e667u;
       const uint32_t S = s ^ (s >> 13);
-      auto in_block = [&](const At& a) { return !(((a.in & ~S) | (a.out & S)) & high); };
-      const int hit = __popcll(__ballot(lane < n && in_block(at))) + __popcll(__ballot(rest && in_block(at2)));
-      overs += hit > (n <= 64 ? kListMax : kListMax / 3);
+      const int hit = __popcll(__ballot(lane < n && !(((at.in & ~S) | (at.out & S)) & high)));
+      overs += n > 64 || hit > kListMax;     // past 64 the pair is walked
     }
     n_over += overs;
     if (n <= rows && lane < n) leaf[(int64_t)lane * pairs + g] = Reach{at.in, at.out, value[at.node]};
@@ -288,7 +285,7 @@ __device__ __forceinline__ void build_lists(const Node* __restrict__ prep, const
     row[NK + 1] = (uint32_t)root;
     return;
   }
-  if (all > 0) {                 // walk
+  if (all > kReachMax) {         // walk
     row[NK] = NK + 1;
     row[NK + 1] = (uint32_t)root;
     return;

@@ -108,16 +108,21 @@ def test_cost_where_lists_overflow(d, n_trees, depth, n_bg, bound):
     assert us * 1e3 < bound * n_trees * n_bg * depth * 2 ** d
 
 
-def test_blocks_list_where_the_lists_find_no_room():
-    """A forest made for so many backgrounds that it keeps no lists."""
-    d = 12
-    say("[case] forest without lists")
+@pytest.mark.parametrize("d", [12, 17])
+@pytest.mark.parametrize("n_trees,max_bg", [(60, 4096), (120, 600)])
+def test_blocks_list_where_the_lists_find_no_room(n_trees, max_bg, d):
+    """Forests made for so many backgrounds that they keep no lists, or lists of
+    fewer than 64 leaves."""
+    say(f"[case] forest without lists d={d} trees={n_trees}")
     rng = np.random.default_rng(43)
-    forest = full_trees(d, 60, 6, rng)
-    x, bgs = rng.uniform(size=d), rng.uniform(size=(3, d))
-    for x, bgs in ((x, bgs), (np.ones(d), np.zeros((2, d)))):
-        got = gpu_values(d, forest, x, bgs, "f64", max_bg=4096)
-        assert np.array_equal(got, oracle.forest_values(d, *forest, x, bgs))
+    forest = full_trees(d, n_trees, 6, rng)
+    for x, bgs in ((rng.uniform(size=d), rng.uniform(size=(3, d))), (np.ones(d), np.zeros((2, d)))):
+        got = gpu_values(d, forest, x, bgs, "f64", max_bg=max_bg)
+        if d == 12:
+            assert np.array_equal(got, oracle.forest_values(d, *forest, x, bgs))
+            continue
+        for S in np.concatenate([rng.integers(0, 1 << d, size=16), [0, (1 << d) - 1]]):
+            assert got[S] == oracle.forest_value_at(int(S), d, *forest, x, bgs), int(S)
 
 
 # both sides of the lines between the kernels: plain walks (up to 32 loads, 12 at
