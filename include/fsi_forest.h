@@ -75,8 +75,8 @@ fsi_status fsi_forest_values(fsi_forest_t forest, const double* x_dev, int n_bg,
  * alpha_f (beta_f) = 1 if x (bg_b) passes every test on f of that path. Its
  * Moebius coefficients are +-value on the sets I u Q, I = {f: beta_f = 0},
  * Q a subset of {f: beta_f = 1, alpha_f = 0}, sign (-1)^|Q| (none if some f
- * in I has alpha_f = 0). One GPU thread per (background, root-to-leaf path)
- * adds value / n_bg at each of them.
+ * in I has alpha_f = 0). The GPU lists the reachable (background,
+ * root-to-leaf path) pairs and adds value / n_bg at each of their sets.
  *  a_dev: 2^d FP64 (device, caller-owned); zeroed by the call, then summed
  *         with FP64 atomics, so the result is not bitwise repeatable (equal
  *         to rounding).

@@ -660,19 +660,19 @@ bool walk_plain(int d, int64_t pairs, int depth) {
   return d < 20 ? pairs <= 4 || loads <= 32 : loads <= 12 >> std::min(d - 20, 4);
 }
 
-// Coalitions per thread of the wide kernel, 0 for the narrow one: eight from
-// d = 21 on (100 depth-6 trees 70 us against 82 with four; 200 at d = 20 101
-// against 90), four from d = 19, and the narrow kernel, which takes one workgroup per
-// CU and 64 coalitions, up to four rounds of them (50 depth-4 trees, 100
+// Coalitions per thread of the wide kernel, 0 for the narrow one: the most, up to
+// eight, that still give every CU four workgroups, what its LDS holds (100 depth-6
+// trees d = 21 70 us with eight, 82 with four; 200 d = 20 101 with eight, 90 with
+// four; 200 d = 19 73 with four, 69 with two, with no list that suffices 211 and 150;
+// d = 18 58 with two, 57 with one, 156 and 106). The narrow kernel takes one workgroup
+// per CU and 64 coalitions, up to four rounds of them (50 depth-4 trees, 100
 // backgrounds: d = 16 wide 818 us, narrow 445; d = 17 wide 831, narrow 844). Its
 // pipeline fills and drains in each round, so at two and four rounds (d = 15, 16)
 // it takes some pairs to be worth it (depth 6, d = 16: 16 trees narrow 29 us, wide 14,
 // 128 trees 43 and 34, where no list suffices 88 and 79; 64 such trees of depth
 // 10: 56 and 85. d = 15: 16 trees 20 and 14, 64 trees 23 and 24).
 int walk_kp(int d, int64_t pairs) {
-  if (d >= 21) return 8;
-  if (d >= 19) return 4;
-  if (d >= 18) return 2;
+  if (d >= 18) return 1 << std::min(d - 18, 3);
   return d >= 17 || (d >= 15 && pairs <= (d == 15 ? 16 : 64)) ? 1 : 0;
 }
 
