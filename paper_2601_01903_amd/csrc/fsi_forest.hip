@@ -354,8 +354,8 @@ __device__ __forceinline__ void match(LeafLists<NP, NK>& L, const LaneLists& ll,
 // Every thread owns KP coalitions, base + tid + j * kThreads. Pairs without a
 // list are walked, eight walks a thread at once where they follow each other
 // (d = 20, x and background apart everywhere: 20 depth-12 trees 614 us one walk at
-// a time and listed first, now 172, plain walks 178; 50 depth-10 trees 585, now
-// 340, 340).
+// a time and listed first, now 160, plain walks 179; 50 depth-10 trees 585, now
+// 309, 342).
 template <typename OutT, int KP>
 __global__ void __launch_bounds__(kThreads)
 walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value,
@@ -454,7 +454,7 @@ walk_wide_kernel(const Node* __restrict__ prep, const double* __restrict__ value
 // with the three parts in turns, 142 with a matching wave beside the adding
 // one, now 114. Where many pairs have no list, the waves walk instead (see
 // kWalkShare; 50 depth-12 trees, two backgrounds, d = 16, x and background apart
-// everywhere: 1240 us by the adding wave, 433 by a kernel of plain walks, now 107).
+// everywhere: 1240 us by the adding wave, 433 by a kernel of plain walks, now 102).
 constexpr int kNarrowPairs = 256;
 constexpr int kNarrowThreads = 768;
 constexpr int kAddWave = 4;        // waves 0-3 list, 8 idles, the other six match
